@@ -43,6 +43,7 @@ hipError_t launch_gather_out(const Dev& d, float* ox, float* oy, float* oz, int3
 hipError_t launch_draws(const uint32_t* ctr, long long n, unsigned long long key, uint32_t* out,
                         hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, long long n, uint32_t v, hipStream_t s);
+hipError_t launch_md_check(const Dev& d, hipStream_t s);
 hipError_t launch_md_init(const Dev& d, unsigned long long vseed, float cv, hipStream_t s);
 hipError_t launch_sqrt_rn(const float* in, float* out, long long n, hipStream_t s);
 hipError_t launch_gather_v(const Dev& d, float* ox, float* oy, float* oz, hipStream_t s);
@@ -757,8 +758,10 @@ int after_load(pr_sys* s) {
   s->d.kpar0 = 0;
   HIP_TRY(launch_identity(s->d, st));
   HIP_TRY(launch_classify(s->d, st));
+  if (s->d.md_theta > 0) HIP_TRY(launch_md_check(s->d, st));
   int e = sync_ctl(s);
   if (e) return e;
+  if (s->d.md_theta > 0) s->d.md_all = s->hctl->md_lone ? 1 : 0;
   s->steps_since_load = 0;
   if (s->hctl->err) {
     s->loaded = false;
@@ -1248,11 +1251,15 @@ int pr_sys_set_md(pr_sys* s, int32_t theta, double dt, double sig, double eps, d
       if (!e) e = s->arena.alloc(&a.vz, n);
     }
     if (!e) e = s->arena.alloc(&d.slot_of, n);
+    if (!e) e = s->arena.alloc(&d.md_n, n / (kThreads * kMdPer) + 1);
+    if (!e) e = s->arena.alloc(&d.md_vel, n);
+    if (!e) e = s->arena.alloc(&d.md_row, n * (size_t)d.B);
     if (e) {
       for (int q = 0; q < 2; ++q) d.set[q].vx = d.set[q].vy = d.set[q].vz = nullptr;
       d.slot_of = nullptr;
       return e;
     }
+    d.md_vec = d.B == 4 && (((uintptr_t)d.set[0].adj | (uintptr_t)d.set[1].adj) & 15u) == 0;
   }
   // the oracle's parameters, rounded to FP32 from double
   const double sc = std::pow(2.0, 1.0 / 6.0) * sig;
@@ -1266,7 +1273,10 @@ int pr_sys_set_md(pr_sys* s, int32_t theta, double dt, double sig, double eps, d
   d.md_e24 = (float)(24.0 * eps);
   const float cv = (float)std::sqrt(temp / 21845.0);
   HIP_TRY(launch_md_init(d, (unsigned long long)vseed, cv, s->stream));
-  return sync_ctl(s);
+  HIP_TRY(launch_md_check(d, s->stream));
+  if ((e = sync_ctl(s))) return e;
+  d.md_all = s->hctl->md_lone ? 1 : 0;
+  return PR_OK;
 }
 
 int pr_sys_read_velocities(pr_sys* s, float* vx, float* vy, float* vz) {

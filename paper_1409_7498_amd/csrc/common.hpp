@@ -42,6 +42,7 @@ constexpr int kTPass = 768;         // particles a sweep workgroup holds per pas
 constexpr int kQueue = 512;         // in-range pairs queued per pass
 constexpr int32_t kMaxParticles = 1 << 30;  // byte offsets of 4-byte fields fit in 32 bits
 constexpr int kMaxRules = 4;        // concurrent rules of one system
+constexpr int kMdPer = 4;           // particles per thread of the MD's kernels
 constexpr int kKinMaxState = 64;    // kinetics counters: states per call
 constexpr int kKinMaxBins = 256;    // kinetics counters: distance bins per call
 constexpr int kKinStride = 2 * kKinMaxState + kKinMaxBins;  // one slice of kinetics counters
@@ -64,6 +65,7 @@ struct Ctl {
   uint32_t stats_n0;   // counter-log index of the block's first step
   uint64_t log_n;      // rows appended to the bond log (may exceed capacity)
   uint32_t fovf_n[3];  // fused binning: A records beyond their bucket, by step mod 3
+  uint32_t md_lone;    // MD: some adjacency row names a particle whose own row is empty
 };
 
 struct RuleD {
@@ -184,6 +186,15 @@ struct Dev {
   int32_t md_theta;
   float md_dt, md_h, md_sc2, md_two_sc, md_sig, md_e24;
   int32_t* slot_of;
+  // the bonded particles of the current MD block, compact: their number per
+  // range of kThreads * kMdPer slots, velocities (w: the slot) and adjacency
+  // rows of compact indices; md_vec: the rows are read as 16-byte vectors (B =
+  // 4, aligned)
+  int32_t* md_n;
+  float4* md_vel;
+  int32_t* md_row;
+  int32_t md_vec;
+  int32_t md_all;      // every particle is taken as bonded (see k_md_check)
   int4 *wina, *wint;    // per slot, the winning pair as A / as T:
                         // (partner id, partner slot, rule, 0)
 };

@@ -2214,76 +2214,225 @@ __device__ __forceinline__ void multi_final_body(const Dev& d, int k, int w) {
 // ---------------------------------------------------------------------------
 // Bonded-force coupling: velocity Verlet with the mirror-LJ bond force over
 // the adjacency table (Sec. II D, Eq. (mirror LJ)), md_theta steps before each
-// reaction step.  Kernel m = 0 .. theta of reaction step k of a block: the
-// forces at the positions of parity (par0 + k + m) (partners found through
-// slot_of); m = 0 kicks half a step and drifts, 0 < m < theta completes the
-// previous step's second half kick, kicks and drifts, m = theta completes
-// the last one.  Drifted positions go to the other parity; for odd theta the
-// last kernel copies the positions over once more, so that every MD block
-// flips the buffers an even number of times and the reaction step finds them
-// in the parity its step number gives.  Every operation is FP32, rounded on
-// its own, in the order the oracle uses.
+// reaction step.  Every operation is FP32, rounded on its own, in the order
+// the oracle uses.  Only bonded particles feel a force, so
+//   k_md_free  takes a particle without bonds through all md_theta drifts in
+//              registers (one read and one write of its state instead of
+//              md_theta) and gathers the bonded ones into compact arrays, each
+//              workgroup's kThreads * kMdPer particles into their own range:
+//              position, velocity with the slot, and slot -> compact index.
+//              (One list for all, reserved by a global counter, serialised at
+//              its address: 116 us with one reservation per wavefront, 24-27
+//              with one per workgroup);
+//   k_md_sub   sub-step m = 0 .. theta over the compact arrays alone, one
+//              workgroup per range: m = 0 kicks half a step and drifts, 0 < m <
+//              theta completes the previous step's second half kick, kicks and
+//              drifts, m = theta completes the last one and writes the state
+//              back.  Sub-step 0 also turns the adjacency rows (ids) into rows
+//              of compact indices, so that a bond costs one 16-byte gather.
+// The compact positions ping-pong between the overflow record arrays and the
+// index map is the sort's rank array (both idle between the reaction steps).
+// The positions are read from and written back to the parity of the reaction
+// step.  Bound: k_md_free by HBM (64 bytes per particle at B = 4), k_md_sub by
+// its launch while few particles are bonded.  1,048,576 particles, ten MD
+// steps per reaction step, the first 32 reaction steps (up to 6% bonded): one
+// kernel over all particles per MD step took 11 x 15.5 us; k_md_free 18 us
+// and 11 x 4.6 us.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void k_md(Dev d, int k, int m) {
+__global__ __launch_bounds__(kThreads) void k_md_free(Dev d, int k) {
+  __shared__ int32_t s_slot[kThreads * kMdPer];  // the workgroup's bonded slots
+  __shared__ int s_n;
   const Ctl* c = d.ctl;
-  const uint32_t par = (c->par0 + (uint32_t)k + (uint32_t)m) & 1u;
+  const uint32_t par = (c->par0 + (uint32_t)k) & 1u;
   const Arr a = pick_set(d, c->set & 1u);
-  const float *X = pick(a.x, par), *Y = pick(a.y, par), *Z = pick(a.z, par);
-  float *XW = pick(a.x, par ^ 1u), *YW = pick(a.y, par ^ 1u), *ZW = pick(a.z, par ^ 1u);
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= d.n || read_err(c)) return;
-  const float xi = X[i], yi = Y[i], zi = Z[i];
-  float fx = 0.0f, fy = 0.0f, fz = 0.0f;
-  bool torn = false;
-  const int32_t* row = a.adj + (size_t)i * d.B;
-  for (int b = 0; b < d.B; ++b) {
-    const int32_t j = row[b];
-    if (j < 0) continue;
-    const int sj = d.slot_of[j];
-    const float dx = min_image(__fsub_rn(X[sj], xi), d.L, d.halfL);
-    const float dy = min_image(__fsub_rn(Y[sj], yi), d.L, d.halfL);
-    const float dz = min_image(__fsub_rn(Z[sj], zi), d.L, d.halfL);
-    const float r2 = __fadd_rn(__fadd_rn(__fmul_rn(dx, dx), __fmul_rn(dy, dy)), __fmul_rn(dz, dz));
-    if (!(r2 > d.md_sc2)) continue;  // no force up to sigma_c
-    const float r = sqrt_rn(r2);
-    const float sgap = __fsub_rn(d.md_two_sc, r);
-    if (!(sgap > 0.0f)) {
-      torn = true;
-      continue;
+  float *X = pick(a.x, par), *Y = pick(a.y, par), *Z = pick(a.z, par);
+  if (read_err(c)) return;
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
+  const int i0 = blockIdx.x * (kThreads * kMdPer) + threadIdx.x;
+  float x[kMdPer], y[kMdPer], z[kMdPer], vx[kMdPer], vy[kMdPer], vz[kMdPer];
+  bool bonded[kMdPer];
+#pragma unroll
+  for (int u = 0; u < kMdPer; ++u) {
+    const int i = i0 + u * kThreads;
+    bonded[u] = false;
+    if (i < d.n) {
+      if (d.md_all) {
+        bonded[u] = true;
+      } else if (d.md_vec) {
+        const int4 r = ((const int4*)a.adj)[i];
+        bonded[u] = r.x >= 0 || r.y >= 0 || r.z >= 0 || r.w >= 0;
+      } else {
+        const int32_t* row = a.adj + (size_t)i * d.B;
+        for (int b = 0; b < d.B; ++b) bonded[u] |= row[b] >= 0;
+      }
+      x[u] = X[i];
+      y[u] = Y[i];
+      z[u] = Z[i];
+      vx[u] = a.vx[i];
+      vy[u] = a.vy[i];
+      vz[u] = a.vz[i];
     }
-    const float q = __fdiv_rn(d.md_sig, sgap);
-    const float q2 = __fmul_rn(q, q);
-    const float q6 = __fmul_rn(__fmul_rn(q2, q2), q2);
-    const float q12 = __fmul_rn(q6, q6);
-    const float cf =
-        __fdiv_rn(__fdiv_rn(__fmul_rn(d.md_e24, __fsub_rn(__fadd_rn(q12, q12), q6)), sgap), r);
-    fx = __fadd_rn(fx, __fmul_rn(cf, dx));
-    fy = __fadd_rn(fy, __fmul_rn(cf, dy));
-    fz = __fadd_rn(fz, __fmul_rn(cf, dz));
   }
-  if (torn) set_err(d.ctl, PR_EINVAL);
-  float vx = a.vx[i], vy = a.vy[i], vz = a.vz[i];
+#pragma unroll
+  for (int u = 0; u < kMdPer; ++u) {
+    const unsigned long long m = __ballot(bonded[u]);
+    if (m) {  // the wavefront's bonded lanes, in lane order
+      int at = 0;
+      if (__lane_id() == 0) at = atomicAdd(&s_n, (int)__popcll(m));
+      at = __builtin_amdgcn_readlane(at, 0);
+      if (bonded[u]) s_slot[at + (int)lanes_below(m)] = i0 + u * kThreads;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kMdPer; ++u) {
+    const int i = i0 + u * kThreads;
+    if (i >= d.n || bonded[u]) continue;
+    // the half kicks of a force-free particle add +0 (which turns -0 into +0)
+    const float wx = __fadd_rn(vx[u], 0.0f), wy = __fadd_rn(vy[u], 0.0f),
+                wz = __fadd_rn(vz[u], 0.0f);
+    const float sx = __fmul_rn(d.md_dt, wx), sy = __fmul_rn(d.md_dt, wy),
+                sz = __fmul_rn(d.md_dt, wz);
+    float px = x[u], py = y[u], pz = z[u];
+    for (int t = 0; t < d.md_theta; ++t) {
+      px = wrap_box(__fadd_rn(px, sx), d.L);
+      py = wrap_box(__fadd_rn(py, sy), d.L);
+      pz = wrap_box(__fadd_rn(pz, sz), d.L);
+    }
+    X[i] = px;
+    Y[i] = py;
+    Z[i] = pz;
+    a.vx[i] = wx;
+    a.vy[i] = wy;
+    a.vz[i] = wz;
+  }
+  __syncthreads();
+  const int nb = s_n, q0 = blockIdx.x * (kThreads * kMdPer);
+  if (threadIdx.x == 0) d.md_n[blockIdx.x] = nb;
+  for (int e = threadIdx.x; e < nb; e += kThreads) {
+    const int i = s_slot[e], q = q0 + e;
+    d.rank[i] = q;
+    d.ovf[0][q] = make_float4(X[i], Y[i], Z[i], 0.0f);
+    d.md_vel[q] = make_float4(a.vx[i], a.vy[i], a.vz[i], __int_as_float(i));
+  }
+}
+
+// The mirror-LJ force of the partner at o on the particle at p, added to f;
+// false when the bond is stretched to 2 sigma_c or beyond.
+__device__ __forceinline__ bool md_bond(const Dev& d, float4 p, float4 o, float& fx, float& fy,
+                                        float& fz) {
+  const float dx = min_image(__fsub_rn(o.x, p.x), d.L, d.halfL);
+  const float dy = min_image(__fsub_rn(o.y, p.y), d.L, d.halfL);
+  const float dz = min_image(__fsub_rn(o.z, p.z), d.L, d.halfL);
+  const float r2 = __fadd_rn(__fadd_rn(__fmul_rn(dx, dx), __fmul_rn(dy, dy)), __fmul_rn(dz, dz));
+  if (!(r2 > d.md_sc2)) return true;  // no force up to sigma_c
+  const float r = sqrt_rn(r2);
+  const float sgap = __fsub_rn(d.md_two_sc, r);
+  if (!(sgap > 0.0f)) return false;
+  const float q = __fdiv_rn(d.md_sig, sgap);
+  const float q2 = __fmul_rn(q, q);
+  const float q6 = __fmul_rn(__fmul_rn(q2, q2), q2);
+  const float q12 = __fmul_rn(q6, q6);
+  const float cf =
+      __fdiv_rn(__fdiv_rn(__fmul_rn(d.md_e24, __fsub_rn(__fadd_rn(q12, q12), q6)), sgap), r);
+  fx = __fadd_rn(fx, __fmul_rn(cf, dx));
+  fy = __fadd_rn(fy, __fmul_rn(cf, dy));
+  fz = __fadd_rn(fz, __fmul_rn(cf, dz));
+  return true;
+}
+
+// The compact index of partner id j (-1: none).
+__device__ __forceinline__ int32_t md_index(const Dev& d, int32_t j) {
+  return j >= 0 ? d.rank[d.slot_of[j]] : -1;
+}
+
+__global__ __launch_bounds__(kThreads) void k_md_sub(Dev d, int k, int m) {
+  const Ctl* c = d.ctl;
+  const uint32_t par = (c->par0 + (uint32_t)k) & 1u;
+  const int nb = d.md_n[blockIdx.x], q0 = blockIdx.x * (kThreads * kMdPer), B = d.B;
+  if (read_err(c)) return;
+  const Arr a = pick_set(d, c->set & 1u);
+  const float4* P = pick(d.ovf, (uint32_t)m);
+  float4* PW = pick(d.ovf, (uint32_t)m ^ 1u);
   const float h = d.md_h;
-  if (m > 0) {  // the second half kick of the previous MD step
-    vx = __fadd_rn(vx, __fmul_rn(h, fx));
-    vy = __fadd_rn(vy, __fmul_rn(h, fy));
-    vz = __fadd_rn(vz, __fmul_rn(h, fz));
+  for (int e = threadIdx.x; e < nb; e += kThreads) {
+    const int q = q0 + e;
+    const float4 p = P[q], v4 = d.md_vel[q];
+    const int slot = __float_as_int(v4.w);
+    float fx = 0.0f, fy = 0.0f, fz = 0.0f;
+    bool ok = true;
+    if (d.md_vec) {  // the four partners gathered together, then taken in row order
+      int4 j;
+      if (m == 0) {
+        j = ((const int4*)a.adj)[slot];
+        j = make_int4(md_index(d, j.x), md_index(d, j.y), md_index(d, j.z), md_index(d, j.w));
+        ((int4*)d.md_row)[q] = j;
+      } else {
+        j = ((const int4*)d.md_row)[q];
+      }
+      float4 o0 = p, o1 = p, o2 = p, o3 = p;  // at distance 0: no force
+      if (j.x >= 0) o0 = P[j.x];
+      if (j.y >= 0) o1 = P[j.y];
+      if (j.z >= 0) o2 = P[j.z];
+      if (j.w >= 0) o3 = P[j.w];
+      ok = md_bond(d, p, o0, fx, fy, fz);
+      ok = md_bond(d, p, o1, fx, fy, fz) && ok;
+      ok = md_bond(d, p, o2, fx, fy, fz) && ok;
+      ok = md_bond(d, p, o3, fx, fy, fz) && ok;
+    } else {
+      int32_t* row = d.md_row + (size_t)q * B;
+      for (int b = 0; b < B; ++b) {
+        int32_t j;
+        if (m == 0) {
+          j = md_index(d, a.adj[(size_t)slot * B + b]);
+          row[b] = j;
+        } else {
+          j = row[b];
+        }
+        if (j >= 0) ok = md_bond(d, p, P[j], fx, fy, fz) && ok;
+      }
+    }
+    if (!ok) set_err(d.ctl, PR_EINVAL);
+    float vx = v4.x, vy = v4.y, vz = v4.z;
+    if (m > 0) {  // the second half kick of the previous MD step
+      vx = __fadd_rn(vx, __fmul_rn(h, fx));
+      vy = __fadd_rn(vy, __fmul_rn(h, fy));
+      vz = __fadd_rn(vz, __fmul_rn(h, fz));
+    }
+    if (m < d.md_theta) {  // the first half kick and the drift of MD step m
+      vx = __fadd_rn(vx, __fmul_rn(h, fx));
+      vy = __fadd_rn(vy, __fmul_rn(h, fy));
+      vz = __fadd_rn(vz, __fmul_rn(h, fz));
+      PW[q] = make_float4(wrap_box(__fadd_rn(p.x, __fmul_rn(d.md_dt, vx)), d.L),
+                          wrap_box(__fadd_rn(p.y, __fmul_rn(d.md_dt, vy)), d.L),
+                          wrap_box(__fadd_rn(p.z, __fmul_rn(d.md_dt, vz)), d.L), 0.0f);
+      d.md_vel[q] = make_float4(vx, vy, vz, v4.w);
+    } else {
+      pick(a.x, par)[slot] = p.x;
+      pick(a.y, par)[slot] = p.y;
+      pick(a.z, par)[slot] = p.z;
+      a.vx[slot] = vx;
+      a.vy[slot] = vy;
+      a.vz[slot] = vz;
+    }
   }
-  if (m < d.md_theta) {  // the first half kick and the drift of MD step m
-    vx = __fadd_rn(vx, __fmul_rn(h, fx));
-    vy = __fadd_rn(vy, __fmul_rn(h, fy));
-    vz = __fadd_rn(vz, __fmul_rn(h, fz));
-    XW[i] = wrap_box(__fadd_rn(xi, __fmul_rn(d.md_dt, vx)), d.L);
-    YW[i] = wrap_box(__fadd_rn(yi, __fmul_rn(d.md_dt, vy)), d.L);
-    ZW[i] = wrap_box(__fadd_rn(zi, __fmul_rn(d.md_dt, vz)), d.L);
-  } else if (d.md_theta & 1) {  // odd theta: one more flip of the buffers
-    XW[i] = xi;
-    YW[i] = yi;
-    ZW[i] = zi;
+}
+
+// Whether some row names a particle whose own row is empty (only a loaded
+// configuration can: a bond fills both rows, or finds one of them full): then
+// ctl->md_lone is set, and every particle is taken as bonded (Dev::md_all).
+__global__ __launch_bounds__(kThreads) void k_md_check(Dev d) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= d.n) return;
+  const int32_t* adj = pick_set(d, d.ctl->set & 1u).adj;
+  for (int b = 0; b < d.B; ++b) {
+    const int32_t j = adj[(size_t)i * d.B + b];
+    if (j < 0) continue;
+    const int32_t* row = adj + (size_t)d.slot_of[j] * d.B;
+    bool empty = true;
+    for (int e = 0; e < d.B; ++e) empty &= row[e] < 0;
+    if (empty) d.ctl->md_lone = 1u;
   }
-  a.vx[i] = vx;
-  a.vy[i] = vy;
-  a.vz[i] = vz;
 }
 
 // Initial velocities: per component the Irwin-Hall(4) offset of the bytes of
@@ -3005,8 +3154,11 @@ hipError_t launch_generate(const Dev& d, int kind, unsigned long long gseed, flo
 // which stamps the two events at the kernel's own start and end.
 hipError_t launch_step(const Dev& d, int k, hipStream_t s, hipEvent_t ev_sweep0,
                        hipEvent_t ev_sweep1) {
-  for (int m = 0; d.md_theta > 0 && m <= d.md_theta; ++m)
-    k_md<<<blocks_for(d.n, kThreads), kThreads, 0, s>>>(d, k, m);
+  if (d.md_theta > 0) {
+    const int g = blocks_for(d.n, kThreads * kMdPer);
+    k_md_free<<<g, kThreads, 0, s>>>(d, k);
+    for (int m = 0; m <= d.md_theta; ++m) k_md_sub<<<g, kThreads, 0, s>>>(d, k, m);
+  }
   if (d.fuse) {  // two kernels: the sweep (with the closing of step k - 1), the resolve
     // the sweep, with the closing of step k - 1 in trailing workgroups (edges
     // above kOneCellBrick stage two region cells per thread)
@@ -3207,6 +3359,13 @@ hipError_t launch_kinetics(const Dev& d, int nstate, int nbins, const float* e2,
     k_kin_pairs<<<g, kThreads, 0, s>>>(dn, nstate, nbins, e2, pairs, hist);
   k_kin_reset<<<std::min(blocks_for(d.ncell, kThreads), 1024), kThreads, 0, s>>>(dn);
   k_kin_sum<<<1, kThreads, 0, s>>>(pop);  // pop is the first slice's start
+  return hipGetLastError();
+}
+
+// ctl->md_lone of the current configuration (k_md_check); slot_of is valid.
+hipError_t launch_md_check(const Dev& d, hipStream_t s) {
+  k_fill_u32<<<1, kThreads, 0, s>>>(&d.ctl->md_lone, 1, 0u);
+  if (d.n > 0) k_md_check<<<blocks_for(d.n, kThreads), kThreads, 0, s>>>(d);
   return hipGetLastError();
 }
 
