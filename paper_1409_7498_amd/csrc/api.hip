@@ -612,15 +612,15 @@ struct pr_sys {
   uint32_t rec_step = 0;
   float rec_jit = 0.0f;
   // captured segments of steps: (a sort when one is due and) K steps and the
-  // block end, keyed by what the captured kernels hold
+  // block end, keyed by the Dev they were captured with (all that the captured
+  // kernels hold: pointers, geometry, rule, jitter scale, storage and binning
+  // mode, MD parameters, parity origin), so that they outlive a load: a loaded
+  // system replays the segments of the runs before it
   struct Seg {
     hipGraphExec_t gexec = nullptr;
     int32_t steps = 0;
     bool sort = false;
-    float jit = -1.0f;
-    long long part = 0;
-    int32_t fuse = 0;
-    uint32_t kpar0 = 0;  // parity origin the segment was captured at
+    Dev d{};
     uint64_t used = 0;
   };
   std::vector<Seg> segs;
@@ -749,7 +749,6 @@ void fuse_after_run(pr_sys* s, uint32_t first_step, uint32_t n_steps) {
 int after_load(pr_sys* s) {
   hipStream_t st = s->stream;
   set_dense(s);
-  drop_graph(s);
   s->steps_since_sort = 0;
   // parity 0 after the reset: both cell-count buffers start cleared
   HIP_TRY(hipMemsetAsync(s->d.cnt[0], 0, sizeof(uint32_t) * (size_t)s->d.ncell, st));
@@ -836,10 +835,8 @@ void after_segment(pr_sys* s, int32_t K, bool with_sort) {
 // The captured graph of a segment of K steps (with a sort first when
 // with_sort), capturing it on the private stream if it is not cached.
 int segment_graph(pr_sys* s, int32_t K, bool with_sort, hipGraphExec_t* out) {
-  const long long part = (long long)(size_t)s->d.part;
   for (pr_sys::Seg& g : s->segs)
-    if (g.steps == K && g.sort == with_sort && g.jit == s->d.jit_c && g.part == part &&
-        g.fuse == s->d.fuse && g.kpar0 == s->d.kpar0) {
+    if (g.steps == K && g.sort == with_sort && std::memcmp(&g.d, &s->d, sizeof(Dev)) == 0) {
       g.used = ++s->seg_clock;
       *out = g.gexec;
       return PR_OK;
@@ -876,12 +873,9 @@ int segment_graph(pr_sys* s, int32_t K, bool with_sort, hipGraphExec_t* out) {
   seg.gexec = ge;
   seg.steps = K;
   seg.sort = with_sort;
-  seg.jit = s->d.jit_c;
-  seg.part = part;
-  seg.fuse = s->d.fuse;
-  seg.kpar0 = s->d.kpar0;
   seg.used = ++s->seg_clock;
   s->segs.push_back(seg);
+  std::memcpy((void*)&s->segs.back().d, (const void*)&s->d, sizeof(Dev));
   *out = ge;
   return PR_OK;
 }
@@ -1226,7 +1220,6 @@ int pr_sys_set_md(pr_sys* s, int32_t theta, double dt, double sig, double eps, d
   int e = check_sys(s, true);
   if (e) return e;
   if (theta < 0 || theta > 100000) return fail(PR_EINVAL, "theta=%d", theta);
-  drop_graph(s);
   // the next run sorts first: fused binning (the MD moves the particles
   // between reaction steps) is taken up or left there
   if (s->d.sorted && s->sort_period > 0)
