@@ -166,7 +166,8 @@ int pr_react_step_multi(int32_t n, float L, const float* x, const float* y, cons
  * fixed region of device memory per GPU (24 MiB, a file-scope device array
  * of the library, held until the process ends).  n is limited to 32768
  * particles (PR_EINVAL beyond, with nothing written); every such call on one
- * GPU shares the region and clears what it needs at its start.  Calls on one
+ * GPU shares the region, at fixed places, and leaves it as the next one needs
+ * it (the first call, and one after a HIP error, clears it at its start).  Calls on one
  * GPU are serialised by the library for the duration of the call (it
  * synchronises stream before returning); launches that other code makes into
  * the region concurrently would race.  Synchronises stream. */

@@ -35,7 +35,7 @@ hipError_t launch_generate(const Dev& d, int kind, unsigned long long gseed, flo
 hipError_t launch_step(const Dev& d, int k, hipStream_t s, hipEvent_t ev_sweep0,
                        hipEvent_t ev_sweep1);
 hipError_t launch_block_end(const Dev& d, int K, hipStream_t s);
-hipError_t launch_single_end(const Dev& d, hipStream_t s);
+hipError_t launch_single(const Dev& d, uint32_t step, uint32_t par, SingleOut* out, hipStream_t s);
 hipError_t launch_sort(const Dev& d, hipStream_t s);
 hipError_t log_order(int32_t* log, int64_t n, hipStream_t s);
 hipError_t launch_gather_out(const Dev& d, float* ox, float* oy, float* oz, int32_t* otyp,
@@ -139,6 +139,7 @@ void set_geometry(Dev& d, int32_t n, float L, int32_t B, const pr_rule* r, uint6
   while (nc > 1 && nc * nc * nc > cell_cap) --nc;
   d.nc = (int32_t)nc;
   d.ncell = (int32_t)(nc * nc * nc);
+  d.ncell_clear = d.ncell;
   d.inv_w = (float)((double)nc / (double)L);
   d.thresh = threshold(r->p);
   d.seed = seed;
@@ -288,22 +289,27 @@ int alloc_scratch(Arena& a, Dev& d, int32_t n, int32_t nwg, hipStream_t s) {
   return PR_OK;
 }
 
+// What one stateless step leaves for the next on the same scratch: its sweep
+// cleared the counts of the call before it (the calls alternate between the
+// two count buffers), its own are cleared by the next one.  clean = false (the
+// scratch is new, or a call failed midway): everything is cleared first.
+struct SingleState {
+  bool clean = false;
+  uint32_t par = 0;
+  int32_t prev_ncell = 0;
+};
+
 // Per-device workspace of the stateless single step, grown on demand.
 struct Workspace {
   Arena arena;
   Dev d{};
   int32_t n = -1, ncell = -1;
-  int32_t* part = nullptr;
-  int32_t ngroups = 0;
-  int32_t* log = nullptr;
   uint8_t* role = nullptr;
-  unsigned long long* sortbuf = nullptr;
-  Ctl* hctl = nullptr;  // pinned host copies
-  int32_t* hpart = nullptr;
-  bool multi = false;   // holds the arrays of several concurrent rules
+  SingleState st;
+  SingleOut* hout = nullptr;  // pinned host memory, written by the step's last kernel
+  bool multi = false;         // holds the arrays of several concurrent rules
   ~Workspace() {
-    if (hctl) (void)hipHostFree(hctl);
-    if (hpart) (void)hipHostFree(hpart);
+    if (hout) (void)hipHostFree(hout);
   }
 };
 
@@ -384,30 +390,36 @@ void bind_single(Dev& d, const Dev& geo, float* x, float* y, float* z, int32_t* 
   d.bonds = bonds;
   d.bonds_cap = cap;
   d.bonds_rule = 0;
-  d.log_cap = (int64_t)geo.n / 2 + 1;
-  d.part_cap = 1;
-  d.ngroups = (d.nwg_sweep + kGroup - 1) / kGroup;
 }
 
-// The launches of one stateless step (count buffers already cleared), the
-// read-back of its control block and counters into hctl / hpart (host
-// memory of d.ngroups * kPart words) and the results.
-int single_step(const Dev& d, uint32_t step, hipStream_t s, Ctl* hctl, int32_t* hpart,
-                int32_t* n_bonds, pr_stats* st) {
-  HIP_TRY(launch_ctl_reset(d.ctl, step, 1, s));
-  HIP_TRY(launch_classify(d, s));
-  HIP_TRY(launch_step(d, 0, s, nullptr, nullptr));
-  HIP_TRY(launch_single_end(d, s));
-  HIP_TRY(hipMemcpyAsync(hctl, d.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(hpart, d.part, sizeof(int32_t) * d.ngroups * kPart,
-                         hipMemcpyDeviceToHost, s));
+// One stateless step on scratch in state ss (sized for n_max particles and
+// ncell_max cells): its launches, then the results from hout (out: where the
+// device writes them, pinned host memory when out == hout, else device memory
+// copied to hout).
+int single_step(Dev& d, SingleState& ss, int32_t n_max, int32_t ncell_max, uint32_t step,
+                hipStream_t s, SingleOut* out, SingleOut* hout, int32_t* n_bonds, pr_stats* st) {
+  if (!ss.clean) {
+    for (int p = 0; p < 2; ++p) HIP_TRY(launch_fill_u32(d.cnt[p], ncell_max, 0u, s));
+    HIP_TRY(launch_fill_u32((uint32_t*)d.slotA, 2LL * n_max, 0xFFFFFFFFu, s));
+    HIP_TRY(launch_fill_u32((uint32_t*)d.tflag, n_max / 4, 0u, s));
+    HIP_TRY(launch_fill_u32((uint32_t*)d.ctl, sizeof(Ctl) / 4, 0u, s));
+    ss.par = 0;
+    ss.prev_ncell = 0;
+  }
+  ss.clean = false;
+  d.ncell_clear = ss.prev_ncell;
+  d.kpar0 = ss.par;
+  HIP_TRY(launch_single(d, step, ss.par, out, s));
+  if (out != hout)
+    HIP_TRY(hipMemcpyAsync(hout, out, sizeof(SingleOut), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
-  const Ctl c = *hctl;
-  if (c.err) return fail(c.err, "invalid particle position (NaN or outside [0, L))");
-  *n_bonds = (int32_t)c.log_n;
-  long long h[kPart] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int g = 0; g < d.ngroups; ++g)
-    for (int q = 0; q < kPart; ++q) h[q] += hpart[g * kPart + q];
+  ss.clean = true;
+  ss.par ^= 1u;
+  ss.prev_ncell = d.ncell;
+  if (hout->err) return fail(hout->err, "invalid particle position (NaN or outside [0, L))");
+  *n_bonds = hout->n_bonds;
+  long long h[kPart];
+  for (int q = 0; q < kPart; ++q) h[q] = hout->sum[q];
   if (st) *st = stats_of(h, d.rule.policy);
   if (h[7] > 0) return fail(PR_ECAP, "%lld adjacency appends found a full row", h[7]);
   return PR_OK;
@@ -425,26 +437,32 @@ std::mutex g_scratch_mu[kScratchMaxDev];  // one call at a time per device
 char* g_scratch_ptr[kScratchMaxDev] = {};
 std::mutex g_scratch_init_mu;
 
-// Carves the scratch of a single step of up to n particles and ncell cells
-// out of arena a (the same buffers pr_react_step's workspace allocates).
-int carve_single(Arena& a, Dev& d, int32_t n, uint8_t** role) {
-  int e = alloc_scratch(a, d, n, sweep_blocks(n), nullptr);
-  if (e) return e;
+SingleState g_scratch_state[kScratchMaxDev];
+
+// Bonds of a stateless step beyond LDS, a power of two.
+size_t sort_keys(int32_t n) {
   size_t n2 = 1;
   while (n2 < (size_t)n / 2 + 1) n2 <<= 1;
-  const int ngroups = (sweep_blocks(n) + kGroup - 1) / kGroup;
-  if ((e = a.alloc(&d.part, (size_t)ngroups * kPart)) ||
-      (e = a.alloc(&d.log, 3 * ((size_t)n / 2 + 1))) || (e = a.alloc(role, (size_t)n)) ||
-      (e = a.alloc(&d.sortbuf, n2)))
+  return n2;
+}
+
+// Carves the scratch of single steps of up to kScratchMaxN particles (and as
+// many cells as such a step can have) out of arena a: the same buffers
+// pr_react_step's workspace allocates, at the same places for every call, so
+// that a call finds what the one before it left cleared.
+int carve_single(Arena& a, Dev& d, uint8_t** role, SingleOut** out) {
+  constexpr int32_t n = kScratchMaxN;
+  d.nrules = 1;
+  d.ncell = 2 * n;
+  int e = alloc_scratch(a, d, n, sweep_blocks(n), nullptr);
+  if (e) return e;
+  if ((e = a.alloc(role, (size_t)n)) || (e = a.alloc(&d.sortbuf, sort_keys(n))) ||
+      (e = a.alloc(out, 1)))
     return e;
   return PR_OK;
 }
 
 }  // namespace
-
-extern "C" {
-
-}  // extern "C"
 
 namespace {
 
@@ -475,39 +493,32 @@ int react_step_impl(int32_t n, float L, const float* x, const float* y, const fl
     ws = new Workspace();
     ws->d = geo;
     ws->d.nrules = multi ? 2 : 1;  // allocation of the several-rule arrays
-    const int32_t n_alloc = std::max(n, 1024);
+    const int32_t n_alloc = (std::max(n, 1024) + 3) & ~3;  // T flags are cleared by words
     if ((e = alloc_scratch(ws->arena, ws->d, n_alloc, sweep_blocks(n_alloc), s))) {
       delete ws;
       ws = nullptr;
       return e;
     }
     ws->multi = multi;
-    size_t n2 = 1;
-    while (n2 < (size_t)n_alloc / 2 + 1) n2 <<= 1;
-    ws->ngroups = (sweep_blocks(n_alloc) + kGroup - 1) / kGroup;
-    if ((e = ws->arena.alloc(&ws->part, (size_t)ws->ngroups * kPart)) ||
-        (e = ws->arena.alloc(&ws->log, 3 * ((size_t)n_alloc / 2 + 1))) ||
-        (e = ws->arena.alloc(&ws->role, (size_t)n_alloc)) ||
-        (e = ws->arena.alloc(&ws->sortbuf, n2)))
+    if ((e = ws->arena.alloc(&ws->role, (size_t)n_alloc)) ||
+        (e = ws->arena.alloc(&ws->d.sortbuf, sort_keys(n_alloc)))) {
+      delete ws;
+      ws = nullptr;
       return e;
-    HIP_TRY(hipHostMalloc((void**)&ws->hctl, sizeof(Ctl)));
-    HIP_TRY(hipHostMalloc((void**)&ws->hpart, sizeof(int32_t) * ws->ngroups * kPart));
+    }
+    if (hipHostMalloc((void**)&ws->hout, sizeof(SingleOut)) != hipSuccess) {
+      delete ws;
+      ws = nullptr;
+      return fail(PR_ENOMEM, "hipHostMalloc failed");
+    }
     ws->n = n_alloc;
     ws->ncell = geo.ncell;
   }
   Dev d = ws->d;  // scratch pointers
-  d.log = ws->log;
-  d.sortbuf = ws->sortbuf;
-  d.part = ws->part;
   bind_single(d, geo, const_cast<float*>(x), const_cast<float*>(y), const_cast<float*>(z),
               const_cast<int32_t*>(type), state, adj, ws->role, bonds, cap);
   d.bonds_rule = triples ? 1 : 0;
-  // The workspace serves calls of any box size: a previous call may have left
-  // counts in cells beyond this call's grid, so both count buffers are cleared
-  // over their whole allocation (each step only clears the cells it uses).
-  HIP_TRY(hipMemsetAsync(d.cnt[0], 0, sizeof(uint32_t) * (size_t)ws->ncell, s));
-  HIP_TRY(hipMemsetAsync(d.cnt[1], 0, sizeof(uint32_t) * (size_t)ws->ncell, s));
-  return single_step(d, step, s, ws->hctl, ws->hpart, n_bonds, st);
+  return single_step(d, ws->st, ws->n, ws->ncell, step, s, ws->hout, ws->hout, n_bonds, st);
 }
 
 }  // namespace
@@ -542,14 +553,6 @@ int pr_react_step_noalloc(int32_t n, float L, const float* x, const float* y, co
                 kScratchMaxN);
   Dev geo{};
   set_geometry(geo, n, L, B, rule, seed, kDefaultBrick);
-  Arena dry;
-  dry.dry = true;
-  uint8_t* role = nullptr;
-  Dev dd = geo;
-  if ((e = carve_single(dry, dd, std::max(n, 1), &role))) return e;
-  if (dry.bytes > kScratchBytes)
-    return fail(PR_EINVAL, "n=%d, %d cells: %zu bytes of scratch, the allocation-free step "
-                "holds %zu", n, geo.ncell, dry.bytes, kScratchBytes);
   *n_bonds = 0;
   if (st) std::memset(st, 0, sizeof *st);
   if (n == 0) return PR_OK;
@@ -570,18 +573,14 @@ int pr_react_step_noalloc(int32_t n, float L, const float* x, const float* y, co
   carve.base = g_scratch_ptr[dev];
   carve.cap = kScratchBytes;
   Dev d = geo;
-  if ((e = carve_single(carve, d, n, &role))) return e;
+  uint8_t* role = nullptr;
+  SingleOut* out = nullptr;
+  if ((e = carve_single(carve, d, &role, &out))) return e;
   bind_single(d, geo, const_cast<float*>(x), const_cast<float*>(y), const_cast<float*>(z),
               const_cast<int32_t*>(type), state, adj, role, bonds, cap);
-  // the region keeps the previous call's contents: clear what the kernels
-  // expect empty (cell counts, A keys, T flags) with fill kernels
-  HIP_TRY(launch_fill_u32(d.cnt[0], d.ncell, 0u, s));
-  HIP_TRY(launch_fill_u32(d.cnt[1], d.ncell, 0u, s));
-  HIP_TRY(launch_fill_u32((uint32_t*)d.slotA, 2LL * n, 0xFFFFFFFFu, s));
-  HIP_TRY(launch_fill_u32((uint32_t*)d.tflag, ((long long)n + 3) / 4, 0u, s));
-  Ctl hctl{};
-  int32_t hpart[((kScratchMaxN + kThreads - 1) / kThreads + kGroup - 1) / kGroup * kPart];
-  return single_step(d, step, s, &hctl, hpart, n_bonds, st);
+  SingleOut hout;
+  return single_step(d, g_scratch_state[dev], kScratchMaxN, 2 * kScratchMaxN, step, s, out, &hout,
+                     n_bonds, st);
 }
 
 }  // extern "C"

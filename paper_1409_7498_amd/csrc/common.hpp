@@ -68,6 +68,13 @@ struct Ctl {
   uint32_t md_lone;    // MD: some adjacency row names a particle whose own row is empty
 };
 
+// What a stateless step reports to the host: the device error, the bonds and
+// the kPart sums of the sweep workgroups' counters.
+struct SingleOut {
+  int32_t err, n_bonds;
+  int64_t sum[kPart];
+};
+
 struct RuleD {
   int32_t type_a, a_min, a_max, d_a;
   int32_t type_t, t_min, t_max, d_t;
@@ -140,6 +147,9 @@ struct Dev {
   unsigned long long* sortbuf;  // stateless step: bonds beyond LDS
   Ctl* ctl;
   // geometry, rule, draws
+  // ncell_clear: cells of the other parity's counts the sweep clears (ncell, or
+  // those of the previous call's grid for the stateless step)
+  int32_t ncell_clear;
   int32_t n, B, nc, ncell, nwg_sweep, nwg_prep, ngroups;
   int32_t bs, nb, nbricks, sorted;  // brick edge (cells), bricks per side, total, storage sorted
   int32_t nd;                        // sort bins per brick, (bs + 1)^3 + 1

@@ -780,7 +780,7 @@ __device__ __forceinline__ void retain(const Dev& d, const Arr& a, uint32_t step
 // ---------------------------------------------------------------------------
 // k_sweep: every particle is re-jittered (resident systems) and written to
 // the other position buffer; T's test the step's A records at their new
-// positions.  kBrick = sorted storage: one workgroup per brick, the A records
+// positions.  Sorted storage: one workgroup per brick, the A records
 // of the brick and its halo (positions, ids, slots, adjacency rows) staged in
 // LDS, each region cell's by the thread that read its count, and the brick's
 // particles handled kTPass at a time.  A T whose 2x2x2 cell block lies in the staged region scans it as four
@@ -792,10 +792,9 @@ __device__ __forceinline__ void retain(const Dev& d, const Arr& a, uint32_t step
 // more in-range pairs than the registers hold, or whose pairs find the queue
 // full, in the staged records; in the global buckets particles that drifted
 // out of the staged region since the last sort, bricks whose region holds
-// more than kStageRecs records, steps with bucket overflow, and all T's of
-// kBrick = false (kThreads consecutive slots per workgroup).  A deferred T
+// more than kStageRecs records and steps with bucket overflow.  A deferred T
 // enters the queue with none of its pairs, so every pair is drawn exactly
-// once.
+// once.  (Unsorted storage: dense_sweep_body.)
 // ---------------------------------------------------------------------------
 // One particle of a sweep pass, loaded with coalesced SoA reads.
 struct Part {
@@ -803,9 +802,6 @@ struct Part {
   float x, y, z;
 };
 
-// Sorted storage always carries the id array; the unsorted mode may run on
-// caller arrays without one (the slot is the id).
-template <bool kBrick>
 __device__ __forceinline__ Part load_part(const Arr& a, const float* X, const float* Y,
                                           const float* Z, int slot, int s1) {
   Part q{kRoleNone, 0, 0.0f, 0.0f, 0.0f};
@@ -817,7 +813,7 @@ __device__ __forceinline__ Part load_part(const Arr& a, const float* X, const fl
     q.x = *(const float*)((const char*)X + bo);
     q.y = *(const float*)((const char*)Y + bo);
     q.z = *(const float*)((const char*)Z + bo);
-    q.id = kBrick || a.id ? *(const int32_t*)((const char*)a.id + bo) : slot;
+    q.id = *(const int32_t*)((const char*)a.id + bo);
   }
   return q;
 }
@@ -840,19 +836,18 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long b) {
 // kOneCellBrick); else one, with the smaller tables.
 // kF: fused binning (the sweep bins the next step's A records; sorted storage).
 // kNt: the re-jittered positions stored non-temporally (Dev::nt_pos).
-template <bool kBrick, bool kTwo, bool kF = false, bool kNt = false>
+template <bool kTwo, bool kF = false, bool kNt = false>
 __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) {
-  static_assert(!kF || kBrick, "fused binning runs on sorted storage");
   constexpr int kCells = kTwo ? kStageCells : kStageCells1;  // region cells at most
-  constexpr int kPer = kBrick ? kTPass / kThreads : 1;
+  constexpr int kPer = kTPass / kThreads;
   constexpr int kTP = kPer * kThreads;
   constexpr uint32_t kQEmpty = 0xFFFFFFFFu;
-  __shared__ float4 s_rec[kBrick ? kStageRecs : 1];
-  __shared__ int4 s_radj[kBrick ? kStageRecs : 1];
-  __shared__ int32_t s_rsa[kBrick ? kStageRecs : 1];
-  __shared__ uint16_t s_off[kBrick ? kCells + 1 : 1];  // first record of a region cell
-  __shared__ uint32_t s_q[kBrick ? kQueue : 1];  // queued pair: local T | staged record << 16
-  __shared__ int32_t s_tid[kBrick ? kTP : 1];    // ids of the pass's T's
+  __shared__ float4 s_rec[kStageRecs];
+  __shared__ int4 s_radj[kStageRecs];
+  __shared__ int32_t s_rsa[kStageRecs];
+  __shared__ uint16_t s_off[kCells + 1];  // first record of a region cell
+  __shared__ uint32_t s_q[kQueue];  // queued pair: local T | staged record << 16
+  __shared__ int32_t s_tid[kTP];    // ids of the pass's T's
   __shared__ uint16_t s_def[kTP];            // deferred T's (local index in the pass)
   __shared__ int4 s_ent[kRetCap];
   __shared__ uint32_t s_ew2[kRetCap];
@@ -870,7 +865,7 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
   // staging at the top wave priority: the workgroups dispatched last stage
   // while the compute units already run the pass loops of the others, and
   // below those waves' priority their staging waits for issue slots
-  if (kBrick) __builtin_amdgcn_s_setprio(3);
+  __builtin_amdgcn_s_setprio(3);
   const Ctl* c = d.ctl;
   const StepInfo si = step_info(c, k);
   const uint32_t par = si.par, step = si.step;
@@ -883,7 +878,7 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
   const Buckets bk = step_buckets<kF>(d, par, step);
   const RetList rl{&s_ne, s_ent, s_ew2};
   int s0, s1;
-  range_of<kBrick>(d, w, s0, s1);
+  range_of<true>(d, w, s0, s1);
   int bx = 0, ex = 0, by = 0, ey = 0, bz = 0, ez = 0;
   bool staged = false, nowrap = false, plain_x = false, plain_y = false, plain_z = false;
   const int nc = d.nc;
@@ -900,78 +895,74 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
     cz -= cz >= nc ? nc : 0;
     return (cz * nc + cy) * nc + cx;
   };
-  if (kBrick) {
-    int bxc, byc;
-    const int bzc = div_nb(d, div_nb(d, w, bxc), byc);
-    region_dim(d, bxc, bx, ex);
-    region_dim(d, byc, by, ey);
-    region_dim(d, bzc, bz, ez);
-    // a region that does not wrap around the box and spans less than half of
-    // it: a difference of two positions in it is below L/2 in magnitude, and
-    // the minimum image leaves it unchanged
-    plain_x = d.nbricks > 1 && bx + ex <= nc && 2 * ex + 1 <= nc;
-    plain_y = d.nbricks > 1 && by + ey <= nc && 2 * ey + 1 <= nc;
-    plain_z = d.nbricks > 1 && bz + ez <= nc && 2 * ez + 1 <= nc;
-    nowrap = plain_x && plain_y && plain_z;
-    ncs = ex * ey * ez;
-    m_exy = recip16((uint32_t)(ex * ey));
-    m_ex = recip16((uint32_t)ex);
-    // the record counts of this thread's region cells (2 tid and 2 tid + 1,
-    // or tid), issued first
+  int bxc, byc;
+  const int bzc = div_nb(d, div_nb(d, w, bxc), byc);
+  region_dim(d, bxc, bx, ex);
+  region_dim(d, byc, by, ey);
+  region_dim(d, bzc, bz, ez);
+  // a region that does not wrap around the box and spans less than half of
+  // it: a difference of two positions in it is below L/2 in magnitude, and
+  // the minimum image leaves it unchanged
+  plain_x = d.nbricks > 1 && bx + ex <= nc && 2 * ex + 1 <= nc;
+  plain_y = d.nbricks > 1 && by + ey <= nc && 2 * ey + 1 <= nc;
+  plain_z = d.nbricks > 1 && bz + ez <= nc && 2 * ez + 1 <= nc;
+  nowrap = plain_x && plain_y && plain_z;
+  ncs = ex * ey * ez;
+  m_exy = recip16((uint32_t)(ex * ey));
+  m_ex = recip16((uint32_t)ex);
+  // the record counts of this thread's region cells (2 tid and 2 tid + 1,
+  // or tid), issued first
 #pragma unroll
-    for (int h = 0; h < (kTwo ? 2 : 1); ++h) {
-      const int cl = kTwo ? 2 * tid + h : tid;
-      if (cl < ncs) {
-        const int gcl = region_cell(cl);
-        (h ? gc2 : gc) = gcl;
-        (h ? mine2 : mine) = bk.cnt[gcl];
-      }
+  for (int h = 0; h < (kTwo ? 2 : 1); ++h) {
+    const int cl = kTwo ? 2 * tid + h : tid;
+    if (cl < ncs) {
+      const int gcl = region_cell(cl);
+      (h ? gc2 : gc) = gcl;
+      (h ? mine2 : mine) = bk.cnt[gcl];
     }
   }
   // the first particle of the first pass, issued behind the record counts
   // (memory operations complete in issue order)
-  Part cur = load_part<kBrick>(a, X, Y, Z, s0 + tid, s1);
-  if (kBrick) {
-    mine = mine < (uint32_t)kCellCap ? mine : (uint32_t)kCellCap;
-    mine2 = mine2 < (uint32_t)kCellCap ? mine2 : (uint32_t)kCellCap;
-    uint32_t total = 0;
-    const uint32_t off = block_scan_excl(mine + mine2, s_wave, total);
-    staged = total <= (uint32_t)kStageRecs && bk.novf == 0;
-    // each thread stages the records of its own region cells: the first
-    // kFirst of a cell loaded together, the rare rest one after another
-    constexpr int kFirst = kTwo ? 2 : 4;
+  Part cur = load_part(a, X, Y, Z, s0 + tid, s1);
+  mine = mine < (uint32_t)kCellCap ? mine : (uint32_t)kCellCap;
+  mine2 = mine2 < (uint32_t)kCellCap ? mine2 : (uint32_t)kCellCap;
+  uint32_t total = 0;
+  const uint32_t off = block_scan_excl(mine + mine2, s_wave, total);
+  staged = total <= (uint32_t)kStageRecs && bk.novf == 0;
+  // each thread stages the records of its own region cells: the first
+  // kFirst of a cell loaded together, the rare rest one after another
+  constexpr int kFirst = kTwo ? 2 : 4;
 #pragma unroll
-    for (int h = 0; h < (kTwo ? 2 : 1); ++h) {
-      const int cl = kTwo ? 2 * tid + h : tid;
-      const uint32_t o = h ? off + mine : off, m = h ? mine2 : mine;
-      if (cl < ncs) {
-        s_off[cl] = (uint16_t)o;
-        if (staged) {
-          const size_t r0 = (size_t)(h ? gc2 : gc) * kCellCap;
-          // the first records in registers (named, so that none of them
-          // lives in scratch), loaded together, then written to LDS
-          float4 rv0 = make_float4(0.f, 0.f, 0.f, 0.f), rv1 = rv0, rv2 = rv0, rv3 = rv0;
-          int32_t sv0 = 0, sv1 = 0, sv2 = 0, sv3 = 0;
-          if (m > 0u) { rv0 = bk.rec[r0]; sv0 = bk.sa[r0]; }
-          if (m > 1u) { rv1 = bk.rec[r0 + 1]; sv1 = bk.sa[r0 + 1]; }
-          if (kFirst > 2 && m > 2u) { rv2 = bk.rec[r0 + 2]; sv2 = bk.sa[r0 + 2]; }
-          if (kFirst > 3 && m > 3u) { rv3 = bk.rec[r0 + 3]; sv3 = bk.sa[r0 + 3]; }
-          if (m > 0u) { s_rec[o] = rv0; s_rsa[o] = sv0; }
-          if (m > 1u) { s_rec[o + 1] = rv1; s_rsa[o + 1] = sv1; }
-          if (kFirst > 2 && m > 2u) { s_rec[o + 2] = rv2; s_rsa[o + 2] = sv2; }
-          if (kFirst > 3 && m > 3u) { s_rec[o + 3] = rv3; s_rsa[o + 3] = sv3; }
-          if (!kF && d.adj_staged)
-            for (uint32_t j = 0; j < m && j < (uint32_t)kFirst; ++j) s_radj[o + j] = d.radj[r0 + j];
-          for (uint32_t j = kFirst; j < m; ++j) {
-            s_rec[o + j] = bk.rec[r0 + j];
-            s_rsa[o + j] = bk.sa[r0 + j];
-            if (!kF && d.adj_staged) s_radj[o + j] = d.radj[r0 + j];
-          }
+  for (int h = 0; h < (kTwo ? 2 : 1); ++h) {
+    const int cl = kTwo ? 2 * tid + h : tid;
+    const uint32_t o = h ? off + mine : off, m = h ? mine2 : mine;
+    if (cl < ncs) {
+      s_off[cl] = (uint16_t)o;
+      if (staged) {
+        const size_t r0 = (size_t)(h ? gc2 : gc) * kCellCap;
+        // the first records in registers (named, so that none of them
+        // lives in scratch), loaded together, then written to LDS
+        float4 rv0 = make_float4(0.f, 0.f, 0.f, 0.f), rv1 = rv0, rv2 = rv0, rv3 = rv0;
+        int32_t sv0 = 0, sv1 = 0, sv2 = 0, sv3 = 0;
+        if (m > 0u) { rv0 = bk.rec[r0]; sv0 = bk.sa[r0]; }
+        if (m > 1u) { rv1 = bk.rec[r0 + 1]; sv1 = bk.sa[r0 + 1]; }
+        if (kFirst > 2 && m > 2u) { rv2 = bk.rec[r0 + 2]; sv2 = bk.sa[r0 + 2]; }
+        if (kFirst > 3 && m > 3u) { rv3 = bk.rec[r0 + 3]; sv3 = bk.sa[r0 + 3]; }
+        if (m > 0u) { s_rec[o] = rv0; s_rsa[o] = sv0; }
+        if (m > 1u) { s_rec[o + 1] = rv1; s_rsa[o + 1] = sv1; }
+        if (kFirst > 2 && m > 2u) { s_rec[o + 2] = rv2; s_rsa[o + 2] = sv2; }
+        if (kFirst > 3 && m > 3u) { s_rec[o + 3] = rv3; s_rsa[o + 3] = sv3; }
+        if (!kF && d.adj_staged)
+          for (uint32_t j = 0; j < m && j < (uint32_t)kFirst; ++j) s_radj[o + j] = d.radj[r0 + j];
+        for (uint32_t j = kFirst; j < m; ++j) {
+          s_rec[o + j] = bk.rec[r0 + j];
+          s_rsa[o + j] = bk.sa[r0 + j];
+          if (!kF && d.adj_staged) s_radj[o + j] = d.radj[r0 + j];
         }
       }
     }
-    if (tid == 0) s_off[ncs] = (uint16_t)total;
   }
+  if (tid == 0) s_off[ncs] = (uint16_t)total;
   __syncthreads();
   const bool dead = s_dead != 0;
   // the workgroup-uniform switches of the pass loop, one scalar register
@@ -987,7 +978,7 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
       (plain_x && plain_y && !plain_z ? kFWrapZ : 0u));
   SweepAcc n = {0, 0, 0, 0, 0};
   for (int base = s0; base < s1 && !dead; base += kTP) {
-    if (base != s0) cur = load_part<kBrick>(a, X, Y, Z, base + tid, s1);
+    if (base != s0) cur = load_part(a, X, Y, Z, base + tid, s1);
 #pragma unroll 1
     for (int u = 0; u < kPer; ++u) {
       const int lt = u * kThreads + tid;
@@ -997,14 +988,12 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
       // wave priority by progress: the arbiter otherwise favours the oldest
       // waves, so the workgroups dispatched first race ahead and the last
       // ones end up running nearly alone on their compute units at the end
-      if (kBrick) {
-        if (u == 0) __builtin_amdgcn_s_setprio(3);
-        else if (u == 1) __builtin_amdgcn_s_setprio(2);
-        else __builtin_amdgcn_s_setprio(1);
-      }
+      if (u == 0) __builtin_amdgcn_s_setprio(3);
+      else if (u == 1) __builtin_amdgcn_s_setprio(2);
+      else __builtin_amdgcn_s_setprio(1);
       // the next particle's loads are in flight while this one is handled
       Part nxt = cur;
-      if (u + 1 < kPer) nxt = load_part<kBrick>(a, X, Y, Z, slot + kThreads, s1);
+      if (u + 1 < kPer) nxt = load_part(a, X, Y, Z, slot + kThreads, s1);
       const uint32_t idj = (uint32_t)cur.id;
       if (slot < s1 && (fl & kFMove)) {  // the re-jitter (stand-in for the MD between steps)
         if (fl & kFJit) rejitter(d, step, idj, cur.x, cur.y, cur.z);
@@ -1036,8 +1025,8 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
       if (slot < s1 && cur.role == kRoleT) {
         n.t_elig++;
         defer = true;
-        if (kBrick && (fl & kFStaged)) {
-          if (kBrick) s_tid[lt] = (int)idj;
+        if (fl & kFStaged) {
+          s_tid[lt] = (int)idj;
           const float px = cur.x, py = cur.y, pz = cur.z;
           // local coordinates (in the staged region) of the lower corner of
           // the T's 2x2x2 cell block: floor(u - 1/2) - base, taken mod nc
@@ -1081,31 +1070,29 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
         }
       }
       if (defer) nh = 0;
-      if (kBrick) {
-        // queue slots for the wavefront's held pairs: lane j's pairs go after
-        // those of the lower lanes (counts from four ballots)
-        const unsigned long long g1 = __ballot(nh >= 1), g2 = __ballot(nh >= 2),
-                                 g3 = __ballot(nh >= 3), g4 = __ballot(nh >= 4);
-        const uint32_t wtot =
-            (uint32_t)(__popcll(g1) + __popcll(g2) + __popcll(g3) + __popcll(g4));
-        if (wtot) {
-          uint32_t qb = 0;
-          if (__lane_id() == 0) qb = (uint32_t)atomicAdd(&s_qn, (int)wtot);
-          qb = (uint32_t)__builtin_amdgcn_readlane((int)qb, 0);
-          const uint32_t p =
-              qb + lanes_below(g1) + lanes_below(g2) + lanes_below(g3) + lanes_below(g4);
-          if (nh > 0) {
-            if (p + (uint32_t)nh <= (uint32_t)kQueue) {
-              n.in_rc += nh;
-              for (int j = 0; j < nh; ++j)
-                s_q[p + j] = (uint32_t)lt | (((hits >> (8 * j)) & 0xFFu) << 16);
-            } else {
-              // the pairs do not all fit: the T is deferred and the slots it
-              // reserved below kQueue are marked empty
-              for (int j = 0; j < nh; ++j)
-                if (p + j < (uint32_t)kQueue) s_q[p + j] = kQEmpty;
-              defer = true;
-            }
+      // queue slots for the wavefront's held pairs: lane j's pairs go after
+      // those of the lower lanes (counts from four ballots)
+      const unsigned long long g1 = __ballot(nh >= 1), g2 = __ballot(nh >= 2),
+                               g3 = __ballot(nh >= 3), g4 = __ballot(nh >= 4);
+      const uint32_t wtot =
+          (uint32_t)(__popcll(g1) + __popcll(g2) + __popcll(g3) + __popcll(g4));
+      if (wtot) {
+        uint32_t qb = 0;
+        if (__lane_id() == 0) qb = (uint32_t)atomicAdd(&s_qn, (int)wtot);
+        qb = (uint32_t)__builtin_amdgcn_readlane((int)qb, 0);
+        const uint32_t p =
+            qb + lanes_below(g1) + lanes_below(g2) + lanes_below(g3) + lanes_below(g4);
+        if (nh > 0) {
+          if (p + (uint32_t)nh <= (uint32_t)kQueue) {
+            n.in_rc += nh;
+            for (int j = 0; j < nh; ++j)
+              s_q[p + j] = (uint32_t)lt | (((hits >> (8 * j)) & 0xFFu) << 16);
+          } else {
+            // the pairs do not all fit: the T is deferred and the slots it
+            // reserved below kQueue are marked empty
+            for (int j = 0; j < nh; ++j)
+              if (p + j < (uint32_t)kQueue) s_q[p + j] = kQEmpty;
+            defer = true;
           }
         }
       }
@@ -1113,16 +1100,14 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
       cur = nxt;
     }
     __syncthreads();
-    if (kBrick) {
-      // the pass's queued pairs: draws on full wavefronts
-      const int qn = min(s_qn, kQueue);
-      for (int e = tid; e < qn; e += kThreads) {
-        const uint32_t q = s_q[e];
-        if (q == kQEmpty) continue;
-        const uint32_t lt = q & 0xFFFFu, r = q >> 16;
-        retain(d, a, step, __float_as_int(s_rec[r].w), s_rsa[r], (uint32_t)s_tid[lt],
-               base + (int)lt, d.adj_staged && !kF ? &s_radj[r] : nullptr, n, rl);
-      }
+    // the pass's queued pairs: draws on full wavefronts
+    const int qn = min(s_qn, kQueue);
+    for (int e = tid; e < qn; e += kThreads) {
+      const uint32_t q = s_q[e];
+      if (q == kQEmpty) continue;
+      const uint32_t lt = q & 0xFFFFu, r = q >> 16;
+      retain(d, a, step, __float_as_int(s_rec[r].w), s_rsa[r], (uint32_t)s_tid[lt],
+             base + (int)lt, d.adj_staged && !kF ? &s_radj[r] : nullptr, n, rl);
     }
     // the deferred T's, re-jittered again from the previous positions: in the
     // staged records when the block lies in a staged region (T's with more
@@ -1134,7 +1119,7 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
       float px = X[slot], py = Y[slot], pz = Z[slot];
       const uint32_t idj = a.id ? (uint32_t)a.id[slot] : (uint32_t)slot;
       if (jit) rejitter(d, step, idj, px, py, pz);
-      if (kBrick && staged) {
+      if (staged) {
         const int lx0 = local_lo(px, d.inv_w, bx, nc), ly0 = local_lo(py, d.inv_w, by, nc),
                   lz0 = local_lo(pz, d.inv_w, bz, nc);
         if ((uint32_t)lx0 < (uint32_t)(ex - 1) && (uint32_t)ly0 < (uint32_t)(ey - 1) &&
@@ -1219,6 +1204,150 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
   if (tid == 0) {
     out[kOutRet] = nk;
     if (kF) out[kOutAElig] = s_cnt[4];
+    if (ne > kRetCap) atomicAdd(&d.ctl->ret_ovf[par], (uint32_t)(ne - kRetCap));
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The random selection's sweep on unsorted storage (the single step on the
+// caller's arrays, and resident systems that never sort): workgroup w takes
+// slots w * kThreads .. + kThreads - 1, one per thread.  The particles are in
+// any order, so a T's eight cells and their records are reads of lines no
+// neighbouring lane shares: their latency and the caches' request rate bound
+// the kernel.  A T issues its eight counts together, keeps them as nibbles of
+// one word (a bucket holds at most eight records) and then takes its records
+// four at a time, with four loads in flight; in-range pairs go to an LDS queue
+// so that the draws run on full wavefronts.  1,000,003 particles in random
+// order, 5% A's: walking the cells one after another with the draw in the
+// loop 74 us, this 55 us; 4,000 particles 16.3 and 10.1 us.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ void dense_sweep_body(const Dev& d, int k, int w, int nwg) {
+  constexpr int kDenseQ = 512;
+  static_assert(kCellCap <= 8, "a cell's record count fits a nibble");
+  __shared__ uint2 s_q[kDenseQ];  // cell (or overflow index), local T | record << 8 | overflow << 31
+  __shared__ int32_t s_tid[kThreads];
+  __shared__ int4 s_ent[kRetCap];
+  __shared__ uint32_t s_ew2[kRetCap];
+  __shared__ int s_cnt[4], s_qn, s_ne;
+  const int tid = threadIdx.x;
+  if (tid < 4) s_cnt[tid] = 0;
+  if (tid == 0) {
+    s_qn = 0;
+    s_ne = 0;
+  }
+  const Ctl* c = d.ctl;
+  const StepInfo si = step_info(c, k);
+  const uint32_t par = si.par, step = si.step;
+  const Arr a = pick_set(d, c->set & 1u);
+  const bool dead = read_err(c) != 0;
+  const Buckets bk = step_buckets<false>(d, par, step);
+  const RetList rl{&s_ne, s_ent, s_ew2};
+  SweepAcc n = {0, 0, 0, 0, 0};
+  const int slot = w * kThreads + tid;
+  float x = 0.0f, y = 0.0f, z = 0.0f;
+  uint32_t id = (uint32_t)slot;
+  bool is_target = false;
+  if (slot < d.n && !dead) {
+    x = pick(a.x, par)[slot];
+    y = pick(a.y, par)[slot];
+    z = pick(a.z, par)[slot];
+    if (a.id) id = (uint32_t)a.id[slot];
+    is_target = a.role[slot] == kRoleT;
+    if (d.jitter) {
+      if (d.jit_c != 0.0f) rejitter(d, step, id, x, y, z);
+      pick(a.x, par ^ 1u)[slot] = x;
+      pick(a.y, par ^ 1u)[slot] = y;
+      pick(a.z, par ^ 1u)[slot] = z;
+    }
+  }
+  __syncthreads();
+  if (is_target) {
+    n.t_elig++;
+    s_tid[tid] = (int32_t)id;
+    const int nc = d.nc;
+    int cx0, cx1, cy0, cy1, cz0, cz1;
+    lo_hi(x, d.inv_w, nc, cx0, cx1);
+    lo_hi(y, d.inv_w, nc, cy0, cy1);
+    lo_hi(z, d.inv_w, nc, cz0, cz1);
+    // rows (y, z) of the block; one cell per side: the block is that cell
+    const int r00 = (cz0 * nc + cy0) * nc, r01 = (cz0 * nc + cy1) * nc,
+              r10 = (cz1 * nc + cy0) * nc, r11 = (cz1 * nc + cy1) * nc;
+    uint32_t cnt[8];
+    cnt[0] = bk.cnt[r00 + cx0];
+    cnt[1] = bk.cnt[r00 + cx1];
+    cnt[2] = bk.cnt[r01 + cx0];
+    cnt[3] = bk.cnt[r01 + cx1];
+    cnt[4] = bk.cnt[r10 + cx0];
+    cnt[5] = bk.cnt[r10 + cx1];
+    cnt[6] = bk.cnt[r11 + cx0];
+    cnt[7] = bk.cnt[r11 + cx1];
+    uint32_t left = 0;  // records not taken yet, a nibble per cell
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      left |= (cnt[q] < (uint32_t)kCellCap ? cnt[q] : (uint32_t)kCellCap) << (4 * q);
+    if (nc == 1) left &= 15u;
+    auto hit = [&](const float4& A, uint32_t cell, uint32_t what) {
+      if (!(dist2(d, x, y, z, A) < d.rc2)) return;
+      n.in_rc++;
+      const int p = atomicAdd(&s_qn, 1);
+      if (p < kDenseQ) {
+        s_q[p] = make_uint2(cell, (uint32_t)tid | what);
+      } else {  // the queue is full: drawn at once
+        const bool o = what >> 31;
+        const size_t r = o ? (size_t)cell : (size_t)cell * kCellCap + (what >> 8);
+        retain(d, a, step, __float_as_int(A.w), (o ? bk.osa : bk.sa)[r], id, slot, nullptr, n, rl);
+      }
+    };
+    while (left) {
+      float4 A[4];
+      uint32_t cell[4], rec[4];
+      bool have[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        have[u] = left != 0u;
+        const int sh = have[u] ? __builtin_ctz(left) & 28 : 0;
+        const int row = sh & 16 ? (sh & 8 ? r11 : r10) : (sh & 8 ? r01 : r00);
+        cell[u] = (uint32_t)(row + (sh & 4 ? cx1 : cx0));
+        rec[u] = ((left >> sh) & 15u) - 1u;
+        if (have[u]) {
+          left -= 1u << sh;
+          A[u] = bk.rec[(size_t)cell[u] * kCellCap + rec[u]];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (have[u]) hit(A[u], cell[u], rec[u] << 8);
+    }
+    for (uint32_t r = 0; r < bk.novf; ++r) hit(bk.ovf[r], r, 1u << 31);
+  }
+  __syncthreads();
+  const int qn = min(s_qn, kDenseQ);
+  for (int e = tid; e < qn; e += kThreads) {
+    const uint2 q = s_q[e];
+    const int lt = (int)(q.y & 0xFFu);
+    const bool o = q.y >> 31;
+    const size_t r = o ? (size_t)q.x : (size_t)q.x * kCellCap + (q.y >> 8);
+    retain(d, a, step, __float_as_int((o ? bk.ovf : bk.rec)[r].w), (o ? bk.osa : bk.sa)[r],
+           (uint32_t)s_tid[lt], w * kThreads + lt, nullptr, n, rl);
+  }
+  // clear the bucket counts of the next step's parity (as the other sweeps)
+  for (int q = w * kThreads + tid; q < d.ncell_clear; q += nwg * kThreads)
+    pick(d.cnt, par ^ 1u)[q] = 0u;
+  wave_add(&s_cnt[kOutTElig], n.t_elig);
+  wave_add(&s_cnt[kOutInRc], n.in_rc);
+  wave_add(&s_cnt[kOutDrawn], n.drawn);
+  wave_add(&s_cnt[kOutExcl], n.excl);
+  __syncthreads();
+  const int ne = s_ne;
+  const int nk = ne < kRetCap ? ne : kRetCap;
+  if (tid < nk) {
+    pick(d.wge, par)[w * kRetCap + tid] = s_ent[tid];
+    pick(d.wgk, par)[w * kRetCap + tid] = s_ew2[tid];
+  }
+  int32_t* out = pick(d.wgo, par) + w * kWgOut;
+  if (tid < 4) out[tid] = s_cnt[tid];
+  if (tid == 0) {
+    out[kOutRet] = nk;
     if (ne > kRetCap) atomicAdd(&d.ctl->ret_ovf[par], (uint32_t)(ne - kRetCap));
   }
 }
@@ -1559,7 +1688,7 @@ __device__ __forceinline__ void near_sweep_body(const Dev& d, int k, int w, int 
   wave_add(&s_cnt[1], in_rc);
   wave_add(&s_cnt[2], excl);
   // clear the bucket counts of the next step's parity (as the other sweep)
-  for (int q = w * kThreads + tid; q < d.ncell; q += nwg * kThreads)
+  for (int q = w * kThreads + tid; q < d.ncell_clear; q += nwg * kThreads)
     pick(d.cnt, par ^ 1u)[q] = 0u;
   __syncthreads();
   int32_t* out = pick(d.wgo, par) + w * kWgOut;
@@ -1997,7 +2126,7 @@ __device__ __forceinline__ void multi_sweep_body(const Dev& d, int k, int w, int
   wave_add(&s_cnt[1], in_rc);
   wave_add(&s_cnt[2], drawn);
   wave_add(&s_cnt[3], excl);
-  for (int q = w * kThreads + tid; q < d.ncell; q += nwg * kThreads)
+  for (int q = w * kThreads + tid; q < d.ncell_clear; q += nwg * kThreads)
     pick(d.cnt, par ^ 1u)[q] = 0u;
   __syncthreads();
   int32_t* out = pick(d.wgo, par) + w * kWgOut;
@@ -2625,9 +2754,53 @@ __global__ __launch_bounds__(kThreads) void k_kin_reset(Dev d) {
 }
 
 // ---------------------------------------------------------------------------
-// Stateless single step: close it and sort its bonds by id_A into the
-// caller's buffer (one workgroup).
+// Stateless single step: the first kernel (position check, roles, binning of
+// the A's) and the last one (counters, the step's bonds sorted by id_A into
+// the caller's buffer).  Four launches make a step: the first kernel also sets
+// the control block up, the sweep clears the cell counts of the previous call
+// (the calls alternate between the two count buffers), and the last one leaves
+// the per-call words as the next call expects them.
 // ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kThreads) void k_single_prep(Dev d, uint32_t step, uint32_t par) {
+  __shared__ int s_na;
+  const int i = blockIdx.x * kThreads + threadIdx.x;
+  if (threadIdx.x == 0) s_na = 0;
+  if (i == 0) {  // err, ovf_n, ret_ovf and nwin_ovf are zero between calls
+    d.ctl->step0 = step;
+    d.ctl->par0 = par;
+    d.ctl->set = 0;
+  }
+  __syncthreads();
+  bool is_src = false;
+  if (i < d.n) {
+    const Arr a = pick_set(d, 0);
+    const float x = a.x[0][i], y = a.y[0][i], z = a.z[0][i];
+    const bool ok = (x >= 0.0f && x < d.L) && (y >= 0.0f && y < d.L) && (z >= 0.0f && z < d.L);
+    if (!ok) set_err(d.ctl, PR_EINVAL);
+    const uint8_t role = role_of(d, a.typ[i], a.st[i]);
+    a.role[i] = role;
+    is_src = role_is_a(role, d.nrules > 1);
+    if (is_src && ok) {  // the unsorted sweeps read no staged adjacency rows
+      const int c = cell_of(d, x, y, z);
+      const uint32_t r = atomicAdd(&pick(d.cnt, par)[c], 1u);
+      const float4 rec = make_float4(x, y, z, __int_as_float(i));
+      if (r < (uint32_t)kCellCap) {
+        const size_t ri = (size_t)c * kCellCap + r;
+        d.rec[ri] = rec;
+        d.rsa[ri] = i;
+      } else {
+        const uint32_t o = atomicAdd(&d.ctl->ovf_n[par], 1u);
+        pick(d.ovf, par)[o] = rec;
+        pick(d.ovf_sa, par)[o] = i;
+      }
+    }
+  }
+  const unsigned long long m = __ballot(is_src);
+  if (__lane_id() == 0 && m) atomicAdd(&s_na, (int)__popcll(m));
+  __syncthreads();
+  if (threadIdx.x == 0) pick(d.abst, par)[blockIdx.x] = s_na;
+}
+
 __device__ void bitonic_sort(unsigned long long* buf, int n2) {
   for (int k = 2; k <= n2; k <<= 1)
     for (int j = k >> 1; j > 0; j >>= 1) {
@@ -2647,34 +2820,128 @@ __device__ void bitonic_sort(unsigned long long* buf, int n2) {
     }
 }
 
-// After k_close and k_advance of the single step: its bonds (the whole log)
-// sorted by id_A into the caller's buffer.
-__global__ __launch_bounds__(kFinThreads) void k_single_sort(Dev d) {
+// The first n2 keys (a power of two up to 1024), one per thread of a
+// 1024-thread workgroup, sorted ascending: the bitonic network with the
+// exchanges inside a wavefront as lane shuffles (45 of the 55 steps of 1024
+// keys) and only those across wavefronts through LDS and barriers.  buf: 1024
+// keys of LDS.
+__device__ __forceinline__ unsigned long long sort_1024(unsigned long long key, int n2,
+                                                        unsigned long long* buf) {
+  const int t = threadIdx.x;
+  for (int k = 2; k <= n2; k <<= 1) {
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      unsigned long long other;
+      if (j >= 64) {
+        __syncthreads();
+        buf[t] = key;
+        __syncthreads();
+        other = buf[t ^ j];
+      } else {
+        other = __shfl_xor(key, j);
+      }
+      // the lower place of a pair keeps the smaller key in an ascending run
+      const bool keep_min = ((t & j) == 0) == ((t & k) == 0);
+      key = keep_min == (key < other) ? key : other;
+    }
+  }
+  return key;
+}
+
+// A bond key (id_A << 32 | id_T) as row t of the caller's buffer; with several
+// rules the rule rides in bits 30-31 of id_T.
+__device__ __forceinline__ void put_bond(const Dev& d, int64_t t, unsigned long long key) {
+  if (t >= d.bonds_cap) return;
+  const uint32_t tt = (uint32_t)key;
+  if (d.bonds_rule) {
+    d.bonds[3 * t] = (int32_t)(key >> 32);
+    d.bonds[3 * t + 1] = (int32_t)(d.nrules > 1 ? tt & 0x3FFFFFFFu : tt);
+    d.bonds[3 * t + 2] = (int32_t)(d.nrules > 1 ? tt >> 30 : 0u);
+  } else {
+    d.bonds[2 * t] = (int32_t)(key >> 32);
+    d.bonds[2 * t + 1] = (int32_t)tt;
+  }
+}
+
+// The last kernel: one workgroup sums the counters of the sweep workgroups and
+// collects their staged bonds (keys to LDS, beyond kSortLds to sortbuf), sorts
+// them and reports to *out, which the host reads after the stream.  Bound by
+// its round trips: the counters of 4 sweep workgroups per thread at 1M
+// particles are loaded together.  It replaces the closing, block-end and sort
+// kernels and two copies: 36 us of kernels at 1,000,003 particles (950 bonds),
+// now 17.5 us; 9 us at 4,000, now 5.
+__global__ __launch_bounds__(kFinThreads) void k_single_finish(Dev d, uint32_t par, SingleOut* out) {
   __shared__ unsigned long long s_b[kSortLds];
-  const Ctl* c = d.ctl;
-  if (read_err(c)) return;
-  const int64_t nb = (int64_t)c->log_n;
-  const int64_t m = nb < d.log_cap ? nb : d.log_cap;
+  __shared__ unsigned long long s_sum[kPart];
+  __shared__ int s_nb;
+  const int tid = threadIdx.x;
+  Ctl* c = d.ctl;
+  if (tid < kPart) s_sum[tid] = 0ull;
+  if (tid == 0) s_nb = 0;
+  __syncthreads();
+  const int32_t err = read_err(c);
+  const int nwov = err ? 0 : (int)c->nwin_ovf[par];
+  auto keep = [&](int2 b) {
+    const int p = atomicAdd(&s_nb, 1);
+    const unsigned long long key = ((unsigned long long)(uint32_t)b.x << 32) | (uint32_t)b.y;
+    if (p < kSortLds) s_b[p] = key;
+    d.sortbuf[p] = key;
+  };
+  int v[kPart] = {0, 0, 0, 0, 0, 0, 0, 0};
+  constexpr int kAt = 4;  // sweep workgroups per thread and round, loaded together
+  for (int w0 = tid; w0 < d.nwg_sweep; w0 += kAt * kFinThreads) {
+    int nb[kAt];
+#pragma unroll
+    for (int u = 0; u < kAt; ++u) {
+      const int w = w0 + u * kFinThreads;
+      nb[u] = 0;
+      if (w < d.nwg_sweep) {
+        const int32_t* o = pick(d.wgo, par) + (size_t)w * kWgOut;
+        v[0] += pick(d.abst, par)[w];
+        v[1] += o[kOutTElig];
+        v[2] += o[kOutInRc];
+        v[3] += o[kOutDrawn];
+        v[4] += o[kOutExcl];
+        v[5] += o[kOutProp];
+        v[7] += o[kOutLost];
+        nb[u] = err ? 0 : o[kOutBonds];
+        v[6] += nb[u];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kAt; ++u)
+      for (int e = 0; e < min(nb[u], kWinCap); ++e)
+        keep((pick(d.wgw, par) + (size_t)(w0 + u * kFinThreads) * kWinCap)[e]);
+  }
+#pragma unroll
+  for (int q = 0; q < kPart; ++q) {
+    const uint32_t t = wave_scan_incl((uint32_t)v[q]);
+    if (__lane_id() == 63 && t) atomicAdd(&s_sum[q], (unsigned long long)t);
+  }
+  for (int e = tid; e < nwov; e += kFinThreads) keep(pick(d.wov, par)[e]);
+  __syncthreads();
+  const int m = s_nb;
   int n2 = 1;
   while (n2 < m) n2 <<= 1;
-  unsigned long long* buf = n2 <= kSortLds ? s_b : d.sortbuf;
-  for (int t = threadIdx.x; t < n2; t += blockDim.x)
-    buf[t] = t < m ? (((unsigned long long)(uint32_t)d.log[3 * t + 1] << 32) |
-                      (uint32_t)d.log[3 * t + 2])
-                   : kEmpty;
-  __threadfence_block();
-  __syncthreads();
-  if (m > 1) bitonic_sort(buf, n2);
-  for (int t = threadIdx.x; t < m && t < d.bonds_cap; t += blockDim.x) {
-    if (d.bonds_rule) {  // (id_A, id_T, rule): the rule rides in bits 30-31 of id_T
-      const uint32_t tt = (uint32_t)buf[t];
-      d.bonds[3 * t] = (int32_t)(buf[t] >> 32);
-      d.bonds[3 * t + 1] = (int32_t)(d.nrules > 1 ? tt & 0x3FFFFFFFu : tt);
-      d.bonds[3 * t + 2] = (int32_t)(d.nrules > 1 ? tt >> 30 : 0u);
-    } else {
-      d.bonds[2 * t] = (int32_t)(buf[t] >> 32);
-      d.bonds[2 * t + 1] = (int32_t)(uint32_t)buf[t];
-    }
+  if (n2 <= kFinThreads) {
+    const unsigned long long key = sort_1024(tid < m ? s_b[tid] : kEmpty, n2, s_b);
+    if (tid < m) put_bond(d, tid, key);
+  } else {
+    unsigned long long* buf = n2 <= kSortLds ? s_b : d.sortbuf;
+    for (int t = tid; t < n2; t += kFinThreads)
+      if (t >= m) buf[t] = kEmpty;
+    __threadfence_block();
+    __syncthreads();
+    bitonic_sort(buf, n2);
+    for (int t = tid; t < m; t += kFinThreads) put_bond(d, t, buf[t]);
+  }
+  if (tid < kPart) out->sum[tid] = (int64_t)s_sum[tid];
+  if (tid == 0) {
+    out->err = err;
+    out->n_bonds = m;
+    c->err = 0;
+    c->ovf_n[par] = 0;
+    c->ret_ovf[par] = 0;
+    c->nwin_ovf[par] = 0;
   }
 }
 
@@ -2851,7 +3118,7 @@ __global__ void k_advance(Ctl* c, int K) {
 // with the sweep's workgroups, so their chain of round trips (with the
 // returning atomic that reserves log rows) runs beside the sweep instead of
 // lengthening the resolve.
-template <bool kBrick, bool kTwo, bool kF, bool kNt = false>
+template <bool kTwo, bool kF, bool kNt = false>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_sweep(Dev d, int k) {
   if (kF && (int)blockIdx.x >= d.nwg_sweep) {
     __shared__ uint32_t s_wave[kThreads / 64 + 1];
@@ -2860,8 +3127,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
                 (int)blockIdx.x - d.nwg_sweep, s_wave);
     return;
   }
-  const int w = kBrick ? xcd_brick(blockIdx.x, d.nwg_sweep) : (int)blockIdx.x;
-  sweep_body<kBrick, kTwo, kF, kNt>(d, k, w, d.nwg_sweep);
+  sweep_body<kTwo, kF, kNt>(d, k, xcd_brick(blockIdx.x, d.nwg_sweep), d.nwg_sweep);
+}
+__global__ __launch_bounds__(kThreads) void k_dense_sweep(Dev d, int k) {
+  dense_sweep_body(d, k, blockIdx.x, gridDim.x);
 }
 template <bool kBrick>
 __global__ __launch_bounds__(kThreads) void k_resolve(Dev d, int k) {
@@ -2950,7 +3219,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
   const int4 m = uniform_map(map);
   const Dev& d = ds[m.x];
   if (k >= d.k_limit || d.rule.policy != PR_POLICY_RANDOM) return;
-  sweep_body<true, kTwo, kF>(d, k, m.y, m.z);
+  sweep_body<kTwo, kF>(d, k, m.y, m.z);
 }
 __global__ __launch_bounds__(kThreads) void k_near_sweep_b(const Dev* __restrict__ ds,
                                                            const int4* __restrict__ map, int k) {
@@ -3149,31 +3418,10 @@ hipError_t launch_generate(const Dev& d, int kind, unsigned long long gseed, flo
   return hipGetLastError();
 }
 
-// Step k of a block: prep (with the closing of step k - 1), sweep, resolve.
-// ev_sweep0/1 (timed runs): the sweep is launched with hipExtLaunchKernel,
-// which stamps the two events at the kernel's own start and end.
-hipError_t launch_step(const Dev& d, int k, hipStream_t s, hipEvent_t ev_sweep0,
-                       hipEvent_t ev_sweep1) {
-  if (d.md_theta > 0) {
-    const int g = blocks_for(d.n, kThreads * kMdPer);
-    k_md_free<<<g, kThreads, 0, s>>>(d, k);
-    for (int m = 0; m <= d.md_theta; ++m) k_md_sub<<<g, kThreads, 0, s>>>(d, k, m);
-  }
-  if (d.fuse) {  // two kernels: the sweep (with the closing of step k - 1), the resolve
-    // the sweep, with the closing of step k - 1 in trailing workgroups (edges
-    // above kOneCellBrick stage two region cells per thread)
-    const dim3 g(d.nwg_sweep + (k > 0 ? d.ngroups : 0)), b(kThreads);
-    auto kern = d.bs > kOneCellBrick ? (d.nt_pos ? k_sweep<true, true, true, true>
-                                                 : k_sweep<true, true, true, false>)
-                                     : (d.nt_pos ? k_sweep<true, false, true, true>
-                                                 : k_sweep<true, false, true, false>);
-    if (ev_sweep0) hipExtLaunchKernelGGL(kern, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
-    else kern<<<g, b, 0, s>>>(d, k);
-    k_resolve<true><<<(d.nwg_sweep + 3) / 4, kThreads, 0, s>>>(d, k);
-    return hipGetLastError();
-  }
-  const int prep_blocks = d.nwg_prep + (k > 0 ? d.ngroups : 0);
-  k_prep<<<prep_blocks, kThreads, 0, s>>>(d, k);
+// The kernels of step k after the binning: sweep, resolve (and the final choice
+// of several rules).
+static hipError_t launch_selection(const Dev& d, int k, hipStream_t s, hipEvent_t ev_sweep0,
+                                   hipEvent_t ev_sweep1) {
   const dim3 g(d.nwg_sweep), b(kThreads);
   if (d.nrules > 1) {
     if (d.sorted) {
@@ -3210,19 +3458,19 @@ hipError_t launch_step(const Dev& d, int k, hipStream_t s, hipEvent_t ev_sweep0,
   }
   if (d.sorted && d.bs > kOneCellBrick) {
     if (ev_sweep0)
-      hipExtLaunchKernelGGL(k_sweep<true, true, false>, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
+      hipExtLaunchKernelGGL(k_sweep<true, false>, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
     else
-      k_sweep<true, true, false><<<g, b, 0, s>>>(d, k);
+      k_sweep<true, false><<<g, b, 0, s>>>(d, k);
   } else if (d.sorted) {
     if (ev_sweep0)
-      hipExtLaunchKernelGGL(k_sweep<true, false, false>, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
+      hipExtLaunchKernelGGL(k_sweep<false, false>, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
     else
-      k_sweep<true, false, false><<<g, b, 0, s>>>(d, k);
+      k_sweep<false, false><<<g, b, 0, s>>>(d, k);
   } else {
     if (ev_sweep0)
-      hipExtLaunchKernelGGL(k_sweep<false, false, false>, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
+      hipExtLaunchKernelGGL(k_dense_sweep, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
     else
-      k_sweep<false, false, false><<<g, b, 0, s>>>(d, k);
+      k_dense_sweep<<<g, b, 0, s>>>(d, k);
   }
   if (d.sorted)
     k_resolve<true><<<(d.nwg_sweep + 3) / 4, kThreads, 0, s>>>(d, k);
@@ -3231,16 +3479,47 @@ hipError_t launch_step(const Dev& d, int k, hipStream_t s, hipEvent_t ev_sweep0,
   return hipGetLastError();
 }
 
+// Step k of a block: prep (with the closing of step k - 1), sweep, resolve.
+// ev_sweep0/1 (timed runs): the sweep is launched with hipExtLaunchKernel,
+// which stamps the two events at the kernel's own start and end.
+hipError_t launch_step(const Dev& d, int k, hipStream_t s, hipEvent_t ev_sweep0,
+                       hipEvent_t ev_sweep1) {
+  if (d.md_theta > 0) {
+    const int g = blocks_for(d.n, kThreads * kMdPer);
+    k_md_free<<<g, kThreads, 0, s>>>(d, k);
+    for (int m = 0; m <= d.md_theta; ++m) k_md_sub<<<g, kThreads, 0, s>>>(d, k, m);
+  }
+  if (d.fuse) {  // two kernels: the sweep (with the closing of step k - 1), the resolve
+    // the sweep, with the closing of step k - 1 in trailing workgroups (edges
+    // above kOneCellBrick stage two region cells per thread)
+    const dim3 g(d.nwg_sweep + (k > 0 ? d.ngroups : 0)), b(kThreads);
+    auto kern = d.bs > kOneCellBrick ? (d.nt_pos ? k_sweep<true, true, true>
+                                                 : k_sweep<true, true, false>)
+                                     : (d.nt_pos ? k_sweep<false, true, true>
+                                                 : k_sweep<false, true, false>);
+    if (ev_sweep0) hipExtLaunchKernelGGL(kern, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
+    else kern<<<g, b, 0, s>>>(d, k);
+    k_resolve<true><<<(d.nwg_sweep + 3) / 4, kThreads, 0, s>>>(d, k);
+    return hipGetLastError();
+  }
+  const int prep_blocks = d.nwg_prep + (k > 0 ? d.ngroups : 0);
+  k_prep<<<prep_blocks, kThreads, 0, s>>>(d, k);
+  return launch_selection(d, k, s, ev_sweep0, ev_sweep1);
+}
+
 hipError_t launch_block_end(const Dev& d, int K, hipStream_t s) {
   k_close<<<d.ngroups, kThreads, 0, s>>>(d, K - 1);
   k_advance<<<1, 64, 0, s>>>(d.ctl, K);
   return hipGetLastError();
 }
 
-hipError_t launch_single_end(const Dev& d, hipStream_t s) {
-  k_close<<<d.ngroups, kThreads, 0, s>>>(d, 0);
-  k_advance<<<1, 64, 0, s>>>(d.ctl, 1);
-  k_single_sort<<<1, kFinThreads, 0, s>>>(d);
+// The stateless step: four launches (five with several rules).
+hipError_t launch_single(const Dev& d, uint32_t step, uint32_t par, SingleOut* out,
+                         hipStream_t s) {
+  k_single_prep<<<d.nwg_sweep, kThreads, 0, s>>>(d, step, par);
+  const hipError_t e = launch_selection(d, 0, s, nullptr, nullptr);
+  if (e != hipSuccess) return e;
+  k_single_finish<<<1, kFinThreads, 0, s>>>(d, par, out);
   return hipGetLastError();
 }
 
