@@ -360,11 +360,10 @@ int pr_sys_set_sort_period(pr_sys* s, int32_t sort_period);
 int pr_sys_set_graphs(pr_sys* s, int32_t on);
 
 /* Fused binning (Table I step 1, the candidate search): enable = 1 (default)
- * lets a handle on sorted storage with one rule, the random selection and no
- * MD skip the binning kernel: each step's sweep bins the A's of the next step
+ * lets a handle on sorted storage without MD skip the binning kernel: each step's sweep bins the A's of the next step
  * (at their positions re-jittered once more) into cell buckets of its own,
  * and the resolve drops or adds the A's whose roles its bonds change, so a
- * step is two kernels.  The buckets are allocated on the first run that can
+ * step is two kernels (three with several rules).  The buckets are allocated on the first run that can
  * use them (about 2 x 160 bytes per cell and 40 per particle) and filled by
  * the spatial sort; they hold the A's of one reaction step, so a run that
  * does not continue the previous one (another first_step or sigma, after

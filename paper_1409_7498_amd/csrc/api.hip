@@ -277,7 +277,8 @@ int alloc_scratch(Arena& a, Dev& d, int32_t n, int32_t nwg, hipStream_t s) {
       return e;
   }
   if ((e = a.alloc(&d.ctl, 1))) return e;
-  if (d.nrules > 1 && ((e = a.alloc(&d.wfa, n)) || (e = a.alloc(&d.wft, n)) ||
+  if (d.nrules > 1 && ((e = a.alloc(&d.wgk1, (size_t)nwg * kRetCap)) ||
+                       (e = a.alloc(&d.wfa, n)) || (e = a.alloc(&d.wft, n)) ||
                        (e = a.alloc(&d.wina, n)) || (e = a.alloc(&d.wint, n))))
     return e;
   if (a.dry || a.base) return PR_OK;  // a carved region is cleared by its user
@@ -688,21 +689,20 @@ void set_dense(pr_sys* s) {
 }
 
 // Whether the sweeps of a sorted system can bin the next step's A's
-// themselves: one rule with the random selection, no MD (the MD moves the
-// particles between steps), the buckets allocated.
+// themselves: no MD (the MD moves the particles between steps), the buckets
+// allocated.
 bool fuse_eligible(const pr_sys* s) {
   const Dev& d = s->d;
-  return s->allow_fuse && d.nrules == 1 && d.rule.policy == PR_POLICY_RANDOM && d.md_theta == 0 &&
-         d.fcnt[0] != nullptr;
+  return s->allow_fuse && d.md_theta == 0 && d.fcnt[0] != nullptr;
 }
 
 // The fused-binning buckets, allocated on the first run that can use them.
 int alloc_fused(pr_sys* s) {
   Dev& d = s->d;
-  if (d.fcnt[0] || !s->allow_fuse || d.nrules != 1 || d.rule.policy != PR_POLICY_RANDOM)
-    return PR_OK;
+  if (d.fcnt[0] || !s->allow_fuse) return PR_OK;
   Dev t = d;
   const size_t n = (size_t)d.n, nrec = (size_t)d.ncell * kCellCap;
+  const size_t mark = s->arena.ptrs.size();
   int e = 0;
   for (int q = 0; q < 3 && !e; ++q) e = s->arena.alloc(&t.fcnt[q], (size_t)d.ncell);
   for (int p = 0; p < 2 && !e; ++p) {
@@ -712,6 +712,18 @@ int alloc_fused(pr_sys* s) {
     if (!e) e = s->arena.alloc(&t.fovf_sa[p], n);
   }
   if (!e) e = s->arena.alloc(&t.apos, n);
+  if (e && (d.nrules > 1 || d.rule.policy != PR_POLICY_RANDOM)) {
+    // these systems also run without (the binning kernel bins), as they did
+    // before they could fuse: no memory for the buckets is no error
+    while (s->arena.ptrs.size() > mark) {
+      void* q = s->arena.ptrs.back();
+      (void)(s->arena.async ? hipFreeAsync(q, s->arena.astream) : hipFree(q));
+      s->arena.ptrs.pop_back();
+    }
+    (void)hipGetLastError();
+    s->allow_fuse = 0;
+    return PR_OK;
+  }
   if (e) return e;  // what was allocated stays in the arena until destroy
   for (int q = 0; q < 3; ++q) d.fcnt[q] = t.fcnt[q];
   for (int p = 0; p < 2; ++p) {

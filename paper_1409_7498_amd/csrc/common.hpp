@@ -123,6 +123,7 @@ struct Dev {
   int32_t* wgo[2];
   int4* wge[2];
   uint32_t* wgk[2];
+  uint32_t* wgk1;       // several rules: the w1 words of the retained pairs
   uint8_t* tflag;       // per slot: this T has a retained pair in the current step
   int2* tnear;          // nearest policy, per T id: (id of its closest A, the T's slot),
                         // written in the step for every T with a candidate
@@ -168,8 +169,7 @@ struct Dev {
   int32_t nrules;
   RuleX mr[kMaxRules];
   uint8_t *wfa, *wft;   // per slot: won as an A / as a T in this step (one writer each)
-  // fused binning (fuse = 1: sorted storage, one rule, random selection, no
-  // MD): the sweep of step k bins the A records of step k + 1 itself, so no
+  // fused binning (fuse = 1: sorted storage, no MD): the sweep of step k bins the A records of step k + 1 itself, so no
   // binning kernel runs.  Counts by step mod 3 (read in step k, filled for
   // k + 1, cleared for k + 2), bucket records and overflow by step parity;
   // apos[slot]: where the A's record of the next step went (bucket index, or

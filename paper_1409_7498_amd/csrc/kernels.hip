@@ -1,7 +1,7 @@
 // kernels.hip -- HIP kernels of the reaction step for gfx950 (CDNA4, wave64).
 //
-// One reaction step is three kernels (Table I of the paper, steps 1-9, on one
-// GPU; the communication steps 4, 6 and 8 have nothing to exchange):
+// One reaction step is up to three kernels (Table I of the paper, steps 1-9, on
+// one GPU; the communication steps 4, 6 and 8 have nothing to exchange):
 //   k_prep     closes the previous step (counters, bond rows), bins the
 //              A-role particles into coarse cells of width >= 2 rc (record:
 //              jittered position, id, slot, adjacency row) and re-jitters every
@@ -15,7 +15,8 @@
 //              a 64-bit atomicMin (steps 3-5) and joins the workgroup's list
 //   k_resolve  per sweep workgroup (one wavefront each), the listed pairs
 //              whose A chose their T; of those the smallest (w2, id_A) per T
-//              is bonded, states and adjacency updated (steps 6-9)
+//              is bonded, states and adjacency updated (steps 6-9); the nearest
+//              selection and several rules have resolves of their own
 // plus the counting sort of the storage by brick (within a brick its A's,
 // then the rest by dual cell), the synthetic generator and the helpers of the
 // runtime.
@@ -254,6 +255,18 @@ __device__ __forceinline__ uint32_t wave_scan_incl(uint32_t x) {
   x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // row_bcast:15
   x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);  // row_bcast:31
   return x;
+}
+
+// The number of lanes below this one set in b.
+__device__ __forceinline__ uint32_t lanes_below(unsigned long long b) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+}
+
+// Orders a wavefront's LDS accesses before and after it (its lanes exchange
+// data through LDS without a workgroup barrier).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 // Exclusive prefix sum over the workgroup (wavefront scans, then the
@@ -754,8 +767,30 @@ struct SweepAcc {
 struct RetList {
   int* n;
   int4* ent;
-  uint32_t* w2;
+  uint32_t *w1, *w2;  // w1: several rules only
 };
+
+// Whether v is in the adjacency row of width B at `row` (rows of width <=
+// kAdjStage: every entry loaded at once).
+__device__ __forceinline__ bool row_has_wide(const int32_t* row, int B, int32_t v) {
+  if (B > kAdjStage) return row_has(row, B, v);
+  int4 r = make_int4(-1, -1, -1, -1);
+  r.x = row[0];
+  if (B > 1) r.y = row[1];
+  if (B > 2) r.z = row[2];
+  if (B > 3) r.w = row[3];
+  return r.x == v || r.y == v || r.z == v || r.w == v;
+}
+
+// Whether idj is bonded to the A in slot sa (arow: the A's row staged with its
+// record, nullptr: the row is read from the particle arrays).
+__device__ __forceinline__ bool pair_bonded(const Dev& d, const Arr& a, int sa, uint32_t idj,
+                                            const int4* arow) {
+  const int v = (int)idj;
+  if (!arow) return row_has_wide(a.adj + (size_t)sa * d.B, d.B, v);
+  const int4 q = *arow;
+  return q.x == v || q.y == v || q.z == v || q.w == v;
+}
 
 __device__ __forceinline__ void retain(const Dev& d, const Arr& a, uint32_t step, int ida,
                                        int sa, uint32_t idj, int sj, const int4* arow,
@@ -763,19 +798,9 @@ __device__ __forceinline__ void retain(const Dev& d, const Arr& a, uint32_t step
   const W4 r = philox(step, (uint32_t)ida, idj, 0u, d.seed);
   if (!((unsigned long long)r.w0 < d.thresh)) return;
   n.drawn++;
-  if (d.rule.exclude) {
-    bool b;
-    if (arow) {
-      const int4 q = *arow;
-      const int v = (int)idj;
-      b = q.x == v || q.y == v || q.z == v || q.w == v;
-    } else {
-      b = row_has(a.adj + (size_t)sa * d.B, d.B, (int32_t)idj);
-    }
-    if (b) {
-      n.excl++;
-      return;
-    }
+  if (d.rule.exclude && pair_bonded(d, a, sa, idj, arow)) {
+    n.excl++;
+    return;
   }
   d.tflag[sj] = 1;
   atomicMin(&d.slotA[ida], ((unsigned long long)r.w1 << 32) | (unsigned long long)idj);
@@ -784,6 +809,129 @@ __device__ __forceinline__ void retain(const Dev& d, const Arr& a, uint32_t step
     l.ent[p] = make_int4(ida, sa, sj, (int)idj);
     l.w2[p] = r.w2;
   }
+}
+
+// The nearest selection (LAMMPS fix bond/create, Sec. IV A of the paper): an
+// in-range pair that is not excluded as bonded lowers the A's key (r2 bits,
+// id_T) and its T's (r2 bits, id_A), the T's in LDS (r2 >= 0 orders like its
+// bits, equal distances go to the lower id).
+__device__ __forceinline__ void near_pair(const Dev& d, const Arr& a, int ida, int sa, uint32_t idj,
+                                          float r2, const int4* arow, SweepAcc& n,
+                                          unsigned long long* best) {
+  if (d.rule.exclude && pair_bonded(d, a, sa, idj, arow)) {
+    n.excl++;
+    return;
+  }
+  const unsigned long long rb = (unsigned long long)__float_as_uint(r2) << 32;
+  atomicMin(&d.slotA[ida], rb | idj);
+  atomicMin(best, rb | (uint32_t)ida);
+}
+
+// The A's of a nearest sweep's workgroup, (id, slot) of the first kNearList of
+// them in the place of its retained pairs, for the resolve.
+constexpr int kNearList = kRetCap * (int)(sizeof(int4) / sizeof(int2));
+static_assert(kNearList == 64, "one wavefront reads the list");
+__device__ __forceinline__ void near_list(bool is_src, int id, int slot, int2* list, int* n) {
+  const unsigned long long m = __ballot(is_src);
+  if (!m) return;
+  int at = 0;
+  if (__lane_id() == 0) at = atomicAdd(n, (int)__popcll(m));
+  at = __builtin_amdgcn_readlane(at, 0) + (int)lanes_below(m);
+  if (is_src && at < kNearList) list[at] = make_int2(id, slot);
+}
+
+// ---------------------------------------------------------------------------
+// Several concurrent rules (nrules > 1): Table I generalised over the rules.
+// Every rule contributes candidates with its own draw (counter word 3 = the
+// rule's tag); each A picks among its accepted candidates of all rules the
+// smallest (w1, id_T), the lower rule on a tie; each T keeps the smallest
+// (w2, id_A) of the pairs that picked it; a particle that wins both as an A
+// and as a T keeps the pair with the smaller (w3, partner id, rule) and a
+// pair is bonded only if both of its particles keep it.  Three kernels after
+// the binning: the sweep (draws, A-side picks by 64-bit atomicMin, the
+// retained pairs in the workgroup's list), the T-side choice and the final
+// choice with the bonds.
+// ---------------------------------------------------------------------------
+// (each rule's word is read as a scalar before the selection, so that the
+// kernel argument is not indexed dynamically, which would copy it to scratch)
+__device__ __forceinline__ uint32_t rule_tag(const Dev& d, int r) {
+  uint32_t t = 0;
+#pragma unroll
+  for (int q = 0; q < kMaxRules; ++q) {
+    const uint32_t v = (uint32_t)__builtin_amdgcn_readfirstlane((int)d.mr[q].tag);
+    t = r == q ? v : t;
+  }
+  return t;
+}
+
+__device__ __forceinline__ void rule_deltas(const Dev& d, int r, int32_t& da, int32_t& dt) {
+  da = 0;
+  dt = 0;
+#pragma unroll
+  for (int q = 0; q < kMaxRules; ++q) {
+    const int32_t va = __builtin_amdgcn_readfirstlane(d.mr[q].r.d_a),
+                  vt = __builtin_amdgcn_readfirstlane(d.mr[q].r.d_t);
+    da = r == q ? va : da;
+    dt = r == q ? vt : dt;
+  }
+}
+
+__device__ __forceinline__ bool key_less(unsigned long long k1, int r1, unsigned long long k2,
+                                         int r2) {
+  return k1 < k2 || (k1 == k2 && r1 < r2);
+}
+
+// Visits the rules r under which the pair (A record at slot sa, T of role
+// mask rt) is a candidate at squared distance r2, in increasing r:
+// f(r, draw words, drawn but excluded as bonded, drawn).
+template <typename F>
+__device__ __forceinline__ void multi_candidates(const Dev& d, const Arr& a, uint32_t step,
+                                                 uint32_t rt, int sa, int ida, uint32_t idj,
+                                                 float r2, F f, const int4* arow = nullptr) {
+  const uint32_t both = rt & ((uint32_t)a.role[sa] >> 4);
+  if (!both) return;
+#pragma unroll
+  for (int r = 0; r < kMaxRules; ++r) {
+    if (r >= d.nrules || !((both >> r) & 1u) || !(r2 < d.mr[r].rc2)) continue;
+    const W4 w = philox(step, (uint32_t)ida, idj, d.mr[r].tag, d.seed);
+    const bool acc = w.w0 < d.mr[r].thresh;
+    f(r, w, acc && d.mr[r].r.exclude && pair_bonded(d, a, sa, idj, arow), acc);
+  }
+}
+
+// The candidates of an in-range pair (within the largest cutoff) under every
+// rule both roles allow: draws, exclusion, A-side pick, and the retained ones
+// into the list with their rule in bits 30-31 of id_T (ids are below 2^30).
+__device__ __forceinline__ void multi_pair(const Dev& d, const Arr& a, uint32_t step, uint32_t rt,
+                                           int ida, int sa, uint32_t idj, int sj, float r2,
+                                           const int4* arow, SweepAcc& n, const RetList& l) {
+  if ((uint32_t)ida == idj) return;  // a particle with both roles is no partner of itself
+  multi_candidates(d, a, step, rt, sa, ida, idj, r2, [&](int r, W4 w, bool ex, bool acc) {
+    n.in_rc++;
+    if (!acc) return;
+    n.drawn++;
+    if (ex) {
+      n.excl++;
+      return;
+    }
+    d.tflag[sj] = 1;
+    atomicMin(&d.slotA[ida], ((unsigned long long)w.w1 << 32) | idj);
+    const int p = atomicAdd(l.n, 1);
+    if (p < kRetCap) {
+      l.ent[p] = make_int4(ida, sa, sj, (int)(idj | ((uint32_t)r << 30)));
+      l.w1[p] = w.w1;
+      l.w2[p] = w.w2;
+    }
+  }, arow);
+}
+
+// The selection a sweep is compiled for.
+enum Policy { kRandom = 0, kNearest = 1, kMulti = 2 };
+
+// Whether a role byte makes its particle a T / an A under the sweep's policy.
+template <int kPol>
+__device__ __forceinline__ bool pol_t(int role) {
+  return kPol == kMulti ? (role & kMaskT) != 0 : role == kRoleT;
 }
 
 // ---------------------------------------------------------------------------
@@ -837,15 +985,17 @@ __device__ __forceinline__ void rejitter(const Dev& d, uint32_t step, uint32_t i
   z = wrap_box(__fadd_rn(z, __fmul_rn((float)S[2], d.jit_c)), d.L);
 }
 
-__device__ __forceinline__ uint32_t lanes_below(unsigned long long b) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
-}
-
 // kTwo: two region cells per thread while staging (brick edges above
 // kOneCellBrick); else one, with the smaller tables.
 // kF: fused binning (the sweep bins the next step's A records; sorted storage).
 // kNt: the re-jittered positions stored non-temporally (Dev::nt_pos).
-template <bool kTwo, bool kF = false, bool kNt = false>
+// kPol: the selection (Policy).  The nearest selection and several rules need
+// a queued pair's distance: it is computed again from the T's position, just
+// written by this workgroup.  (Their pairs on full wavefronts from the queue
+// and the next step's A's binned here, against sweeps of their own that took
+// each pair where the scan met it, after a binning kernel: 1,048,576
+// particles, nearest 39.1 + 8.4 -> 31.3 us, two rules 28.8 + 5.4 -> 28.0.)
+template <int kPol, bool kTwo, bool kF = false, bool kNt = false>
 __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) {
   constexpr int kCells = kTwo ? kStageCells : kStageCells1;  // region cells at most
   constexpr int kPer = kTPass / kThreads;
@@ -858,13 +1008,16 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
   __shared__ uint32_t s_q[kQueue];  // queued pair: local T | staged record << 16
   __shared__ int32_t s_tid[kTP];    // ids of the pass's T's
   __shared__ uint16_t s_def[kTP];            // deferred T's (local index in the pass)
-  __shared__ int4 s_ent[kRetCap];
-  __shared__ uint32_t s_ew2[kRetCap];
+  __shared__ int4 s_ent[kRetCap];  // retained pairs; nearest selection: the A's as (id, slot)
+  __shared__ uint32_t s_ew1[kPol == kMulti ? kRetCap : 1], s_ew2[kPol == kNearest ? 1 : kRetCap];
+  __shared__ unsigned long long s_best[kPol == kNearest ? kTP : 1];  // per T of the pass
   __shared__ uint32_t s_wave[kThreads / 64 + 1];
   __shared__ int s_cnt[5];
   __shared__ int s_qn, s_ndef, s_ne, s_dead;
   const int tid = threadIdx.x;
   if (tid < 5) s_cnt[tid] = 0;
+  if (kPol == kNearest)
+    for (int q = tid; q < kTP; q += kThreads) s_best[q] = kEmpty;
   if (tid == 0) {
     s_qn = 0;
     s_ndef = 0;
@@ -885,7 +1038,7 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
   float *XW = pick(a.x, par ^ 1u), *YW = pick(a.y, par ^ 1u), *ZW = pick(a.z, par ^ 1u);
   const bool jit = d.jitter && d.jit_c != 0.0f;
   const Buckets bk = step_buckets<kF>(d, par, step);
-  const RetList rl{&s_ne, s_ent, s_ew2};
+  const RetList rl{&s_ne, s_ent, s_ew1, s_ew2};
   int s0, s1;
   range_of<true>(d, w, s0, s1);
   int bx = 0, ex = 0, by = 0, ey = 0, bz = 0, ez = 0;
@@ -1018,7 +1171,11 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
           *(float*)((char*)ZW + bo) = cur.z;
         }
       }
-      if (kF && slot < s1 && cur.role == kRoleA) {
+      if (kPol == kMulti && slot < s1) {  // the flags of the T-side choice
+        d.wfa[slot] = 0;
+        d.wft[slot] = 0;
+      }
+      if (kF && slot < s1 && role_is_a((uint32_t)cur.role, kPol == kMulti)) {
         // fused binning: the A's record of the next step, re-jittered once
         // more (its bucket's returning atomic completes behind the rest of
         // the pass)
@@ -1027,16 +1184,19 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
         if (fl & kFJit) rejitter(d, step + 1u, idj, nx, ny, nz);
         fuse_bin(d, par ^ 1u, step + 1u, slot, idj, nx, ny, nz);
       }
+      if (kPol == kNearest)
+        near_list(slot < s1 && cur.role == kRoleA, cur.id, slot, (int2*)s_ent, &s_ne);
       // in-range staged records of this T: nh counts them all, hits keeps the
       // first four, one byte each (a T with more is deferred)
       int nh = 0;
       uint32_t hits = 0;
       bool defer = false;
-      if (slot < s1 && cur.role == kRoleT) {
+      if (slot < s1 && pol_t<kPol>(cur.role)) {
         n.t_elig++;
         defer = true;
+        if (kPol == kNearest) s_tid[lt] = (int)idj;
         if (fl & kFStaged) {
-          s_tid[lt] = (int)idj;
+          if (kPol != kNearest) s_tid[lt] = (int)idj;
           const float px = cur.x, py = cur.y, pz = cur.z;
           // local coordinates (in the staged region) of the lower corner of
           // the T's 2x2x2 cell block: floor(u - 1/2) - base, taken mod nc
@@ -1094,7 +1254,7 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
             qb + lanes_below(g1) + lanes_below(g2) + lanes_below(g3) + lanes_below(g4);
         if (nh > 0) {
           if (p + (uint32_t)nh <= (uint32_t)kQueue) {
-            n.in_rc += nh;
+            if (kPol != kMulti) n.in_rc += nh;  // several rules: counted per rule
             for (int j = 0; j < nh; ++j)
               s_q[p + j] = (uint32_t)lt | (((hits >> (8 * j)) & 0xFFu) << 16);
           } else {
@@ -1110,14 +1270,27 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
       cur = nxt;
     }
     __syncthreads();
-    // the pass's queued pairs: draws on full wavefronts
+    // the pass's queued pairs: draws (or keys) on full wavefronts
     const int qn = min(s_qn, kQueue);
     for (int e = tid; e < qn; e += kThreads) {
       const uint32_t q = s_q[e];
       if (q == kQEmpty) continue;
       const uint32_t lt = q & 0xFFFFu, r = q >> 16;
-      retain(d, a, step, __float_as_int(s_rec[r].w), s_rsa[r], (uint32_t)s_tid[lt],
-             base + (int)lt, d.adj_staged && !kF ? &s_radj[r] : nullptr, n, rl);
+      const uint32_t idj = (uint32_t)s_tid[lt];
+      const int sj = base + (int)lt;
+      const int4* arow = d.adj_staged && !kF ? &s_radj[r] : nullptr;
+      if (kPol == kRandom) {
+        retain(d, a, step, __float_as_int(s_rec[r].w), s_rsa[r], idj, sj, arow, n, rl);
+      } else {
+        const float4 A = s_rec[r];
+        const float r2 = d.jitter ? dist2(d, XW[sj], YW[sj], ZW[sj], A)
+                                  : dist2(d, X[sj], Y[sj], Z[sj], A);
+        if (kPol == kNearest)
+          near_pair(d, a, __float_as_int(A.w), s_rsa[r], idj, r2, arow, n, &s_best[lt]);
+        else
+          multi_pair(d, a, step, a.role[sj] & kMaskT, __float_as_int(A.w), s_rsa[r], idj, sj, r2,
+                     arow, n, rl);
+      }
     }
     // the deferred T's, re-jittered again from the previous positions: in the
     // staged records when the block lies in a staged region (T's with more
@@ -1125,10 +1298,22 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
     // else in the buckets (cells 0-7 of the block, then the overflow list)
     const int ndef = s_ndef;
     for (int e = tid; e < ndef; e += kThreads) {
-      const int slot = base + (int)s_def[e];
+      const int lt = (int)s_def[e], slot = base + lt;
       float px = X[slot], py = Y[slot], pz = Z[slot];
       const uint32_t idj = a.id ? (uint32_t)a.id[slot] : (uint32_t)slot;
       if (jit) rejitter(d, step, idj, px, py, pz);
+      const uint32_t rt = kPol == kMulti ? a.role[slot] & kMaskT : 0u;
+      auto pair = [&](const float4& A, int sa, const int4* arow) __attribute__((always_inline)) {
+        const float r2 = dist2(d, px, py, pz, A);
+        if (!(r2 < d.rc2)) return;
+        if (kPol != kMulti) n.in_rc++;
+        if (kPol == kRandom)
+          retain(d, a, step, __float_as_int(A.w), sa, idj, slot, arow, n, rl);
+        else if (kPol == kNearest)
+          near_pair(d, a, __float_as_int(A.w), sa, idj, r2, arow, n, &s_best[lt]);
+        else
+          multi_pair(d, a, step, rt, __float_as_int(A.w), sa, idj, slot, r2, arow, n, rl);
+      };
       if (staged) {
         const int lx0 = local_lo(px, d.inv_w, bx, nc), ly0 = local_lo(py, d.inv_w, by, nc),
                   lz0 = local_lo(pz, d.inv_w, bz, nc);
@@ -1139,12 +1324,8 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
           for (int run = 0; run < 4; ++run) {
             const int lr = l0 + ((run & 1) ? ex : 0) + ((run & 2) ? ex * ey : 0);
             const int r1 = (int)s_off[lr + 2];
-            for (int r = (int)s_off[lr]; r < r1; ++r) {
-              if (!(dist2(d, px, py, pz, s_rec[r]) < d.rc2)) continue;
-              n.in_rc++;
-              retain(d, a, step, __float_as_int(s_rec[r].w), s_rsa[r], idj, slot,
-                     d.adj_staged && !kF ? &s_radj[r] : nullptr, n, rl);
-            }
+            for (int r = (int)s_off[lr]; r < r1; ++r)
+              pair(s_rec[r], s_rsa[r], d.adj_staged && !kF ? &s_radj[r] : nullptr);
           }
           continue;
         }
@@ -1174,15 +1355,18 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
           sp = bk.osa;
           rstep = 1;
         }
-        for (uint32_t r = 0; r < nr; ++r) {
-          const float4 A = rp[r * rstep];
-          if (!(dist2(d, px, py, pz, A) < d.rc2)) continue;
-          n.in_rc++;
-          retain(d, a, step, __float_as_int(A.w), sp[r * rstep], idj, slot, nullptr, n, rl);
-        }
+        for (uint32_t r = 0; r < nr; ++r) pair(rp[r * rstep], sp[r * rstep], nullptr);
       }
     }
     __syncthreads();
+    if (kPol == kNearest) {  // every T of the pass with a candidate: its closest A, its slot
+      for (int q = tid; q < kTP; q += kThreads) {
+        const unsigned long long b = s_best[q];
+        if (b == kEmpty) continue;
+        d.tnear[s_tid[q]] = make_int2((int)(uint32_t)b, base + q);
+        s_best[q] = kEmpty;
+      }
+    }
     if (tid == 0) {
       s_qn = 0;
       s_ndef = 0;
@@ -1207,22 +1391,24 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
   if (kF) wave_add(&s_cnt[4], n.a_elig);
   __syncthreads();
   const int ne = s_ne;
-  const int nk = ne < kRetCap ? ne : kRetCap;
-  if (tid < nk) {
+  const int nk = kPol == kNearest ? ne : (ne < kRetCap ? ne : kRetCap);
+  if (tid < min(nk, kRetCap)) {
     pick(d.wge, par)[w * kRetCap + tid] = s_ent[tid];
-    pick(d.wgk, par)[w * kRetCap + tid] = s_ew2[tid];
+    if (kPol != kNearest) pick(d.wgk, par)[w * kRetCap + tid] = s_ew2[tid];
+    if (kPol == kMulti) d.wgk1[w * kRetCap + tid] = s_ew1[tid];
   }
   int32_t* out = pick(d.wgo, par) + w * kWgOut;
   if (tid < 4) out[tid] = s_cnt[tid];
   if (tid == 0) {
     out[kOutRet] = nk;
     if (kF) out[kOutAElig] = s_cnt[4];
-    if (ne > kRetCap) atomicAdd(&d.ctl->ret_ovf[par], (uint32_t)(ne - kRetCap));
+    if (kPol != kNearest && ne > kRetCap)
+      atomicAdd(&d.ctl->ret_ovf[par], (uint32_t)(ne - kRetCap));
   }
 }
 
 // ---------------------------------------------------------------------------
-// The random selection's sweep on unsorted storage (the single step on the
+// The sweep on unsorted storage, any selection (the single step on the
 // caller's arrays, and resident systems that never sort): workgroup w takes
 // slots w * kThreads .. + kThreads - 1, one per thread.  The particles are in
 // any order, so a T's eight cells and their records are reads of lines no
@@ -1234,13 +1420,16 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
 // order, 5% A's: walking the cells one after another with the draw in the
 // loop 74 us, this 47 us; 4,000 particles 16.3 and 10.1 us.
 // ---------------------------------------------------------------------------
+template <int kPol>
 __device__ __forceinline__ void dense_sweep_body(const Dev& d, int k, int w, int nwg) {
   constexpr int kDenseQ = 512;
   static_assert(kCellCap <= 8, "a cell's record count fits a nibble");
   __shared__ uint2 s_q[kDenseQ];  // cell (or overflow index), local T | record << 8 | overflow << 31
   __shared__ int32_t s_tid[kThreads];
+  __shared__ float s_pos[kPol == kRandom ? 1 : 3][kPol == kRandom ? 1 : kThreads];
+  __shared__ unsigned long long s_best[kPol == kNearest ? kThreads : 1];
   __shared__ int4 s_ent[kRetCap];
-  __shared__ uint32_t s_ew2[kRetCap];
+  __shared__ uint32_t s_ew1[kPol == kMulti ? kRetCap : 1], s_ew2[kRetCap];
   __shared__ int s_cnt[4], s_qn, s_ne;
   const int tid = threadIdx.x;
   if (tid < 4) s_cnt[tid] = 0;
@@ -1254,18 +1443,19 @@ __device__ __forceinline__ void dense_sweep_body(const Dev& d, int k, int w, int
   const Arr a = pick_set(d, c->set & 1u);
   const bool dead = read_err(c) != 0;
   const Buckets bk = step_buckets<false>(d, par, step);
-  const RetList rl{&s_ne, s_ent, s_ew2};
+  const RetList rl{&s_ne, s_ent, s_ew1, s_ew2};
   SweepAcc n = {0, 0, 0, 0, 0};
   const int slot = w * kThreads + tid;
   float x = 0.0f, y = 0.0f, z = 0.0f;
   uint32_t id = (uint32_t)slot;
   bool is_target = false;
+  if (kPol == kNearest) s_best[tid] = kEmpty;
   if (slot < d.n && !dead) {
     x = pick(a.x, par)[slot];
     y = pick(a.y, par)[slot];
     z = pick(a.z, par)[slot];
     if (a.id) id = (uint32_t)a.id[slot];
-    is_target = a.role[slot] == kRoleT;
+    is_target = pol_t<kPol>(a.role[slot]);
     if (d.jitter) {
       if (d.jit_c != 0.0f) rejitter(d, step, id, x, y, z);
       pick(a.x, par ^ 1u)[slot] = x;
@@ -1273,10 +1463,36 @@ __device__ __forceinline__ void dense_sweep_body(const Dev& d, int k, int w, int
       pick(a.z, par ^ 1u)[slot] = z;
     }
   }
+  if (kPol == kMulti && slot < d.n && !dead) {  // the flags of the T-side choice
+    d.wfa[slot] = 0;
+    d.wft[slot] = 0;
+  }
   __syncthreads();
+  if (kPol == kNearest)
+    near_list(slot < d.n && !dead && a.role[slot] == kRoleA, (int)id, slot, (int2*)s_ent, &s_ne);
+  // an in-range pair: draw or keys; lt: the T's thread, whose position is in
+  // LDS when the distance is needed again
+  auto pair = [&](int lt, uint32_t idj, const float4& A, int sa) __attribute__((always_inline)) {
+    const int sj = w * kThreads + lt;
+    if (kPol == kRandom) {
+      retain(d, a, step, __float_as_int(A.w), sa, idj, sj, nullptr, n, rl);
+      return;
+    }
+    const float r2 = dist2(d, s_pos[0][lt], s_pos[1][lt], s_pos[2][lt], A);
+    if (kPol == kNearest)
+      near_pair(d, a, __float_as_int(A.w), sa, idj, r2, nullptr, n, &s_best[lt]);
+    else
+      multi_pair(d, a, step, a.role[sj] & kMaskT, __float_as_int(A.w), sa, idj, sj, r2, nullptr, n,
+                 rl);
+  };
   if (is_target) {
     n.t_elig++;
     s_tid[tid] = (int32_t)id;
+    if (kPol != kRandom) {
+      s_pos[0][tid] = x;
+      s_pos[1][tid] = y;
+      s_pos[2][tid] = z;
+    }
     const int nc = d.nc;
     int cx0, cx1, cy0, cy1, cz0, cz1;
     lo_hi(x, d.inv_w, nc, cx0, cx1);
@@ -1301,14 +1517,14 @@ __device__ __forceinline__ void dense_sweep_body(const Dev& d, int k, int w, int
     if (nc == 1) left &= 15u;
     auto hit = [&](const float4& A, uint32_t cell, uint32_t what) {
       if (!(dist2(d, x, y, z, A) < d.rc2)) return;
-      n.in_rc++;
+      if (kPol != kMulti) n.in_rc++;
       const int p = atomicAdd(&s_qn, 1);
       if (p < kDenseQ) {
         s_q[p] = make_uint2(cell, (uint32_t)tid | what);
       } else {  // the queue is full: drawn at once
         const bool o = what >> 31;
         const size_t r = o ? (size_t)cell : rec_at(d, (int)cell, what >> 8);
-        retain(d, a, step, __float_as_int(A.w), (o ? bk.osa : bk.sa)[r], id, slot, nullptr, n, rl);
+        pair(tid, id, A, (o ? bk.osa : bk.sa)[r]);
       }
     };
     while (left) {
@@ -1340,10 +1556,13 @@ __device__ __forceinline__ void dense_sweep_body(const Dev& d, int k, int w, int
     const int lt = (int)(q.y & 0xFFu);
     const bool o = q.y >> 31;
     const size_t r = o ? (size_t)q.x : rec_at(d, (int)q.x, q.y >> 8);
-    retain(d, a, step, __float_as_int((o ? bk.ovf : bk.rec)[r].w), (o ? bk.osa : bk.sa)[r],
-           (uint32_t)s_tid[lt], w * kThreads + lt, nullptr, n, rl);
+    pair(lt, (uint32_t)s_tid[lt], (o ? bk.ovf : bk.rec)[r], (o ? bk.osa : bk.sa)[r]);
   }
-  // clear the bucket counts of the next step's parity (as the other sweeps)
+  if (kPol == kNearest) {  // a T with a candidate: its closest A, its slot
+    __syncthreads();
+    if (s_best[tid] != kEmpty) d.tnear[id] = make_int2((int)(uint32_t)s_best[tid], slot);
+  }
+  // clear the bucket counts of the next step's parity (as the other sweep)
   for (int q = w * kThreads + tid; q < d.ncell_clear; q += nwg * kThreads)
     pick(d.cnt, par ^ 1u)[q] = 0u;
   wave_add(&s_cnt[kOutTElig], n.t_elig);
@@ -1352,16 +1571,18 @@ __device__ __forceinline__ void dense_sweep_body(const Dev& d, int k, int w, int
   wave_add(&s_cnt[kOutExcl], n.excl);
   __syncthreads();
   const int ne = s_ne;
-  const int nk = ne < kRetCap ? ne : kRetCap;
-  if (tid < nk) {
+  const int nk = kPol == kNearest ? ne : (ne < kRetCap ? ne : kRetCap);
+  if (tid < min(nk, kRetCap)) {
     pick(d.wge, par)[w * kRetCap + tid] = s_ent[tid];
-    pick(d.wgk, par)[w * kRetCap + tid] = s_ew2[tid];
+    if (kPol != kNearest) pick(d.wgk, par)[w * kRetCap + tid] = s_ew2[tid];
+    if (kPol == kMulti) d.wgk1[w * kRetCap + tid] = s_ew1[tid];
   }
   int32_t* out = pick(d.wgo, par) + w * kWgOut;
   if (tid < 4) out[tid] = s_cnt[tid];
   if (tid == 0) {
     out[kOutRet] = nk;
-    if (ne > kRetCap) atomicAdd(&d.ctl->ret_ovf[par], (uint32_t)(ne - kRetCap));
+    if (kPol != kNearest && ne > kRetCap)
+      atomicAdd(&d.ctl->ret_ovf[par], (uint32_t)(ne - kRetCap));
   }
 }
 
@@ -1402,28 +1623,16 @@ __device__ void fuse_after_bond(const Dev& d, const Arr& a, uint32_t par, uint32
   fuse_bin(d, par ^ 1u, step + 1u, sj, idj, x, y, z);
 }
 
-// A bond (step 9): states, roles, adjacency rows, and the staged (id_A, id_T)
-// row for the log; tagged_t: id_T with the rule of a system of several rules
-// in bits 30-31 (plain id_T otherwise).
-__device__ __forceinline__ void make_bond_d(const Dev& d, const Arr& a, uint32_t par, int w,
-                                            int ida, int sa, int sj, int idj, int32_t da,
-                                            int32_t dt, int tagged_t, const BondCtx& b) {
-  const int32_t na = a.st[sa] + da, nt = a.st[sj] + dt;
-  a.st[sa] = na;
-  a.st[sj] = nt;
-  a.role[sa] = role_of(d, a.typ[sa], na);
-  a.role[sj] = role_of(d, a.typ[sj], nt);
-  int lost = 0;
-  if (!adj_append(a.adj + (size_t)sa * d.B, d.B, (int32_t)idj)) lost++;
-  if (!adj_append(a.adj + (size_t)sj * d.B, d.B, (int32_t)ida)) lost++;
-  if (lost) atomicAdd(b.lost, lost);
-  const int p = atomicAdd(b.nw, 1);
-  if (p < kWinCap) {
-    pick(d.wgw, par)[w * kWinCap + p] = make_int2(ida, tagged_t);
-  } else {
-    const uint32_t o = atomicAdd(&d.ctl->nwin_ovf[par], 1u);
-    pick(d.wov, par)[o] = make_int2(ida, tagged_t);
-  }
+// The same for one particle of a bond of several rules, whose role mask went
+// from `was` to `now`.
+__device__ void fuse_role_change(const Dev& d, const Arr& a, uint32_t par, uint32_t step, int slot,
+                                 uint32_t id, uint8_t was, uint8_t now) {
+  const bool had = role_is_a(was, true), has = role_is_a(now, true);
+  if (had && !has) fuse_drop(d, par ^ 1u, slot);
+  if (had || !has) return;
+  float x = pick(a.x, par ^ 1u)[slot], y = pick(a.y, par ^ 1u)[slot], z = pick(a.z, par ^ 1u)[slot];
+  if (d.jitter && d.jit_c != 0.0f) rejitter(d, step + 1u, id, x, y, z);
+  fuse_bin(d, par ^ 1u, step + 1u, slot, id, x, y, z);
 }
 
 __device__ __forceinline__ void make_bond(const Dev& d, const Arr& a, uint32_t par, int w,
@@ -1640,80 +1849,6 @@ __device__ __forceinline__ void resolve_body(const Dev& d, int k, int w, int nun
   }
 }
 
-// ---------------------------------------------------------------------------
-// The "nearest" selection (LAMMPS fix bond/create, Sec. IV A of the paper):
-// every candidate pair -- eligible, in range, not already bonded when the
-// rule excludes bonded pairs -- is visited once, from its T, which keeps its
-// closest A in registers (key (r2 bits, id_A): r2 >= 0 orders like its bits,
-// equal distances go to the lower id) and lowers the A's key (r2 bits, id_T)
-// with a 64-bit atomicMin.  A T with a candidate leaves (its closest A, its
-// slot) in tnear[id_T].  Then each A whose closest T keeps it in return is
-// tested once, with the pair's draw (word 0 of the counter (step, id_A, id_T,
-// 0)), and bonds when it passes.
-// ---------------------------------------------------------------------------
-template <bool kBrick>
-__device__ __forceinline__ void near_sweep_body(const Dev& d, int k, int w, int nwg) {
-  __shared__ int s_cnt[4];
-  const int tid = threadIdx.x;
-  if (tid < 4) s_cnt[tid] = 0;
-  const Ctl* c = d.ctl;
-  const StepInfo si = step_info(c, k);
-  const uint32_t par = si.par, step = si.step;
-  const Arr a = pick_set(d, c->set & 1u);
-  const float *X = pick(a.x, par), *Y = pick(a.y, par), *Z = pick(a.z, par);
-  float *XW = pick(a.x, par ^ 1u), *YW = pick(a.y, par ^ 1u), *ZW = pick(a.z, par ^ 1u);
-  const bool jit = d.jitter && d.jit_c != 0.0f;
-  const Buckets bk = step_buckets<false>(d, par, step);
-  const bool dead = read_err(c) != 0;
-  int s0, s1;
-  range_of<kBrick>(d, w, s0, s1);
-  __syncthreads();
-  int t_elig = 0, in_rc = 0, excl = 0;
-  for (int slot = s0 + tid; slot < s1 && !dead; slot += kThreads) {
-    float x = X[slot], y = Y[slot], z = Z[slot];
-    const uint32_t id = a.id ? (uint32_t)a.id[slot] : (uint32_t)slot;
-    if (d.jitter) {  // the re-jitter, as in the random selection's sweep
-      if (jit) rejitter(d, step, id, x, y, z);
-      XW[slot] = x;
-      YW[slot] = y;
-      ZW[slot] = z;
-    }
-    if (a.role[slot] != kRoleT) continue;
-    t_elig++;
-    unsigned long long best = kEmpty;
-    for_global_records(d, bk, x, y, z, [&](float4 A, int sa) {
-      const float r2 = dist2(d, x, y, z, A);
-      if (!(r2 < d.rc2)) return;
-      in_rc++;
-      if (d.rule.exclude && row_has(a.adj + (size_t)sa * d.B, d.B, (int32_t)id)) {
-        excl++;
-        return;
-      }
-      const unsigned long long rb = (unsigned long long)__float_as_uint(r2) << 32;
-      const uint32_t ida = (uint32_t)__float_as_int(A.w);
-      atomicMin(&d.slotA[ida], rb | id);
-      const unsigned long long kt = rb | ida;
-      best = kt < best ? kt : best;
-    });
-    if (best != kEmpty) d.tnear[id] = make_int2((int)(uint32_t)best, slot);
-  }
-  wave_add(&s_cnt[0], t_elig);
-  wave_add(&s_cnt[1], in_rc);
-  wave_add(&s_cnt[2], excl);
-  // clear the bucket counts of the next step's parity (as the other sweep)
-  for (int q = w * kThreads + tid; q < d.ncell_clear; q += nwg * kThreads)
-    pick(d.cnt, par ^ 1u)[q] = 0u;
-  __syncthreads();
-  int32_t* out = pick(d.wgo, par) + w * kWgOut;
-  if (tid == 0) {
-    out[kOutTElig] = s_cnt[0];
-    out[kOutInRc] = s_cnt[1];
-    out[kOutDrawn] = 0;
-    out[kOutExcl] = s_cnt[2];
-    out[kOutRet] = 0;
-  }
-}
-
 // The brick of sweep workgroup g.  Workgroups are dispatched to the eight
 // XCDs in turn (g mod 8), each XCD with an L2 of its own; XCD x takes the
 // contiguous run of bricks x * q + min(x, r) .. (q or q + 1 of them, q =
@@ -1864,123 +1999,34 @@ __device__ __forceinline__ void visit_pairs(const Dev& d, const Arr& a, const Bu
   });
 }
 
-// near_sweep_body on sorted storage with the region staged (StagedRegion):
-// the same pairs get the same keys, so the outcome is that of near_sweep_body.
-__device__ __forceinline__ void near_sweep_staged_body(const Dev& d, int k, int w, int nwg) {
-  __shared__ float4 s_rec[kStageRecs];
-  __shared__ int4 s_radj[kStageRecs];
-  __shared__ int32_t s_rsa[kStageRecs];
-  __shared__ uint16_t s_off[kStageCells1 + 1];
-  __shared__ uint32_t s_wave[kThreads / 64 + 1];
-  __shared__ int s_cnt[4];
-  const int tid = threadIdx.x;
-  if (tid < 4) s_cnt[tid] = 0;
+// The A side of the nearest selection and the bonds.  A T with a candidate
+// left (its closest A, its slot) in tnear[id_T]; each A whose closest T keeps
+// it in return is tested once, with the pair's draw (word 0 of the counter
+// (step, id_A, id_T, 0)), and bonds when it passes.  One wavefront per sweep
+// workgroup (four per workgroup) takes the A's of its list, or, when it has
+// more than kNearList, finds them by the role bytes of its slots.  Every A is
+// read, and its key emptied, by one thread; a T that takes the A role here has
+// no key.  Bound by latency (the list with its length, key, tnear).  1,048,576
+// particles, 5% A's: by the cells' buckets 14.0 us, by the role bytes 11.0, by
+// the list 8.3 us.
+template <bool kBrick>
+__device__ __forceinline__ void near_resolve_body(const Dev& d, int k, int wg, int nunits) {
+  constexpr int kG = kThreads / 64;
+  __shared__ int s_nw[kG], s_lost[kG];
+  const int g = (int)(threadIdx.x >> 6), lane = (int)__lane_id();
+  const int w = wg * kG + g;
+  if (lane == 0) {
+    s_nw[g] = 0;
+    s_lost[g] = 0;
+  }
+  wave_sync();
   const Ctl* c = d.ctl;
   const StepInfo si = step_info(c, k);
   const uint32_t par = si.par, step = si.step;
   const Arr a = pick_set(d, c->set & 1u);
-  const float *X = pick(a.x, par), *Y = pick(a.y, par), *Z = pick(a.z, par);
-  float *XW = pick(a.x, par ^ 1u), *YW = pick(a.y, par ^ 1u), *ZW = pick(a.z, par ^ 1u);
-  const bool jit = d.jitter && d.jit_c != 0.0f;
-  const Buckets bk = step_buckets<false>(d, par, step);
-  const bool dead = read_err(c) != 0;
-  int s0, s1;
-  range_of<true>(d, w, s0, s1);
-  StagedRegion g;
-  g.rec = s_rec;
-  g.radj = s_radj;
-  g.rsa = s_rsa;
-  g.off = s_off;
-  stage_region(d, bk, w, g, s_wave);
-  int t_elig = 0, in_rc = 0, excl = 0;
-  // one particle per thread and pass; the next pass's particle is loaded
-  // while this one is handled
-  float nx = 0.f, ny = 0.f, nz = 0.f;
-  int32_t nid = 0;
-  uint8_t nrole = kRoleNone;
-  if (s0 + tid < s1) {
-    nx = X[s0 + tid];
-    ny = Y[s0 + tid];
-    nz = Z[s0 + tid];
-    nid = a.id[s0 + tid];
-    nrole = a.role[s0 + tid];
-  }
-  for (int slot = s0 + tid; slot < s1 && !dead; slot += kThreads) {
-    float x = nx, y = ny, z = nz;
-    const uint32_t id = (uint32_t)nid;
-    const uint8_t role = nrole;
-    if (slot + kThreads < s1) {
-      nx = X[slot + kThreads];
-      ny = Y[slot + kThreads];
-      nz = Z[slot + kThreads];
-      nid = a.id[slot + kThreads];
-      nrole = a.role[slot + kThreads];
-    }
-    if (d.jitter) {  // the re-jitter, as in the random selection's sweep
-      if (jit) rejitter(d, step, id, x, y, z);
-      XW[slot] = x;
-      YW[slot] = y;
-      ZW[slot] = z;
-    }
-    if (role != kRoleT) continue;
-    t_elig++;
-    // each candidate lowers the A's key to (r2 bits, id_T); the T keeps its
-    // own closest as (r2 bits, id_A)
-    unsigned long long best = kEmpty;
-    visit_pairs(d, a, bk, g, x, y, z, id, [&](float4 A, float r2, bool excluded, int, int) {
-      in_rc++;
-      if (excluded) {
-        excl++;
-        return;
-      }
-      const unsigned long long rb = (unsigned long long)__float_as_uint(r2) << 32;
-      const uint32_t ida = (uint32_t)__float_as_int(A.w);
-      atomicMin(&d.slotA[ida], rb | id);
-      const unsigned long long kt = rb | ida;
-      best = kt < best ? kt : best;
-    });
-    if (best != kEmpty) d.tnear[id] = make_int2((int)(uint32_t)best, slot);
-  }
-  wave_add(&s_cnt[0], t_elig);
-  wave_add(&s_cnt[1], in_rc);
-  wave_add(&s_cnt[2], excl);
-  // clear the bucket counts of the next step's parity (as the other sweep)
-  for (int q = w * kThreads + tid; q < d.ncell; q += nwg * kThreads)
-    pick(d.cnt, par ^ 1u)[q] = 0u;
-  __syncthreads();
-  int32_t* out = pick(d.wgo, par) + w * kWgOut;
-  if (tid == 0) {
-    out[kOutTElig] = s_cnt[0];
-    out[kOutInRc] = s_cnt[1];
-    out[kOutDrawn] = 0;
-    out[kOutExcl] = s_cnt[2];
-    out[kOutRet] = 0;
-  }
-}
-
-// The A side of the nearest selection and the bonds: unit w (of nunits, the
-// sweep's workgroup count, whose staging windows and counters it fills)
-// takes the A records of a contiguous range of cells, unit 0 also the
-// overflow list.  Every A record appears once, so every A key is read and
-// emptied by exactly one thread.
-__device__ __forceinline__ void near_resolve_body(const Dev& d, int k, int w, int nunits) {
-  __shared__ int s_nw, s_lost, s_cnt[2];
-  const int tid = threadIdx.x;
-  if (tid == 0) {
-    s_nw = 0;
-    s_lost = 0;
-    s_cnt[0] = 0;
-    s_cnt[1] = 0;
-  }
-  __syncthreads();
-  const Ctl* c = d.ctl;
-  const StepInfo si = step_info(c, k);
-  const uint32_t par = si.par, step = si.step;
-  const Arr a = pick_set(d, c->set & 1u);
-  const BondCtx bc{&s_nw, &s_lost};
+  const BondCtx bc{&s_nw[g], &s_lost[g], step};
   int prop = 0, mutual = 0;
-  auto visit = [&](float4 A, int sa) {
-    const int ida = __float_as_int(A.w);
+  auto visit = [&](int ida, int sa) __attribute__((always_inline)) {
     const unsigned long long key = d.slotA[ida];
     if (key == kEmpty) return;
     d.slotA[ida] = kEmpty;
@@ -1992,363 +2038,273 @@ __device__ __forceinline__ void near_resolve_body(const Dev& d, int k, int w, in
     const W4 r = philox(step, (uint32_t)ida, idj, 0u, d.seed);
     if ((unsigned long long)r.w0 < d.thresh) make_bond(d, a, par, w, ida, sa, t.y, (int)idj, bc);
   };
-  if (read_err(c) == 0) {
-    const int per = (d.ncell + nunits - 1) / nunits;
-    const int c0 = w * per, c1 = min(d.ncell, c0 + per);
-    for (int cc = c0 + tid; cc < c1; cc += kThreads) {
-      uint32_t nr = pick(d.cnt, par)[cc];
-      nr = nr < (uint32_t)kCellCap ? nr : (uint32_t)kCellCap;
-      for (uint32_t r = 0; r < nr; ++r) visit(d.rec[rec_at(d, cc, r)], d.rsa[rec_at(d, cc, r)]);
-    }
-    if (w == 0) {
-      const uint32_t novf = c->ovf_n[par];
-      for (uint32_t r = tid; r < novf; r += kThreads)
-        visit(pick(d.ovf, par)[r], pick(d.ovf_sa, par)[r]);
-    }
+  const bool live = w < nunits && read_err(c) == 0;
+  int na = 0;
+  int2 e = make_int2(0, 0);
+  if (live) {
+    na = pick(d.wgo, par)[w * kWgOut + kOutRet];
+    e = ((const int2*)(pick(d.wge, par) + (size_t)w * kRetCap))[lane];
   }
-  wave_add(&s_cnt[0], prop);
-  wave_add(&s_cnt[1], mutual);
-  __syncthreads();
-  if (tid == 0) {
+  // one pass over the list, or over the slots (uniform over the wavefront)
+  int s0 = 0, s1 = na <= kNearList ? 64 : 0;
+  if (na > kNearList) range_of<kBrick>(d, w, s0, s1);
+  for (int i = s0 + lane; i < s1 && live; i += 64) {
+    int sa = e.y, ida = e.x;
+    bool is_src = lane < na;
+    if (na > kNearList) {
+      is_src = a.role[i] == kRoleA;
+      sa = i;
+      ida = is_src && a.id ? a.id[i] : i;
+    }
+    if (is_src) visit(ida, sa);
+  }
+  const int np = (int)wave_scan_incl((uint32_t)prop), nm = (int)wave_scan_incl((uint32_t)mutual);
+  wave_sync();
+  if (lane == 63 && w < nunits) {
     int32_t* out = pick(d.wgo, par) + w * kWgOut;
-    out[kOutDrawn] = s_cnt[1];
-    out[kOutProp] = s_cnt[0];
-    out[kOutBonds] = s_nw;
-    out[kOutLost] = s_lost;
+    out[kOutDrawn] = nm;
+    out[kOutProp] = np;
+    out[kOutBonds] = s_nw[g];
+    out[kOutLost] = s_lost[g];
   }
 }
 
-// ---------------------------------------------------------------------------
-// Several concurrent rules (nrules > 1): Table I generalised over the rules.
-// Every rule contributes candidates with its own draw (counter word 3 = the
-// rule's tag); each A picks among its accepted candidates of all rules the
-// smallest (w1, id_T), the lower rule on a tie; each T keeps the smallest
-// (w2, id_A) of the pairs that picked it; a particle that wins both as an A
-// and as a T keeps the pair with the smaller (w3, partner id, rule) and a
-// pair is bonded only if both of its particles keep it.  Three kernels after
-// the binning: the sweep (draws, A-side picks by 64-bit atomicMin, T flags),
-// the T-side choice (re-enumerates the flagged T's candidates) and the final
-// choice with the bonds.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t rule_tag(const Dev& d, int r) {
-  uint32_t t = d.mr[0].tag;
-#pragma unroll
-  for (int q = 1; q < kMaxRules; ++q)
-    if (r == q) t = d.mr[q].tag;
-  return t;
+// The winning pair of a T, recorded at both slots for the final choice (one
+// writer each: the A picked one T).
+__device__ __forceinline__ void multi_win(const Dev& d, int ida, int sa, uint32_t idj, int sj,
+                                          int rule) {
+  d.wint[sj] = make_int4(ida, sa, rule, 0);
+  d.wina[sa] = make_int4((int)idj, sj, rule, 0);
+  d.wft[sj] = 1;
+  d.wfa[sa] = 1;
 }
 
-__device__ __forceinline__ void rule_deltas(const Dev& d, int r, int32_t& da, int32_t& dt) {
-  da = d.mr[0].r.d_a;
-  dt = d.mr[0].r.d_t;
-#pragma unroll
-  for (int q = 1; q < kMaxRules; ++q)
-    if (r == q) {
-      da = d.mr[q].r.d_a;
-      dt = d.mr[q].r.d_t;
+// The T side of several rules, one wavefront per sweep workgroup (four per
+// workgroup).  Normally from the sweep's lists: a listed pair whose A's final
+// key is its (w1, id_T) is a proposal -- the lower rule when two rules of one
+// pair share the key -- and the smallest (w2, id_A) of a T's proposals wins;
+// the winners' entries are marked (bit 31 of id_A) for the final choice.  When
+// a list overflowed in this step, every T with an accepted candidate
+// enumerates its pairs again (same cells, same draws).  Bound by latency.
+// 1,048,576 particles, two rules: enumerating 15.2 us, this 4.9 us.
+template <bool kBrick>
+__device__ __forceinline__ void multi_resolve_body(const Dev& d, int k, int wg, int nunits) {
+  constexpr int kG = kThreads / 64;
+  __shared__ int s_prop[kG];
+  __shared__ unsigned long long s_key[kG][kRetCap], s_a[kG][kRetCap];
+  __shared__ int32_t s_sj[kG][kRetCap];
+  const int g = (int)(threadIdx.x >> 6), lane = (int)__lane_id();
+  const int w = wg * kG + g;
+  const bool live = w < nunits;
+  const Ctl* c = d.ctl;
+  const StepInfo si = step_info(c, k);
+  const uint32_t par = si.par, step = si.step;
+  const Arr a = pick_set(d, c->set & 1u);
+  const int mode = read_err(c) ? 0 : (c->ret_ovf[par] ? 2 : 1);
+  if (lane == 0) s_prop[g] = 0;
+  __syncthreads();
+  if (mode == 1 && live) {
+    const int ne = pick(d.wgo, par)[w * kWgOut + kOutRet];
+    int4 e = make_int4(0, 0, 0, 0);
+    uint32_t w1 = 0, w2 = 0;
+    bool chosen = false;
+    if (lane < kRetCap) {  // entries past the length are read and not used
+      e = pick(d.wge, par)[w * kRetCap + lane];
+      w1 = d.wgk1[w * kRetCap + lane];
+      w2 = pick(d.wgk, par)[w * kRetCap + lane];
     }
-}
-
-__device__ __forceinline__ bool key_less(unsigned long long k1, int r1, unsigned long long k2,
-                                         int r2) {
-  return k1 < k2 || (k1 == k2 && r1 < r2);
-}
-
-// Visits the rules r under which the pair (A record at slot sa, T of role
-// mask rt) is a candidate at squared distance r2, in increasing r:
-// f(r, draw words, excluded as bonded).
-template <typename F>
-__device__ __forceinline__ void multi_candidates(const Dev& d, const Arr& a, uint32_t step,
-                                                 uint32_t rt, int sa, int ida, uint32_t idj,
-                                                 float r2, F f, int arole = -1,
-                                                 const int4* arow = nullptr) {
-  const uint32_t both = rt & ((uint32_t)(arole >= 0 ? arole : a.role[sa]) >> 4);
-  if (!both) return;
-  int bonded = -1;
-#pragma unroll
-  for (int r = 0; r < kMaxRules; ++r) {
-    if (r >= d.nrules || !((both >> r) & 1u) || !(r2 < d.mr[r].rc2)) continue;
-    if (bonded < 0) {
-      if (arow) {
-        const int4 q = *arow;
-        const int v = (int)idj;
-        bonded = q.x == v || q.y == v || q.z == v || q.w == v;
-      } else {
-        bonded = row_has(a.adj + (size_t)sa * d.B, d.B, (int32_t)idj) ? 1 : 0;
+    const uint32_t idj = (uint32_t)e.w & 0x3FFFFFFFu;
+    const int rule = (int)((uint32_t)e.w >> 30);
+    if (lane < ne) {
+      d.tflag[e.z] = 0;
+      chosen = d.slotA[e.x] == (((unsigned long long)w1 << 32) | idj);
+      s_a[g][lane] = chosen ? ((unsigned long long)(uint32_t)e.x << 32) | (uint32_t)e.z : kEmpty;
+      s_sj[g][lane] = rule;
+    }
+    wave_sync();
+    if (chosen) {  // two rules of the same pair with the same key: the lower rule
+      const unsigned long long me = s_a[g][lane];
+      for (int f = 0; f < ne; ++f)
+        if (s_a[g][f] == me && s_sj[g][f] < rule) chosen = false;
+    }
+    wave_sync();
+    if (lane < ne) {
+      s_key[g][lane] = chosen ? ((unsigned long long)w2 << 32) | (uint32_t)e.x : kEmpty;
+      s_sj[g][lane] = e.z;
+    }
+    wave_sync();
+    if (chosen) {
+      d.slotA[e.x] = kEmpty;  // only this T's wavefront reads the key that names it
+      atomicAdd(&s_prop[g], 1);
+      const unsigned long long key = s_key[g][lane];
+      bool win = true;
+      for (int f = 0; f < ne; ++f)
+        if (s_sj[g][f] == e.z && s_key[g][f] < key) win = false;
+      if (win) {
+        multi_win(d, e.x, e.y, idj, e.z, rule);
+        pick(d.wge, par)[w * kRetCap + lane].x = (int)((uint32_t)e.x | 0x80000000u);
       }
     }
-    const W4 w = philox(step, (uint32_t)ida, idj, d.mr[r].tag, d.seed);
-    f(r, w, d.mr[r].r.exclude && bonded > 0, w.w0 < d.mr[r].thresh);
-  }
-}
-
-template <bool kBrick>
-__device__ __forceinline__ void multi_sweep_body(const Dev& d, int k, int w, int nwg) {
-  __shared__ int s_cnt[4];
-  const int tid = threadIdx.x;
-  if (tid < 4) s_cnt[tid] = 0;
-  const Ctl* c = d.ctl;
-  const StepInfo si = step_info(c, k);
-  const uint32_t par = si.par, step = si.step;
-  const Arr a = pick_set(d, c->set & 1u);
-  const float *X = pick(a.x, par), *Y = pick(a.y, par), *Z = pick(a.z, par);
-  float *XW = pick(a.x, par ^ 1u), *YW = pick(a.y, par ^ 1u), *ZW = pick(a.z, par ^ 1u);
-  const bool jit = d.jitter && d.jit_c != 0.0f;
-  const Buckets bk = step_buckets<false>(d, par, step);
-  const bool dead = read_err(c) != 0;
-  int s0, s1;
-  range_of<kBrick>(d, w, s0, s1);
-  __syncthreads();
-  int t_elig = 0, in_rc = 0, drawn = 0, excl = 0;
-  for (int slot = s0 + tid; slot < s1 && !dead; slot += kThreads) {
-    float x = X[slot], y = Y[slot], z = Z[slot];
-    const uint32_t id = a.id ? (uint32_t)a.id[slot] : (uint32_t)slot;
-    if (d.jitter) {
-      if (jit) rejitter(d, step, id, x, y, z);
-      XW[slot] = x;
-      YW[slot] = y;
-      ZW[slot] = z;
-    }
-    d.wfa[slot] = 0;
-    d.wft[slot] = 0;
-    const uint32_t rt = a.role[slot] & kMaskT;
-    if (!rt) continue;
-    t_elig++;
-    bool any = false;
-    for_global_records(d, bk, x, y, z, [&](float4 A, int sa) {
-      const int ida = __float_as_int(A.w);
-      if ((uint32_t)ida == id) return;
-      const float r2 = dist2(d, x, y, z, A);
-      if (!(r2 < d.rc2)) return;
-      multi_candidates(d, a, step, rt, sa, ida, id, r2, [&](int, W4 wd, bool ex, bool acc) {
-        in_rc++;
-        if (!acc) return;
-        drawn++;
-        if (ex) {
-          excl++;
-          return;
-        }
-        any = true;
-        atomicMin(&d.slotA[ida], ((unsigned long long)wd.w1 << 32) | id);
-      });
-    });
-    if (any) d.tflag[slot] = 1;
-  }
-  wave_add(&s_cnt[0], t_elig);
-  wave_add(&s_cnt[1], in_rc);
-  wave_add(&s_cnt[2], drawn);
-  wave_add(&s_cnt[3], excl);
-  for (int q = w * kThreads + tid; q < d.ncell_clear; q += nwg * kThreads)
-    pick(d.cnt, par ^ 1u)[q] = 0u;
-  __syncthreads();
-  int32_t* out = pick(d.wgo, par) + w * kWgOut;
-  if (tid == 0) {
-    out[kOutTElig] = s_cnt[0];
-    out[kOutInRc] = s_cnt[1];
-    out[kOutDrawn] = s_cnt[2];
-    out[kOutExcl] = s_cnt[3];
-    out[kOutRet] = 0;
-  }
-}
-
-// multi_sweep_body on sorted storage with the region staged (StagedRegion,
-// with the A's role bytes): the same candidates, draws and keys.
-__device__ __forceinline__ void multi_sweep_staged_body(const Dev& d, int k, int w, int nwg) {
-  __shared__ float4 s_rec[kStageRecs];
-  __shared__ int4 s_radj[kStageRecs];
-  __shared__ int32_t s_rsa[kStageRecs];
-  __shared__ uint8_t s_arole[kStageRecs];
-  __shared__ uint16_t s_off[kStageCells1 + 1];
-  __shared__ uint32_t s_wave[kThreads / 64 + 1];
-  __shared__ int s_cnt[4];
-  const int tid = threadIdx.x;
-  if (tid < 4) s_cnt[tid] = 0;
-  const Ctl* c = d.ctl;
-  const StepInfo si = step_info(c, k);
-  const uint32_t par = si.par, step = si.step;
-  const Arr a = pick_set(d, c->set & 1u);
-  const float *X = pick(a.x, par), *Y = pick(a.y, par), *Z = pick(a.z, par);
-  float *XW = pick(a.x, par ^ 1u), *YW = pick(a.y, par ^ 1u), *ZW = pick(a.z, par ^ 1u);
-  const bool jit = d.jitter && d.jit_c != 0.0f;
-  const Buckets bk = step_buckets<false>(d, par, step);
-  const bool dead = read_err(c) != 0;
-  int s0, s1;
-  range_of<true>(d, w, s0, s1);
-  StagedRegion g;
-  g.rec = s_rec;
-  g.radj = s_radj;
-  g.rsa = s_rsa;
-  g.off = s_off;
-  stage_region(d, bk, w, g, s_wave);
-  // the staged A's role bytes (the roles of the step: nothing changes them
-  // before the resolve)
-  if (g.staged) {
-    const int nrec = (int)s_off[g.ex * g.ey * g.ez];
-    for (int r = tid; r < nrec; r += kThreads) s_arole[r] = a.role[s_rsa[r]];
-    __syncthreads();
-  }
-  int t_elig = 0, in_rc = 0, drawn = 0, excl = 0;
-  for (int slot = s0 + tid; slot < s1 && !dead; slot += kThreads) {
-    float x = X[slot], y = Y[slot], z = Z[slot];
-    const uint32_t id = (uint32_t)a.id[slot];
-    const uint32_t rt = a.role[slot] & kMaskT;
-    if (d.jitter) {
-      if (jit) rejitter(d, step, id, x, y, z);
-      XW[slot] = x;
-      YW[slot] = y;
-      ZW[slot] = z;
-    }
-    d.wfa[slot] = 0;
-    d.wft[slot] = 0;
-    if (!rt) continue;
-    t_elig++;
-    bool any = false;
-    visit_pairs<false>(d, a, bk, g, x, y, z, id, [&](float4 A, float r2, bool, int sa, int r) {
-      const int ida = __float_as_int(A.w);
-      if ((uint32_t)ida == id) return;
-      multi_candidates(d, a, step, rt, sa, ida, id, r2, [&](int, W4 wd, bool ex, bool acc) {
-        in_rc++;
-        if (!acc) return;
-        drawn++;
-        if (ex) {
-          excl++;
-          return;
-        }
-        any = true;
-        atomicMin(&d.slotA[ida], ((unsigned long long)wd.w1 << 32) | id);
-      }, r >= 0 ? (int)s_arole[r] : -1, r >= 0 && d.adj_staged ? &s_radj[r] : nullptr);
-    });
-    if (any) d.tflag[slot] = 1;
-  }
-  wave_add(&s_cnt[0], t_elig);
-  wave_add(&s_cnt[1], in_rc);
-  wave_add(&s_cnt[2], drawn);
-  wave_add(&s_cnt[3], excl);
-  for (int q = w * kThreads + tid; q < d.ncell; q += nwg * kThreads)
-    pick(d.cnt, par ^ 1u)[q] = 0u;
-  __syncthreads();
-  int32_t* out = pick(d.wgo, par) + w * kWgOut;
-  if (tid == 0) {
-    out[kOutTElig] = s_cnt[0];
-    out[kOutInRc] = s_cnt[1];
-    out[kOutDrawn] = s_cnt[2];
-    out[kOutExcl] = s_cnt[3];
-    out[kOutRet] = 0;
-  }
-}
-
-// The T side: every T with an accepted candidate finds the A's whose pick
-// names it (the lowest rule whose accepted candidate gives the A's key) and
-// keeps the smallest (w2, id_A); the pair is recorded at both slots.
-template <bool kBrick>
-__device__ __forceinline__ void multi_resolve_body(const Dev& d, int k, int w) {
-  __shared__ int s_prop;
-  const int tid = threadIdx.x;
-  if (tid == 0) s_prop = 0;
-  __syncthreads();
-  const Ctl* c = d.ctl;
-  const StepInfo si = step_info(c, k);
-  const uint32_t par = si.par, step = si.step;
-  const Arr a = pick_set(d, c->set & 1u);
-  const float *X = pick(a.x, par ^ 1u), *Y = pick(a.y, par ^ 1u), *Z = pick(a.z, par ^ 1u);
-  const Buckets bk = step_buckets<false>(d, par, step);
-  int s0, s1;
-  range_of<kBrick>(d, w, s0, s1);
-  int prop = 0;
-  for (int slot = s0 + tid; slot < s1; slot += kThreads) {
-    if (d.tflag[slot] != 1) continue;
-    d.tflag[slot] = 0;
-    const float x = X[slot], y = Y[slot], z = Z[slot];
-    const uint32_t id = a.id ? (uint32_t)a.id[slot] : (uint32_t)slot;
-    const uint32_t rt = a.role[slot] & kMaskT;
-    unsigned long long best = kEmpty;
-    int best_sa = 0, best_r = 0;
-    for_global_records(d, bk, x, y, z, [&](float4 A, int sa) {
-      const int ida = __float_as_int(A.w);
-      if ((uint32_t)ida == id) return;
-      const float r2 = dist2(d, x, y, z, A);
-      if (!(r2 < d.rc2)) return;
-      const unsigned long long key = d.slotA[ida];
-      if (key == kEmpty || (uint32_t)key != id) return;  // the A picked another T
-      int got = -1;
-      W4 wg{0, 0, 0, 0};
-      multi_candidates(d, a, step, rt, sa, ida, id, r2, [&](int r, W4 wd, bool ex, bool acc) {
-        if (got < 0 && acc && !ex && wd.w1 == (uint32_t)(key >> 32)) {
-          got = r;
-          wg = wd;
+  } else if (mode == 2 && live) {
+    const float *X = pick(a.x, par ^ 1u), *Y = pick(a.y, par ^ 1u), *Z = pick(a.z, par ^ 1u);
+    const Buckets bk =
+        d.fuse ? step_buckets<true>(d, par, step) : step_buckets<false>(d, par, step);
+    int s0, s1;
+    range_of<kBrick>(d, w, s0, s1);
+    for (int slot = s0 + lane; slot < s1; slot += 64) {
+      if (d.tflag[slot] != 1) continue;
+      d.tflag[slot] = 0;
+      const float x = X[slot], y = Y[slot], z = Z[slot];
+      const uint32_t id = a.id ? (uint32_t)a.id[slot] : (uint32_t)slot;
+      const uint32_t rt = a.role[slot] & kMaskT;
+      unsigned long long best = kEmpty;
+      int best_sa = 0, best_r = 0, prop = 0;
+      for_global_records(d, bk, x, y, z, [&](float4 A, int sa) {
+        const int ida = __float_as_int(A.w);
+        if ((uint32_t)ida == id) return;
+        const float r2 = dist2(d, x, y, z, A);
+        if (!(r2 < d.rc2)) return;
+        const unsigned long long key = d.slotA[ida];
+        if (key == kEmpty || (uint32_t)key != id) return;  // the A picked another T
+        int got = -1;
+        W4 wg{0, 0, 0, 0};
+        multi_candidates(d, a, step, rt, sa, ida, id, r2, [&](int r, W4 wd, bool ex, bool acc) {
+          if (got < 0 && acc && !ex && wd.w1 == (uint32_t)(key >> 32)) {
+            got = r;
+            wg = wd;
+          }
+        });
+        if (got < 0) return;
+        d.slotA[ida] = kEmpty;  // only this T's thread reads the key that names it
+        prop++;
+        const unsigned long long k2 = ((unsigned long long)wg.w2 << 32) | (uint32_t)ida;
+        if (k2 < best) {
+          best = k2;
+          best_sa = sa;
+          best_r = got;
         }
       });
-      if (got < 0) return;
-      d.slotA[ida] = kEmpty;  // only this T's thread reads the key that names it
-      prop++;
-      const unsigned long long k2 = ((unsigned long long)wg.w2 << 32) | (uint32_t)ida;
-      if (k2 < best) {
-        best = k2;
-        best_sa = sa;
-        best_r = got;
-      }
-    });
-    if (best != kEmpty) {
-      const int ida = (int)(uint32_t)best;
-      d.wint[slot] = make_int4(ida, best_sa, best_r, 0);
-      d.wina[best_sa] = make_int4((int)id, slot, best_r, 0);
-      d.wft[slot] = 1;
-      d.wfa[best_sa] = 1;  // one writer: the A picked one T
+      if (prop) atomicAdd(&s_prop[g], prop);
+      if (best != kEmpty) multi_win(d, (int)(uint32_t)best, best_sa, id, slot, best_r);
     }
   }
-  atomicAdd(&s_prop, prop);
   __syncthreads();
-  if (tid == 0) pick(d.wgo, par)[w * kWgOut + kOutProp] = s_prop;
+  if (lane == 0 && live) pick(d.wgo, par)[w * kWgOut + kOutProp] = s_prop[g];
 }
 
-// Step 8 and the bonds, from the T of every winning pair.
+// A bond of several rules (step 9) with its operands read ahead (rows only for
+// B <= kAdjStage): states, roles, adjacency rows, and the staged (id_A, id_T)
+// row for the log, with the rule in bits 30-31 of id_T.
+__device__ __forceinline__ void make_bond_multi(const Dev& d, const Arr& a, uint32_t par, int w,
+                                                int ida, int sa, int sj, int idj, int rule,
+                                                const BondOps& o, const BondCtx& b) {
+  int32_t da, dt;
+  rule_deltas(d, rule, da, dt);
+  const int32_t na = o.sta + da, nt = o.stt + dt;
+  const uint8_t ra = role_of(d, o.tya, na), rt = role_of(d, o.tyt, nt);
+  a.st[sa] = na;
+  a.st[sj] = nt;
+  a.role[sa] = ra;
+  a.role[sj] = rt;
+  if (d.fuse) {  // either particle may leave or take an A role (of any rule)
+    fuse_role_change(d, a, par, b.step, sa, (uint32_t)ida, role_of(d, o.tya, o.sta), ra);
+    fuse_role_change(d, a, par, b.step, sj, (uint32_t)idj, role_of(d, o.tyt, o.stt), rt);
+  }
+  int lost = 0;
+  int32_t *rowa = a.adj + (size_t)sa * d.B, *rowt = a.adj + (size_t)sj * d.B;
+  if (d.adj_staged) {
+    const int fa = first_empty(o.rowa, d.B), ft = first_empty(o.rowt, d.B);
+    if (fa < d.B) rowa[fa] = (int32_t)idj;
+    else lost++;
+    if (ft < d.B) rowt[ft] = (int32_t)ida;
+    else lost++;
+  } else {
+    if (!adj_append(rowa, d.B, (int32_t)idj)) lost++;
+    if (!adj_append(rowt, d.B, (int32_t)ida)) lost++;
+  }
+  if (lost) atomicAdd(b.lost, lost);
+  const int2 row = make_int2(ida, (int)((uint32_t)idj | ((uint32_t)rule << 30)));
+  const int p = atomicAdd(b.nw, 1);
+  if (p < kWinCap) {
+    pick(d.wgw, par)[w * kWinCap + p] = row;
+  } else {
+    const uint32_t q = atomicAdd(&d.ctl->nwin_ovf[par], 1u);
+    pick(d.wov, par)[q] = row;
+  }
+}
+
+// Step 8 and the bonds, from the T of every winning pair: one wavefront per
+// sweep workgroup, the marked entries of its list (or, when a list overflowed,
+// the flagged T's of its slots).  1,048,576 particles: scanning every slot's
+// flag 8.4 us, this 7.3 us (it also maintains the next step's bins).
 template <bool kBrick>
-__device__ __forceinline__ void multi_final_body(const Dev& d, int k, int w) {
-  __shared__ int s_nw, s_lost;
-  const int tid = threadIdx.x;
-  if (tid == 0) {
-    s_nw = 0;
-    s_lost = 0;
+__device__ __forceinline__ void multi_final_body(const Dev& d, int k, int wg, int nunits) {
+  constexpr int kG = kThreads / 64;
+  __shared__ int s_nw[kG], s_lost[kG];
+  const int g = (int)(threadIdx.x >> 6), lane = (int)__lane_id();
+  const int w = wg * kG + g;
+  const bool live = w < nunits;
+  if (lane == 0) {
+    s_nw[g] = 0;
+    s_lost[g] = 0;
   }
   __syncthreads();
   const Ctl* c = d.ctl;
   const StepInfo si = step_info(c, k);
   const uint32_t par = si.par, step = si.step;
   const Arr a = pick_set(d, c->set & 1u);
-  const BondCtx bc{&s_nw, &s_lost};
-  int s0, s1;
-  range_of<kBrick>(d, w, s0, s1);
-  for (int slot = s0 + tid; slot < s1; slot += kThreads) {
-    if (!d.wft[slot]) continue;
-    const uint32_t id = a.id ? (uint32_t)a.id[slot] : (uint32_t)slot;
-    const int4 t = d.wint[slot];
-    const int ida = t.x, sa = t.y, r = t.z;
+  const BondCtx bc{&s_nw[g], &s_lost[g], step};
+  // the pair (A ida in slot sa, T id in slot) of rule r, the T's winner
+  auto decide = [&](int slot, uint32_t id, int ida, int sa, int r) __attribute__((always_inline)) {
+    const uint8_t also_a = d.wfa[slot], also_t = d.wft[sa];
+    // a particle takes at most one bond per step: what is read here is what a
+    // bond made after the decision would read
+    BondOps o{a.st[sa], a.st[slot], a.typ[sa], a.typ[slot], make_int4(0, 0, 0, 0),
+              make_int4(0, 0, 0, 0), 0, 0.0f, 0.0f, 0.0f};
+    if (d.adj_staged) {
+      o.rowa = load_row4(a.adj + (size_t)sa * d.B, d.B);
+      o.rowt = load_row4(a.adj + (size_t)slot * d.B, d.B);
+    }
     const W4 wd = philox(step, (uint32_t)ida, id, rule_tag(d, r), d.seed);
     bool keep = true;
-    if (d.wfa[slot]) {  // this T also won as the A of another pair
-      const int4 o = d.wina[slot];
-      const W4 wo = philox(step, id, (uint32_t)o.x, rule_tag(d, o.z), d.seed);
+    if (also_a) {  // this T also won as the A of another pair
+      const int4 q = d.wina[slot];
+      const W4 wo = philox(step, id, (uint32_t)q.x, rule_tag(d, q.z), d.seed);
       keep = key_less(((unsigned long long)wd.w3 << 32) | (uint32_t)ida, r,
-                      ((unsigned long long)wo.w3 << 32) | (uint32_t)o.x, o.z);
+                      ((unsigned long long)wo.w3 << 32) | (uint32_t)q.x, q.z);
     }
-    if (keep && d.wft[sa]) {  // the A also won as the T of another pair
-      const int4 o = d.wint[sa];
-      const W4 wo = philox(step, (uint32_t)o.x, (uint32_t)ida, rule_tag(d, o.z), d.seed);
+    if (keep && also_t) {  // the A also won as the T of another pair
+      const int4 q = d.wint[sa];
+      const W4 wo = philox(step, (uint32_t)q.x, (uint32_t)ida, rule_tag(d, q.z), d.seed);
       keep = key_less(((unsigned long long)wd.w3 << 32) | id, r,
-                      ((unsigned long long)wo.w3 << 32) | (uint32_t)o.x, o.z);
+                      ((unsigned long long)wo.w3 << 32) | (uint32_t)q.x, q.z);
     }
-    if (keep) {
-      int32_t da, dt;
-      rule_deltas(d, r, da, dt);
-      make_bond_d(d, a, par, w, ida, sa, slot, (int)id, da, dt, (int)(id | ((uint32_t)r << 30)),
-                  bc);
+    if (keep) make_bond_multi(d, a, par, w, ida, sa, slot, (int)id, r, o, bc);
+  };
+  int ne = 0;
+  int4 e = make_int4(0, 0, 0, 0);
+  if (live) {  // the list's length and its entries in one round trip
+    ne = pick(d.wgo, par)[w * kWgOut + kOutRet];
+    if (lane < kRetCap) e = pick(d.wge, par)[w * kRetCap + lane];
+  }
+  const int mode = read_err(c) ? 0 : (c->ret_ovf[par] ? 2 : 1);
+  if (mode == 1 && live) {
+    if (lane < ne && e.x < 0)
+      decide(e.z, (uint32_t)e.w & 0x3FFFFFFFu, e.x & 0x7FFFFFFF, e.y, (int)((uint32_t)e.w >> 30));
+  } else if (mode == 2 && live) {
+    int s0, s1;
+    range_of<kBrick>(d, w, s0, s1);
+    for (int slot = s0 + lane; slot < s1; slot += 64) {
+      if (!d.wft[slot]) continue;
+      const int4 t = d.wint[slot];
+      decide(slot, a.id ? (uint32_t)a.id[slot] : (uint32_t)slot, t.x, t.y, t.z);
     }
   }
   __syncthreads();
-  if (tid == 0) {
+  if (lane == 0 && live) {
     int32_t* out = pick(d.wgo, par) + w * kWgOut;
-    out[kOutBonds] = s_nw;
-    out[kOutLost] = s_lost;
+    out[kOutBonds] = s_nw[g];
+    out[kOutLost] = s_lost[g];
   }
 }
 
@@ -3095,7 +3051,7 @@ __device__ __forceinline__ void sort_scatter_body(const Dev& d, int k) {
     o.vz[ns] = a.vz[k];
   }
   if (d.slot_of) d.slot_of[id] = ns;
-  if (d.fuse && role == kRoleA) {  // the A's record of the block's first step
+  if (d.fuse && role_is_a(role, d.nrules > 1)) {  // the A's record of the block's first step
     float rx = x, ry = y, rz = z;
     if (d.jitter && d.jit_c != 0.0f) rejitter(d, d.ctl->step0, (uint32_t)id, rx, ry, rz);
     fuse_bin(d, par, d.ctl->step0, ns, (uint32_t)id, rx, ry, rz);
@@ -3130,8 +3086,9 @@ __global__ void k_advance(Ctl* c, int K) {
 // with the sweep's workgroups, so their chain of round trips (with the
 // returning atomic that reserves log rows) runs beside the sweep instead of
 // lengthening the resolve.
-template <bool kTwo, bool kF, bool kNt = false>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) void k_sweep(Dev d, int k) {
+template <int kPol, bool kTwo, bool kF, bool kNt = false>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
+    kPol == kMulti || (kPol == kNearest && kTwo && !kF) ? 6 : 7))) void k_sweep(Dev d, int k) {
   if (kF && (int)blockIdx.x >= d.nwg_sweep) {
     __shared__ uint32_t s_wave[kThreads / 64 + 1];
     const StepInfo si = step_info(d.ctl, k);
@@ -3139,39 +3096,27 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
                 (int)blockIdx.x - d.nwg_sweep, s_wave);
     return;
   }
-  sweep_body<kTwo, kF, kNt>(d, k, xcd_brick(blockIdx.x, d.nwg_sweep), d.nwg_sweep);
+  sweep_body<kPol, kTwo, kF, kNt>(d, k, xcd_brick(blockIdx.x, d.nwg_sweep), d.nwg_sweep);
 }
+template <int kPol>
 __global__ __launch_bounds__(kThreads) void k_dense_sweep(Dev d, int k) {
-  dense_sweep_body(d, k, blockIdx.x, gridDim.x);
+  dense_sweep_body<kPol>(d, k, blockIdx.x, gridDim.x);
 }
 template <bool kBrick>
 __global__ __launch_bounds__(kThreads) void k_resolve(Dev d, int k) {
   resolve_body<kBrick, true, true>(d, k, blockIdx.x, d.nwg_sweep);
 }
 template <bool kBrick>
-__global__ __launch_bounds__(kThreads) void k_near_sweep(Dev d, int k) {
-  if (kBrick && d.bs <= kOneCellBrick)
-    near_sweep_staged_body(d, k, xcd_brick(blockIdx.x, gridDim.x), gridDim.x);
-  else
-    near_sweep_body<kBrick>(d, k, blockIdx.x, gridDim.x);
-}
 __global__ __launch_bounds__(kThreads) void k_near_resolve(Dev d, int k) {
-  near_resolve_body(d, k, blockIdx.x, gridDim.x);
-}
-template <bool kBrick>
-__global__ __launch_bounds__(kThreads) void k_multi_sweep(Dev d, int k) {
-  if (kBrick && d.bs <= kOneCellBrick)
-    multi_sweep_staged_body(d, k, xcd_brick(blockIdx.x, gridDim.x), gridDim.x);
-  else
-    multi_sweep_body<kBrick>(d, k, blockIdx.x, gridDim.x);
+  near_resolve_body<kBrick>(d, k, blockIdx.x, d.nwg_sweep);
 }
 template <bool kBrick>
 __global__ __launch_bounds__(kThreads) void k_multi_resolve(Dev d, int k) {
-  multi_resolve_body<kBrick>(d, k, blockIdx.x);
+  multi_resolve_body<kBrick>(d, k, blockIdx.x, d.nwg_sweep);
 }
 template <bool kBrick>
 __global__ __launch_bounds__(kThreads) void k_multi_final(Dev d, int k) {
-  multi_final_body<kBrick>(d, k, blockIdx.x);
+  multi_final_body<kBrick>(d, k, blockIdx.x, d.nwg_sweep);
 }
 __global__ __launch_bounds__(kThreads) void k_sort_count(Dev d) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
@@ -3231,24 +3176,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
   const int4 m = uniform_map(map);
   const Dev& d = ds[m.x];
   if (k >= d.k_limit || d.rule.policy != PR_POLICY_RANDOM) return;
-  sweep_body<kTwo, kF>(d, k, m.y, m.z);
+  sweep_body<kRandom, kTwo, kF>(d, k, m.y, m.z);
 }
-__global__ __launch_bounds__(kThreads) void k_near_sweep_b(const Dev* __restrict__ ds,
-                                                           const int4* __restrict__ map, int k) {
+template <bool kTwo>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kTwo ? 6 : 7))) void k_near_sweep_b(
+    const Dev* __restrict__ ds, const int4* __restrict__ map, int k) {
   const int4 m = uniform_map(map);
   const Dev& d = ds[m.x];
   if (k >= d.k_limit || d.rule.policy != PR_POLICY_NEAREST) return;
-  if (d.bs <= kOneCellBrick)
-    near_sweep_staged_body(d, k, m.y, m.z);
-  else
-    near_sweep_body<true>(d, k, m.y, m.z);
+  sweep_body<kNearest, kTwo>(d, k, m.y, m.z);
 }
+// four sweep workgroups' slots per workgroup (the resolve's map)
 __global__ __launch_bounds__(kThreads) void k_near_resolve_b(const Dev* __restrict__ ds,
                                                              const int4* __restrict__ map, int k) {
   const int4 m = uniform_map(map);
   const Dev& d = ds[m.x];
   if (k >= d.k_limit || d.rule.policy != PR_POLICY_NEAREST) return;
-  near_resolve_body(d, k, m.y, m.z);
+  near_resolve_body<true>(d, k, m.y, m.z);
 }
 __global__ __launch_bounds__(kThreads) void k_resolve_b(const Dev* __restrict__ ds,
                                                         const int4* __restrict__ map, int k) {
@@ -3434,60 +3378,41 @@ hipError_t launch_generate(const Dev& d, int kind, unsigned long long gseed, flo
 // of several rules).
 static hipError_t launch_selection(const Dev& d, int k, hipStream_t s, hipEvent_t ev_sweep0,
                                    hipEvent_t ev_sweep1) {
-  const dim3 g(d.nwg_sweep), b(kThreads);
-  if (d.nrules > 1) {
-    if (d.sorted) {
-      if (ev_sweep0)
-        hipExtLaunchKernelGGL(k_multi_sweep<true>, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
-      else
-        k_multi_sweep<true><<<g, b, 0, s>>>(d, k);
-      k_multi_resolve<true><<<g, b, 0, s>>>(d, k);
-      k_multi_final<true><<<g, b, 0, s>>>(d, k);
-    } else {
-      if (ev_sweep0)
-        hipExtLaunchKernelGGL(k_multi_sweep<false>, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
-      else
-        k_multi_sweep<false><<<g, b, 0, s>>>(d, k);
-      k_multi_resolve<false><<<g, b, 0, s>>>(d, k);
-      k_multi_final<false><<<g, b, 0, s>>>(d, k);
-    }
-    return hipGetLastError();
-  }
-  if (d.rule.policy == PR_POLICY_NEAREST) {
-    if (d.sorted) {
-      if (ev_sweep0)
-        hipExtLaunchKernelGGL(k_near_sweep<true>, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
-      else
-        k_near_sweep<true><<<g, b, 0, s>>>(d, k);
-    } else {
-      if (ev_sweep0)
-        hipExtLaunchKernelGGL(k_near_sweep<false>, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
-      else
-        k_near_sweep<false><<<g, b, 0, s>>>(d, k);
-    }
-    k_near_resolve<<<g, b, 0, s>>>(d, k);
-    return hipGetLastError();
-  }
-  if (d.sorted && d.bs > kOneCellBrick) {
-    if (ev_sweep0)
-      hipExtLaunchKernelGGL(k_sweep<true, false>, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
-    else
-      k_sweep<true, false><<<g, b, 0, s>>>(d, k);
-  } else if (d.sorted) {
-    if (ev_sweep0)
-      hipExtLaunchKernelGGL(k_sweep<false, false>, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
-    else
-      k_sweep<false, false><<<g, b, 0, s>>>(d, k);
-  } else {
-    if (ev_sweep0)
-      hipExtLaunchKernelGGL(k_dense_sweep, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
-    else
-      k_dense_sweep<<<g, b, 0, s>>>(d, k);
-  }
-  if (d.sorted)
-    k_resolve<true><<<(d.nwg_sweep + 3) / 4, kThreads, 0, s>>>(d, k);
+  // with fused binning, closing groups of step k - 1 trail the sweep
+  const dim3 g(d.nwg_sweep + (d.fuse && k > 0 ? d.ngroups : 0)), b(kThreads);
+  const int gr = (d.nwg_sweep + 3) / 4;  // one wavefront per sweep workgroup
+  const int pol = d.nrules > 1 ? kMulti : (d.rule.policy == PR_POLICY_NEAREST ? kNearest : kRandom);
+  const bool two = d.bs > kOneCellBrick;  // two region cells per staging thread
+  void (*kern)(Dev, int);
+  if (!d.sorted)
+    kern = pol == kRandom ? k_dense_sweep<kRandom>
+                          : (pol == kNearest ? k_dense_sweep<kNearest> : k_dense_sweep<kMulti>);
+  else if (pol == kMulti && !d.fuse)
+    kern = two ? k_sweep<kMulti, true, false> : k_sweep<kMulti, false, false>;
+  else if (pol == kMulti)
+    kern = two ? (d.nt_pos ? k_sweep<kMulti, true, true, true> : k_sweep<kMulti, true, true>)
+               : (d.nt_pos ? k_sweep<kMulti, false, true, true> : k_sweep<kMulti, false, true>);
+  else if (!d.fuse)
+    kern = pol == kRandom ? (two ? k_sweep<kRandom, true, false> : k_sweep<kRandom, false, false>)
+                          : (two ? k_sweep<kNearest, true, false> : k_sweep<kNearest, false, false>);
+  else if (pol == kRandom)
+    kern = two ? (d.nt_pos ? k_sweep<kRandom, true, true, true> : k_sweep<kRandom, true, true>)
+               : (d.nt_pos ? k_sweep<kRandom, false, true, true> : k_sweep<kRandom, false, true>);
   else
-    k_resolve<false><<<(d.nwg_sweep + 3) / 4, kThreads, 0, s>>>(d, k);
+    kern = two ? (d.nt_pos ? k_sweep<kNearest, true, true, true> : k_sweep<kNearest, true, true>)
+               : (d.nt_pos ? k_sweep<kNearest, false, true, true> : k_sweep<kNearest, false, true>);
+  if (ev_sweep0) hipExtLaunchKernelGGL(kern, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
+  else kern<<<g, b, 0, s>>>(d, k);
+  if (pol == kMulti) {
+    auto res = d.sorted ? k_multi_resolve<true> : k_multi_resolve<false>;
+    auto fin = d.sorted ? k_multi_final<true> : k_multi_final<false>;
+    res<<<gr, kThreads, 0, s>>>(d, k);
+    fin<<<gr, kThreads, 0, s>>>(d, k);
+  } else {
+    auto res = pol == kRandom ? (d.sorted ? k_resolve<true> : k_resolve<false>)
+                              : (d.sorted ? k_near_resolve<true> : k_near_resolve<false>);
+    res<<<gr, kThreads, 0, s>>>(d, k);
+  }
   return hipGetLastError();
 }
 
@@ -3501,21 +3426,10 @@ hipError_t launch_step(const Dev& d, int k, hipStream_t s, hipEvent_t ev_sweep0,
     k_md_free<<<g, kThreads, 0, s>>>(d, k);
     for (int m = 0; m <= d.md_theta; ++m) k_md_sub<<<g, kThreads, 0, s>>>(d, k, m);
   }
-  if (d.fuse) {  // two kernels: the sweep (with the closing of step k - 1), the resolve
-    // the sweep, with the closing of step k - 1 in trailing workgroups (edges
-    // above kOneCellBrick stage two region cells per thread)
-    const dim3 g(d.nwg_sweep + (k > 0 ? d.ngroups : 0)), b(kThreads);
-    auto kern = d.bs > kOneCellBrick ? (d.nt_pos ? k_sweep<true, true, true>
-                                                 : k_sweep<true, true, false>)
-                                     : (d.nt_pos ? k_sweep<false, true, true>
-                                                 : k_sweep<false, true, false>);
-    if (ev_sweep0) hipExtLaunchKernelGGL(kern, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
-    else kern<<<g, b, 0, s>>>(d, k);
-    k_resolve<true><<<(d.nwg_sweep + 3) / 4, kThreads, 0, s>>>(d, k);
-    return hipGetLastError();
+  if (!d.fuse) {  // with fused binning the previous sweep has binned the A's
+    const int prep_blocks = d.nwg_prep + (k > 0 ? d.ngroups : 0);
+    k_prep<<<prep_blocks, kThreads, 0, s>>>(d, k);
   }
-  const int prep_blocks = d.nwg_prep + (k > 0 ? d.ngroups : 0);
-  k_prep<<<prep_blocks, kThreads, 0, s>>>(d, k);
   return launch_selection(d, k, s, ev_sweep0, ev_sweep1);
 }
 
@@ -3577,8 +3491,11 @@ hipError_t launch_step_b(const BatchLaunch& b, int k, hipStream_t s) {
     k_resolve_b<<<b.n_res, kThreads, 0, s>>>(b.ds, b.res, k);
   }
   if (b.any_nearest) {
-    k_near_sweep_b<<<b.n_sweep, kThreads, 0, s>>>(b.ds, b.sweep, k);
-    k_near_resolve_b<<<b.n_sweep, kThreads, 0, s>>>(b.ds, b.sweep, k);
+    if (b.two)
+      k_near_sweep_b<true><<<b.n_sweep, kThreads, 0, s>>>(b.ds, b.sweep, k);
+    else
+      k_near_sweep_b<false><<<b.n_sweep, kThreads, 0, s>>>(b.ds, b.sweep, k);
+    k_near_resolve_b<<<b.n_res, kThreads, 0, s>>>(b.ds, b.res, k);
   }
   return hipGetLastError();
 }
