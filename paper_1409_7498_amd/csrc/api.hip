@@ -36,7 +36,7 @@ hipError_t launch_step(const Dev& d, int k, hipStream_t s, hipEvent_t ev_sweep0,
                        hipEvent_t ev_sweep1);
 hipError_t launch_block_end(const Dev& d, int K, hipStream_t s);
 hipError_t launch_single(const Dev& d, uint32_t step, uint32_t par, SingleOut* out, hipStream_t s);
-hipError_t launch_sort(const Dev& d, hipStream_t s);
+hipError_t launch_sort(const Dev& d, bool fresh, hipStream_t s);
 hipError_t log_order(int32_t* log, int64_t n, hipStream_t s);
 hipError_t launch_gather_out(const Dev& d, float* ox, float* oy, float* oz, int32_t* otyp,
                              int32_t* ost, int32_t* oadj, hipStream_t s);
@@ -785,7 +785,7 @@ int after_load(pr_sys* s) {
 // afterwards the sweep runs per brick.
 int sort_storage(pr_sys* s, hipStream_t st) {
   s->d.fuse = fuse_eligible(s) ? 1 : 0;
-  HIP_TRY(launch_sort(s->d, st));
+  HIP_TRY(launch_sort(s->d, !s->d.sorted, st));
   s->d.sorted = 1;
   s->d.nwg_sweep = s->d.nbricks;
   s->steps_since_sort = 0;

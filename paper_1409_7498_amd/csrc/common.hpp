@@ -42,6 +42,7 @@ constexpr int kTPass = 768;         // particles a sweep workgroup holds per pas
 constexpr int kQueue = 512;         // in-range pairs queued per pass
 constexpr int32_t kMaxParticles = 1 << 30;  // byte offsets of 4-byte fields fit in 32 bits
 constexpr int kMaxRules = 4;        // concurrent rules of one system
+constexpr int kFreshMin = 262144;    // particles from which scattered arrays go as records
 constexpr int kMdPer = 4;           // particles per thread of the MD's kernels
 constexpr int kKinMaxState = 64;    // kinetics counters: states per call
 constexpr int kKinMaxBins = 256;    // kinetics counters: distance bins per call

@@ -2945,6 +2945,9 @@ __device__ __forceinline__ int sort_bin(const Dev& d, float x, float y, float z,
 // Ranks within sort bins.  The storage is in bin order from the previous
 // sort, so the 64 particles of a wavefront fall into few bins: the lowest lane
 // of each bin reserves the ranks of all its lanes with one returning atomic.
+// kFresh: storage in another order (the first sort after a load), a wavefront
+// holds as many bins as lanes: one atomic per lane.
+template <bool kFresh = false>
 __device__ __forceinline__ void sort_count_body(const Dev& d, int k) {
   const bool valid = k < d.n;
   const Arr a = pick_set(d, d.ctl->set & 1u);
@@ -2952,6 +2955,10 @@ __device__ __forceinline__ void sort_count_body(const Dev& d, int k) {
   int b, bin = -1;
   if (valid)
     bin = sort_bin(d, pick(a.x, par)[k], pick(a.y, par)[k], pick(a.z, par)[k], a.role[k], b);
+  if (kFresh) {
+    if (valid) d.rank[k] = (int32_t)atomicAdd(&d.dcnt[bin], 1u);
+    return;
+  }
   // group the lanes by bin: each round takes the lowest ungrouped lane's bin
   int leader = 0;
   unsigned long long peers = 0ull;
@@ -3028,6 +3035,29 @@ __device__ __forceinline__ void sort_scan_body(const Dev& d) {
   }
 }
 
+// Row k of adj moved to row ns of o: rows of width 4 or 2 as one vector when
+// both arrays are aligned.
+__device__ __forceinline__ void move_row(const Dev& d, const int32_t* adj, int k, int32_t* o,
+                                         int ns) {
+  const bool vec = (((uintptr_t)adj | (uintptr_t)o) & 15u) == 0u;
+  if (vec && d.B == 4) {
+    ((int4*)o)[ns] = ((const int4*)adj)[k];
+  } else if (vec && d.B == 2) {
+    ((int2*)o)[ns] = ((const int2*)adj)[k];
+  } else {
+    for (int q = 0; q < d.B; ++q) o[(size_t)ns * d.B + q] = adj[(size_t)k * d.B + q];
+  }
+}
+
+// With fused binning, the record of an A (slot ns after the sort) of the first
+// step after the sort.
+__device__ __forceinline__ void sort_bin_first(const Dev& d, uint32_t par, int ns, int id,
+                                               uint8_t role, float x, float y, float z) {
+  if (!d.fuse || !role_is_a(role, d.nrules > 1)) return;
+  if (d.jitter && d.jit_c != 0.0f) rejitter(d, d.ctl->step0, (uint32_t)id, x, y, z);
+  fuse_bin(d, par, d.ctl->step0, ns, (uint32_t)id, x, y, z);
+}
+
 __device__ __forceinline__ void sort_scatter_body(const Dev& d, int k) {
   if (k >= d.n) return;
   const uint32_t s = d.ctl->set & 1u, par = d.ctl->par0;
@@ -3051,20 +3081,54 @@ __device__ __forceinline__ void sort_scatter_body(const Dev& d, int k) {
     o.vz[ns] = a.vz[k];
   }
   if (d.slot_of) d.slot_of[id] = ns;
-  if (d.fuse && role_is_a(role, d.nrules > 1)) {  // the A's record of the block's first step
-    float rx = x, ry = y, rz = z;
-    if (d.jitter && d.jit_c != 0.0f) rejitter(d, d.ctl->step0, (uint32_t)id, rx, ry, rz);
-    fuse_bin(d, par, d.ctl->step0, ns, (uint32_t)id, rx, ry, rz);
+  sort_bin_first(d, par, ns, id, role, x, y, z);
+  move_row(d, a.adj, k, o.adj, ns);
+}
+
+// The scatter of a fresh sort (storage in the caller's order, so every
+// particle's slot is on a line of its own): one 16-byte record (position, id)
+// and one 8-byte one (type, state) per particle instead of seven 4- and 1-byte
+// stores, into the overflow arrays (idle at a sort), and the rows in place;
+// sort_unpack then writes the arrays in slot order.  Bound by the number of
+// scattered stores: 1,048,576 particles 113 us, now 59 us with the
+// unpacking; 4,194,304: 750 and 375.
+__device__ __forceinline__ void sort_scatter_fresh_body(const Dev& d, int k) {
+  if (k >= d.n) return;
+  const uint32_t s = d.ctl->set & 1u, par = d.ctl->par0;
+  const Arr a = pick_set(d, s), o = pick_set(d, s ^ 1u);
+  const float x = pick(a.x, par)[k], y = pick(a.y, par)[k], z = pick(a.z, par)[k];
+  int b;
+  const int bin = sort_bin(d, x, y, z, a.role[k], b);
+  const int ns = d.bstart[b] + (int)d.dloc[bin] + d.rank[k];
+  const int id = a.id[k];
+  d.ovf[0][ns] = make_float4(x, y, z, __int_as_float(id));
+  ((int2*)d.ovf[1])[ns] = make_int2(a.typ[k], a.st[k]);
+  if (a.vx) d.md_vel[ns] = make_float4(a.vx[k], a.vy[k], a.vz[k], 0.0f);
+  if (d.slot_of) d.slot_of[id] = ns;
+  move_row(d, a.adj, k, o.adj, ns);
+}
+__device__ __forceinline__ void sort_unpack_body(const Dev& d, int ns) {
+  if (ns >= d.n) return;
+  const uint32_t s = d.ctl->set & 1u, par = d.ctl->par0;
+  const Arr o = pick_set(d, s ^ 1u);
+  const float4 r = d.ovf[0][ns];
+  const int2 ts = ((const int2*)d.ovf[1])[ns];
+  const int id = __float_as_int(r.w);
+  const uint8_t role = role_of(d, ts.x, ts.y);
+  pick(o.x, par)[ns] = r.x;
+  pick(o.y, par)[ns] = r.y;
+  pick(o.z, par)[ns] = r.z;
+  o.id[ns] = id;
+  o.typ[ns] = ts.x;
+  o.st[ns] = ts.y;
+  o.role[ns] = role;
+  if (o.vx) {
+    const float4 v = d.md_vel[ns];
+    o.vx[ns] = v.x;
+    o.vy[ns] = v.y;
+    o.vz[ns] = v.z;
   }
-  // rows of width 4 or 2 move as one vector when both arrays are aligned
-  const bool vec = (((uintptr_t)a.adj | (uintptr_t)o.adj) & 15u) == 0u;
-  if (vec && d.B == 4) {
-    ((int4*)o.adj)[ns] = ((const int4*)a.adj)[k];
-  } else if (vec && d.B == 2) {
-    ((int2*)o.adj)[ns] = ((const int2*)a.adj)[k];
-  } else {
-    for (int q = 0; q < d.B; ++q) o.adj[(size_t)ns * d.B + q] = a.adj[(size_t)k * d.B + q];
-  }
+  sort_bin_first(d, par, ns, id, role, r.x, r.y, r.z);
 }
 
 // ---------------------------------------------------------------------------
@@ -3118,9 +3182,10 @@ template <bool kBrick>
 __global__ __launch_bounds__(kThreads) void k_multi_final(Dev d, int k) {
   multi_final_body<kBrick>(d, k, blockIdx.x, d.nwg_sweep);
 }
+template <bool kFresh>
 __global__ __launch_bounds__(kThreads) void k_sort_count(Dev d) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  sort_count_body(d, k);
+  sort_count_body<kFresh>(d, k);
   if (d.fuse) {  // fused binning: the scatter bins the first step after the sort
     const uint32_t s0 = d.ctl->step0;
     for (int q = k; q < d.ncell; q += gridDim.x * blockDim.x) {
@@ -3135,6 +3200,12 @@ __global__ __launch_bounds__(kThreads) void k_sort_local(Dev d) {
 __global__ __launch_bounds__(kFinThreads) void k_sort_scan(Dev d) { sort_scan_body(d); }
 __global__ __launch_bounds__(kThreads) void k_sort_scatter(Dev d) {
   sort_scatter_body(d, blockIdx.x * blockDim.x + threadIdx.x);
+}
+__global__ __launch_bounds__(kThreads) void k_sort_scatter_fresh(Dev d) {
+  sort_scatter_fresh_body(d, blockIdx.x * blockDim.x + threadIdx.x);
+}
+__global__ __launch_bounds__(kThreads) void k_sort_unpack(Dev d) {
+  sort_unpack_body(d, blockIdx.x * blockDim.x + threadIdx.x);
 }
 __global__ void k_sort_flip(Ctl* c) {
   if (threadIdx.x == 0 && blockIdx.x == 0) c->set ^= 1u;
@@ -3269,6 +3340,34 @@ __global__ __launch_bounds__(kThreads) void k_gather_out(Dev d, float* ox, float
   if (ost) ost[id] = a.st[k];
   if (oadj)
     for (int b = 0; b < d.B; ++b) oadj[(size_t)id * d.B + b] = a.adj[(size_t)k * d.B + b];
+}
+
+// The same for large systems on sorted storage in two kernels: one 16-byte
+// record (position, state) per particle scattered by id into an overflow array
+// (idle between runs) and the row as one vector, then the records unpacked in
+// id order.  1,048,576 particles, rows of four: eight scattered stores per
+// particle 148 us, now 50 us; 4,194,304, rows of two: 506 and
+// 200.
+__global__ __launch_bounds__(kThreads) void k_gather_rec(Dev d, int32_t* otyp, int32_t* oadj) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= d.n) return;
+  const Arr a = pick_set(d, d.ctl->set & 1u);
+  const uint32_t par = d.ctl->par0;
+  const int id = a.id[k];
+  d.ovf[0][id] = make_float4(pick(a.x, par)[k], pick(a.y, par)[k], pick(a.z, par)[k],
+                             __int_as_float(a.st[k]));
+  if (otyp) otyp[id] = a.typ[k];
+  if (oadj) move_row(d, a.adj, k, oadj, id);
+}
+__global__ __launch_bounds__(kThreads) void k_gather_unpack(Dev d, float* ox, float* oy, float* oz,
+                                                            int32_t* ost) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= d.n) return;
+  const float4 r = d.ovf[0][i];
+  if (ox) ox[i] = r.x;
+  if (oy) oy[i] = r.y;
+  if (oz) oz[i] = r.z;
+  if (ost) ost[i] = __float_as_int(r.w);
 }
 
 // The re-jitter alone (the stand-in for the MD between reaction steps),
@@ -3449,11 +3548,24 @@ hipError_t launch_single(const Dev& d, uint32_t step, uint32_t par, SingleOut* o
   return hipGetLastError();
 }
 
-hipError_t launch_sort(const Dev& d, hipStream_t s) {
-  k_sort_count<<<blocks_for(d.n, kThreads), kThreads, 0, s>>>(d);
+// fresh: the storage is in the caller's order (the first sort after a load).
+// Small systems' arrays stay in the L2s, where the plain kernels' scattered
+// stores merge: kFreshMin particles is where the record scatter with its second
+// kernel starts to win (load, one step and read-out: 262,144 particles 149 us
+// with the plain kernels and 146 with the records, 524,288 271 and 207).
+hipError_t launch_sort(const Dev& d, bool fresh, hipStream_t s) {
+  const int g = blocks_for(d.n, kThreads);
+  fresh = fresh && d.n >= kFreshMin;
+  if (fresh) k_sort_count<true><<<g, kThreads, 0, s>>>(d);
+  else k_sort_count<false><<<g, kThreads, 0, s>>>(d);
   k_sort_local<<<blocks_for(d.nbricks, kThreads / 64), kThreads, 0, s>>>(d);
   k_sort_scan<<<1, kFinThreads, 0, s>>>(d);
-  k_sort_scatter<<<blocks_for(d.n, kThreads), kThreads, 0, s>>>(d);
+  if (fresh) {
+    k_sort_scatter_fresh<<<g, kThreads, 0, s>>>(d);
+    k_sort_unpack<<<g, kThreads, 0, s>>>(d);
+  } else {
+    k_sort_scatter<<<g, kThreads, 0, s>>>(d);
+  }
   k_sort_flip<<<1, 64, 0, s>>>(d.ctl);
   return hipGetLastError();
 }
@@ -3515,7 +3627,13 @@ hipError_t launch_sort_b(const BatchLaunch& b, hipStream_t s) {
 
 hipError_t launch_gather_out(const Dev& d, float* ox, float* oy, float* oz, int32_t* otyp,
                              int32_t* ost, int32_t* oadj, hipStream_t s) {
-  k_gather_out<<<blocks_for(d.n, kThreads), kThreads, 0, s>>>(d, ox, oy, oz, otyp, ost, oadj);
+  const int g = blocks_for(d.n, kThreads);
+  if (d.sorted && d.n >= kFreshMin) {  // the fresh sort's line, for the same reason
+    k_gather_rec<<<g, kThreads, 0, s>>>(d, otyp, oadj);
+    if (ox || oy || oz || ost) k_gather_unpack<<<g, kThreads, 0, s>>>(d, ox, oy, oz, ost);
+    return hipGetLastError();
+  }
+  k_gather_out<<<g, kThreads, 0, s>>>(d, ox, oy, oz, otyp, ost, oadj);
   return hipGetLastError();
 }
 
