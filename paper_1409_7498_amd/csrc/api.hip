@@ -47,9 +47,8 @@ hipError_t launch_md_check(const Dev& d, hipStream_t s);
 hipError_t launch_md_init(const Dev& d, unsigned long long vseed, float cv, hipStream_t s);
 hipError_t launch_sqrt_rn(const float* in, float* out, long long n, hipStream_t s);
 hipError_t launch_gather_v(const Dev& d, float* ox, float* oy, float* oz, hipStream_t s);
-hipError_t launch_kinetics(const Dev& d, int nstate, int nbins, const float* e2,
-                           unsigned long long* pop, unsigned long long* pairs,
-                           unsigned long long* hist, hipStream_t s);
+hipError_t launch_kinetics(const Dev& d, int nstate, int nbins, double rc, unsigned long long* kin,
+                           KinOut* out, hipStream_t s);
 hipError_t launch_jitter_only(const Dev& d, int n_steps, hipStream_t s, hipEvent_t ev0,
                               hipEvent_t ev1);
 hipError_t launch_stream_copy(const void* src, void* dst, long long bytes, int width,
@@ -629,14 +628,18 @@ struct pr_sys {
   int32_t *rtyp = nullptr, *rst = nullptr, *radj = nullptr;
   Ctl* hctl = nullptr;
   bool own_hctl = true;  // false: the pinned word belongs to a server's pool
-  // kinetics counters (allocated on first use): pop, pairs, hist, bin edges
+  // kinetics counters (allocated on first use): the slices, zero between
+  // read-outs (kin_clean: the last one ran to its end), and the pinned host
+  // memory the device writes the sums to
   unsigned long long* kin = nullptr;
-  float* kin_e2 = nullptr;
+  bool kin_clean = false;
+  KinOut* kin_out = nullptr;
   ~pr_sys() {
     for (Seg& g : segs)
       if (g.gexec) (void)hipGraphExecDestroy(g.gexec);
     if (cap) (void)hipStreamDestroy(cap);
     if (hctl && own_hctl) (void)hipHostFree(hctl);
+    if (kin_out) (void)hipHostFree(kin_out);
   }
 };
 
@@ -1353,31 +1356,25 @@ int pr_sys_kinetics(pr_sys* s, int32_t nstate, int64_t* pop, int64_t* pairs, int
   if (s->d.nrules > 1) return fail(PR_EINVAL, "kinetics counters take one rule");
   // kKinSlices slices of counters (the kernels spread their sums over them)
   const size_t nk = (size_t)kKinStride * kKinSlices;
-  if (!s->kin && ((e = s->arena.alloc(&s->kin, nk)) ||
-                  (e = s->arena.alloc(&s->kin_e2, (size_t)kKinMaxBins + 1))))
-    return e;
-  // bin edges: e2[b] = fl32((rc b / nbins)^2), the product taken in double
-  std::vector<float> e2((size_t)nbins + 1);
-  for (int b = 0; b <= nbins; ++b) {
-    const double r = (double)s->rule.rc * (double)b / (double)nbins;
-    e2[(size_t)b] = (float)(r * r);
+  if (!s->kin && (e = s->arena.alloc(&s->kin, nk))) return e;
+  if (!s->kin_out && hipHostMalloc((void**)&s->kin_out, sizeof(KinOut)) != hipSuccess) {
+    s->kin_out = nullptr;
+    return fail(PR_ENOMEM, "hipHostMalloc failed");
   }
   hipStream_t st = s->stream;
-  unsigned long long *kp = s->kin, *kq = s->kin + kKinMaxState, *kh = s->kin + 2 * kKinMaxState;
-  HIP_TRY(hipMemcpyAsync(s->kin_e2, e2.data(), e2.size() * sizeof(float), hipMemcpyHostToDevice,
-                         st));
-  HIP_TRY(launch_fill_u32((uint32_t*)s->kin, 2 * (long long)nk, 0u, st));
-  HIP_TRY(launch_kinetics(s->d, nstate, nbins, s->kin_e2, kp, kq, kh, st));
-  std::vector<unsigned long long> h(kKinStride);  // the first slice holds the sums
-  HIP_TRY(hipMemcpyAsync(h.data(), s->kin, (size_t)kKinStride * sizeof(unsigned long long),
-                         hipMemcpyDeviceToHost, st));
-  if ((e = sync_ctl(s))) return e;
-  if (s->hctl->err) return fail(s->hctl->err, "device error during the run");
+  if (!s->kin_clean)
+    HIP_TRY(launch_fill_u32((uint32_t*)s->kin, 2 * (long long)nk, 0u, st));
+  s->kin_clean = false;
+  HIP_TRY(launch_kinetics(s->d, nstate, nbins, (double)s->rule.rc, s->kin, s->kin_out, st));
+  HIP_TRY(hipStreamSynchronize(st));
+  s->kin_clean = true;
+  const KinOut& h = *s->kin_out;
+  if (h.err) return fail(h.err, "device error during the run");
   for (int q = 0; q < nstate; ++q) {
-    pop[q] = (int64_t)h[(size_t)q];
-    pairs[q] = (int64_t)h[(size_t)(kKinMaxState + q)];
+    pop[q] = h.v[q];
+    pairs[q] = h.v[kKinMaxState + q];
   }
-  for (int b = 0; b < nbins; ++b) hist[b] = (int64_t)h[(size_t)(2 * kKinMaxState + b)];
+  for (int b = 0; b < nbins; ++b) hist[b] = h.v[2 * kKinMaxState + b];
   return PR_OK;
 }
 

@@ -76,6 +76,13 @@ struct SingleOut {
   int64_t sum[kPart];
 };
 
+// What a kinetics read-out reports to the host: the device error and the
+// counters (populations, pairs, histogram at their places in a slice).
+struct KinOut {
+  int32_t err;
+  int64_t v[kKinStride];
+};
+
 struct RuleD {
   int32_t type_a, a_min, a_max, d_a;
   int32_t type_t, t_min, t_max, d_t;
