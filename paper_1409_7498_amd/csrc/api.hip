@@ -18,10 +18,13 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <mutex>
 #include <string>
 #include <vector>
+
+#include <sys/mman.h>
 
 #include "common.hpp"
 #include "../../include/polyreact.h"
@@ -256,11 +259,13 @@ struct Arena {
 
 // Scratch of one step (everything but the particle arrays and the logs).
 // nwg: sweep workgroups to provide for (the larger of the two sweep grids).
+// The arrays that start as zero (cell counts, T flags, control block) come
+// first, in this order.
 int alloc_scratch(Arena& a, Dev& d, int32_t n, int32_t nwg, hipStream_t s) {
   int e;
-  if ((e = a.alloc(&d.tflag, n)))
+  if ((e = a.alloc(&d.cnt[0], d.ncell)) || (e = a.alloc(&d.cnt[1], d.ncell)) ||
+      (e = a.alloc(&d.tflag, n)) || (e = a.alloc(&d.ctl, 1)))
     return e;
-  if ((e = a.alloc(&d.cnt[0], d.ncell)) || (e = a.alloc(&d.cnt[1], d.ncell))) return e;
   const size_t nrec = (size_t)d.ncell * kCellCap;
   if ((e = a.alloc(&d.rec, nrec)) || (e = a.alloc(&d.rsa, nrec)) ||
       (e = a.alloc(&d.radj, nrec)))
@@ -275,7 +280,6 @@ int alloc_scratch(Arena& a, Dev& d, int32_t n, int32_t nwg, hipStream_t s) {
         (e = a.alloc(&d.abst[p], (size_t)sweep_blocks(n))))
       return e;
   }
-  if ((e = a.alloc(&d.ctl, 1))) return e;
   if (d.nrules > 1 && ((e = a.alloc(&d.wgk1, (size_t)nwg * kRetCap)) ||
                        (e = a.alloc(&d.wfa, n)) || (e = a.alloc(&d.wft, n)) ||
                        (e = a.alloc(&d.wina, n)) || (e = a.alloc(&d.wint, n))))
@@ -699,43 +703,30 @@ bool fuse_eligible(const pr_sys* s) {
   return s->allow_fuse && d.md_theta == 0 && d.fcnt[0] != nullptr;
 }
 
-// The fused-binning buckets, allocated on the first run that can use them.
+int alloc_buckets(Arena& A, Dev& d);
+
+// The fused-binning buckets, allocated (as one piece) on the first run that can
+// use them.
 int alloc_fused(pr_sys* s) {
   Dev& d = s->d;
   if (d.fcnt[0] || !s->allow_fuse) return PR_OK;
   Dev t = d;
-  const size_t n = (size_t)d.n, nrec = (size_t)d.ncell * kCellCap;
-  const size_t mark = s->arena.ptrs.size();
-  int e = 0;
-  for (int q = 0; q < 3 && !e; ++q) e = s->arena.alloc(&t.fcnt[q], (size_t)d.ncell);
-  for (int p = 0; p < 2 && !e; ++p) {
-    if (!e) e = s->arena.alloc(&t.frec[p], nrec);
-    if (!e) e = s->arena.alloc(&t.fsa[p], nrec);
-    if (!e) e = s->arena.alloc(&t.fovf[p], n);
-    if (!e) e = s->arena.alloc(&t.fovf_sa[p], n);
-  }
-  if (!e) e = s->arena.alloc(&t.apos, n);
+  Arena dry;
+  dry.dry = true;
+  int e = alloc_buckets(dry, t);
+  Arena carve;
+  carve.cap = dry.bytes;
+  if (!e) e = s->arena.alloc(&carve.base, carve.cap);
   if (e && (d.nrules > 1 || d.rule.policy != PR_POLICY_RANDOM)) {
     // these systems also run without (the binning kernel bins), as they did
     // before they could fuse: no memory for the buckets is no error
-    while (s->arena.ptrs.size() > mark) {
-      void* q = s->arena.ptrs.back();
-      (void)(s->arena.async ? hipFreeAsync(q, s->arena.astream) : hipFree(q));
-      s->arena.ptrs.pop_back();
-    }
     (void)hipGetLastError();
     s->allow_fuse = 0;
     return PR_OK;
   }
-  if (e) return e;  // what was allocated stays in the arena until destroy
-  for (int q = 0; q < 3; ++q) d.fcnt[q] = t.fcnt[q];
-  for (int p = 0; p < 2; ++p) {
-    d.frec[p] = t.frec[p];
-    d.fsa[p] = t.fsa[p];
-    d.fovf[p] = t.fovf[p];
-    d.fovf_sa[p] = t.fovf_sa[p];
-  }
-  d.apos = t.apos;
+  if (!e) e = alloc_buckets(carve, t);
+  if (e) return e;
+  d = t;
   drop_graph(s);
   return PR_OK;
 }
@@ -760,20 +751,26 @@ void fuse_after_run(pr_sys* s, uint32_t first_step, uint32_t n_steps) {
   s->rec_jit = s->d.jit_c;
 }
 
-int after_load(pr_sys* s) {
+// The device side of a load (the configuration is in storage set 0): the
+// launches, and the copy of the control block that load_end looks at.
+int load_begin(pr_sys* s) {
   hipStream_t st = s->stream;
   set_dense(s);
   s->steps_since_sort = 0;
-  // parity 0 after the reset: both cell-count buffers start cleared
-  HIP_TRY(hipMemsetAsync(s->d.cnt[0], 0, sizeof(uint32_t) * (size_t)s->d.ncell, st));
-  HIP_TRY(hipMemsetAsync(s->d.cnt[1], 0, sizeof(uint32_t) * (size_t)s->d.ncell, st));
+  // parity 0 after the reset: both cell-count buffers (neighbours) start cleared
+  HIP_TRY(hipMemsetAsync(s->d.cnt[0], 0,
+                         (size_t)((char*)(s->d.cnt[1] + s->d.ncell) - (char*)s->d.cnt[0]), st));
   HIP_TRY(launch_ctl_reset(s->d.ctl, 0, 1, st));
   s->d.kpar0 = 0;
   HIP_TRY(launch_identity(s->d, st));
   HIP_TRY(launch_classify(s->d, st));
   if (s->d.md_theta > 0) HIP_TRY(launch_md_check(s->d, st));
-  int e = sync_ctl(s);
-  if (e) return e;
+  HIP_TRY(hipMemcpyAsync(s->hctl, s->d.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
+  return PR_OK;
+}
+
+// The host side, once the stream has reached load_begin's end.
+int load_end(pr_sys* s) {
   if (s->d.md_theta > 0) s->d.md_all = s->hctl->md_lone ? 1 : 0;
   s->steps_since_load = 0;
   if (s->hctl->err) {
@@ -782,6 +779,13 @@ int after_load(pr_sys* s) {
   }
   s->loaded = true;
   return PR_OK;
+}
+
+int after_load(pr_sys* s) {
+  int e = load_begin(s);
+  if (e) return e;
+  HIP_TRY(hipStreamSynchronize(s->stream));
+  return load_end(s);
 }
 
 // Counting sort of the storage by brick (writes the other storage set);
@@ -898,10 +902,11 @@ int segment_graph(pr_sys* s, int32_t K, bool with_sort, hipGraphExec_t* out) {
 
 namespace {
 
-// Every device allocation of a resident system but the partial-counter log
-// (grown on demand) and the host-read staging buffers (on first read).
-int alloc_system(Arena& A, Dev& d, int32_t n, int32_t B, int64_t log_cap, hipStream_t st) {
-  int e = alloc_scratch(A, d, n, std::max(sweep_blocks(n), d.nbricks), st);
+// Every device array of a resident system but the partial-counter log (grown
+// on demand) and the host-read staging buffers (on first read), added up (a
+// dry arena) or carved out of one allocation.
+int alloc_system(Arena& A, Dev& d, int32_t n, int32_t B, int64_t log_cap) {
+  int e = alloc_scratch(A, d, n, std::max(sweep_blocks(n), d.nbricks), nullptr);
   for (int q = 0; q < 2 && !e; ++q) {
     Arr& a = d.set[q];
     for (int p = 0; p < 2 && !e; ++p) {
@@ -921,10 +926,41 @@ int alloc_system(Arena& A, Dev& d, int32_t n, int32_t B, int64_t log_cap, hipStr
   if (!e) e = A.alloc(&d.dcnt, (size_t)d.nbricks * d.nd);
   if (!e) e = A.alloc(&d.dloc, (size_t)d.nbricks * d.nd);
   if (!e) e = A.alloc(&d.rank, n);
-  if (!e && !A.dry &&
-      (hipMemsetAsync(d.bcnt, 0, sizeof(uint32_t) * d.nbricks, st) != hipSuccess ||
-       hipMemsetAsync(d.dcnt, 0, sizeof(uint32_t) * d.nbricks * d.nd, st) != hipSuccess))
-    e = fail(PR_EHIP, "hipMemsetAsync failed");
+  return e;
+}
+
+// What a new system expects: counts, T flags, control block and sort counts
+// zero, the A keys empty (three clears of neighbouring arrays).
+int clear_system(const Dev& d, hipStream_t st) {
+  HIP_TRY(hipMemsetAsync(d.cnt[0], 0, (size_t)((char*)(d.ctl + 1) - (char*)d.cnt[0]), st));
+  HIP_TRY(hipMemsetAsync(d.slotA, 0xFF, sizeof(unsigned long long) * (size_t)d.n, st));
+  HIP_TRY(hipMemsetAsync(d.bcnt, 0, (size_t)((char*)(d.dcnt + (size_t)d.nbricks * d.nd) -
+                                             (char*)d.bcnt), st));
+  return PR_OK;
+}
+
+// Steps the counter log of a new system holds.
+constexpr int64_t kPartSteps = 1024;
+
+// The arrays of a new system (d: its geometry) and its first counter log.
+int alloc_new(Arena& A, Dev& d, int64_t log_cap) {
+  int e = alloc_system(A, d, d.n, d.B, log_cap);
+  if (!e) e = A.alloc(&d.part, (size_t)kPartSteps * d.ngroups * kPart);
+  return e;
+}
+
+// The fused-binning buckets.
+int alloc_buckets(Arena& A, Dev& d) {
+  const size_t n = (size_t)d.n, nrec = (size_t)d.ncell * kCellCap;
+  int e = 0;
+  for (int q = 0; q < 3 && !e; ++q) e = A.alloc(&d.fcnt[q], (size_t)d.ncell);
+  for (int p = 0; p < 2 && !e; ++p) {
+    if (!e) e = A.alloc(&d.frec[p], nrec);
+    if (!e) e = A.alloc(&d.fsa[p], nrec);
+    if (!e) e = A.alloc(&d.fovf[p], n);
+    if (!e) e = A.alloc(&d.fovf_sa[p], n);
+  }
+  if (!e) e = A.alloc(&d.apos, n);
   return e;
 }
 
@@ -944,7 +980,7 @@ int pr_footprint(const pr_replica_desc* r, uint32_t n_steps, int64_t* bytes) {
   Arena A;
   A.dry = true;
   const int64_t log_cap = r->log_cap > 0 ? r->log_cap : r->n;
-  if ((e = alloc_system(A, d, r->n, r->B, log_cap, nullptr))) return e;
+  if ((e = alloc_system(A, d, r->n, r->B, log_cap))) return e;
   // partial counters for max(1024, n_steps) steps; host-read staging buffers
   const size_t part = (size_t)std::max<uint32_t>(1024u, n_steps) * d.ngroups * kPart * 4;
   const size_t rd = (size_t)r->n * (3 * 4 + 4 + 4 * (size_t)r->B);
@@ -956,14 +992,29 @@ int pr_footprint(const pr_replica_desc* r, uint32_t n_steps, int64_t* bytes) {
 
 namespace {
 
-// Resources a server lends to the systems it creates: device memory drawn in
-// stream order from its pool (systems are created and retired while other
-// work runs, and a plain hipFree would wait for that work) and a pinned
-// control word from its own pool (hipHostFree waits for the device too).
+// Resources the owner of several systems lends to those it creates.  A server:
+// device memory drawn in stream order from its pool (systems are created and
+// retired while other work runs, and a plain hipFree would wait for that
+// work).  A batch: a piece of its own allocation (slab), with room for the
+// fused buckets when fused is set.  Both: a pinned control word (allocating one
+// per system, and hipHostFree, wait for the device).
 struct SysLease {
   hipMemPool_t pool = nullptr;
+  char* slab = nullptr;
+  size_t slab_bytes = 0;
+  bool fused = false;
   Ctl* hctl = nullptr;
 };
+
+// Device bytes of a new system (d: its geometry), as alloc_new lays it out.
+size_t new_bytes(const Dev& d, int64_t log_cap, bool fused) {
+  Arena dry;
+  dry.dry = true;
+  Dev t = d;
+  if (alloc_new(dry, t, log_cap)) return 0;
+  if (fused && alloc_buckets(dry, t)) return 0;
+  return dry.bytes;
+}
 
 int sys_create(pr_sys** out, int32_t n, float L, int32_t B, const pr_rule* rule, uint64_t seed,
                int64_t log_cap, void* stream, int32_t brick, const SysLease* lease,
@@ -976,7 +1027,7 @@ int sys_create(pr_sys** out, int32_t n, float L, int32_t B, const pr_rule* rule,
   if (e) return e;
   pr_sys* s = new pr_sys();
   s->stream = (hipStream_t)stream;
-  s->arena.async = lease != nullptr;
+  s->arena.async = lease && lease->pool;
   s->arena.astream = s->stream;
   s->arena.pool = lease ? lease->pool : nullptr;
   s->rule = *rule;
@@ -991,14 +1042,27 @@ int sys_create(pr_sys** out, int32_t n, float L, int32_t B, const pr_rule* rule,
   Dev& d = s->d;
   set_geometry_rules(d, n, L, B, rule, nrules, seed, brick > 0 ? brick : kDefaultBrick);
   s->log_cap = log_cap > 0 ? log_cap : n;
-  e = alloc_system(s->arena, d, n, B, s->log_cap, s->stream);
+  // one device allocation for all arrays: creating a system of 45 allocations
+  // and freeing them took 1.2 ms (every hipFree waits for the device)
+  Arena carve;
+  if (lease && lease->slab) {
+    carve.base = lease->slab;
+    carve.cap = lease->slab_bytes;
+  } else {
+    carve.cap = new_bytes(d, s->log_cap, false);
+    e = s->arena.alloc(&carve.base, carve.cap);
+  }
+  if (!e) e = alloc_new(carve, d, s->log_cap);
+  if (!e && lease && lease->fused) e = alloc_buckets(carve, d);
+  if (!e) e = clear_system(d, s->stream);
   if (!e && !s->hctl && hipHostMalloc((void**)&s->hctl, sizeof(Ctl)) != hipSuccess)
     e = fail(PR_ENOMEM, "hipHostMalloc failed");
-  if (!e) e = grow_part(s, 1024);
   if (e) {
     delete s;
     return e;
   }
+  s->part_cap = kPartSteps;
+  d.part_cap = kPartSteps;
   d.bonds = nullptr;
   d.bonds_cap = 0;
   d.log_cap = s->log_cap;
@@ -1062,7 +1126,12 @@ int pr_sys_load(pr_sys* s, const float* x, const float* y, const float* z, const
   return after_load(s);
 }
 
-int pr_sys_generate(pr_sys* s, int32_t kind, uint64_t gen_seed, double sigma0) {
+}  // extern "C"
+
+namespace {
+
+// The synthetic configuration, up to load_begin.
+int generate_begin(pr_sys* s, int32_t kind, uint64_t gen_seed, double sigma0) {
   int e = check_sys(s, false);
   if (e) return e;
   if (kind != 0 && kind != 1) return fail(PR_EINVAL, "kind must be 0 (step) or 1 (chain)");
@@ -1075,7 +1144,18 @@ int pr_sys_generate(pr_sys* s, int32_t kind, uint64_t gen_seed, double sigma0) {
   const float c0 = (float)(sigma0 / 256.0);
   const unsigned long long thr = threshold(kind == 0 ? 0.05 : 0.001);
   HIP_TRY(launch_generate(d, kind, gen_seed, c0, a, nl, thr, s->stream));
-  return after_load(s);
+  return load_begin(s);
+}
+
+}  // namespace
+
+extern "C" {
+
+int pr_sys_generate(pr_sys* s, int32_t kind, uint64_t gen_seed, double sigma0) {
+  int e = generate_begin(s, kind, gen_seed, sigma0);
+  if (e) return e;
+  HIP_TRY(hipStreamSynchronize(s->stream));
+  return load_end(s);
 }
 
 int pr_sys_set_sort_period(pr_sys* s, int32_t sort_period) {
@@ -1813,11 +1893,13 @@ struct pr_batch {
   int32_t sort_period = 64;
   hipGraphExec_t gexec = nullptr;
   int32_t g_steps = 0;
+  Ctl* hctl = nullptr;            // the replicas' pinned control words
   ~pr_batch() {
     if (gexec) (void)hipGraphExecDestroy(gexec);
     if (copied) (void)hipEventDestroy(copied);
     if (cap) (void)hipStreamDestroy(cap);
     for (pr_sys* s : sys) pr_sys_destroy(s);
+    if (hctl) (void)hipHostFree(hctl);
   }
 };
 
@@ -1850,18 +1932,16 @@ int fill_maps(const std::vector<pr_sys*>& sys, Arena& arena, BatchLaunch& bl) {
     const int np = (d.n + kThreads - 1) / kThreads;
     for (int q = 0; q < np; ++q) part.push_back(make_int4(r, q, np, 0));
   }
-  int4 *m0, *mk, *ms, *mc, *mp, *mr;
+  // one array, one upload
+  std::vector<int4> all;
+  for (const auto* v : {&prep0, &prepk, &sweep, &close, &part, &res})
+    all.insert(all.end(), v->begin(), v->end());
+  int4* m0 = nullptr;
   int e;
-  if ((e = arena.alloc(&m0, prep0.size())) || (e = arena.alloc(&mk, prepk.size())) ||
-      (e = arena.alloc(&ms, sweep.size())) || (e = arena.alloc(&mc, close.size())) ||
-      (e = arena.alloc(&mp, part.size())) || (e = arena.alloc(&mr, res.size())))
-    return e;
-  HIP_TRY(hipMemcpy(m0, prep0.data(), prep0.size() * sizeof(int4), hipMemcpyHostToDevice));
-  HIP_TRY(hipMemcpy(mk, prepk.data(), prepk.size() * sizeof(int4), hipMemcpyHostToDevice));
-  HIP_TRY(hipMemcpy(ms, sweep.data(), sweep.size() * sizeof(int4), hipMemcpyHostToDevice));
-  HIP_TRY(hipMemcpy(mc, close.data(), close.size() * sizeof(int4), hipMemcpyHostToDevice));
-  HIP_TRY(hipMemcpy(mp, part.data(), part.size() * sizeof(int4), hipMemcpyHostToDevice));
-  HIP_TRY(hipMemcpy(mr, res.data(), res.size() * sizeof(int4), hipMemcpyHostToDevice));
+  if ((e = arena.alloc(&m0, all.size()))) return e;
+  HIP_TRY(hipMemcpy(m0, all.data(), all.size() * sizeof(int4), hipMemcpyHostToDevice));
+  int4 *mk = m0 + prep0.size(), *ms = mk + prepk.size(), *mc = ms + sweep.size(),
+       *mp = mc + close.size(), *mr = mp + part.size();
   bl.prep0 = m0;
   bl.prepk = mk;
   bl.sweep = ms;
@@ -1928,33 +2008,72 @@ int pr_batch_create(pr_batch** out, const pr_replica_desc* reps, int32_t n_rep, 
     delete b;
     return fail(PR_EHIP, "hipStreamCreate/hipEventCreate failed");
   }
+  // one device allocation for the arrays of all replicas (with their fused
+  // buckets when all of them can fuse: one rule, the random selection)
   int e = PR_OK;
+  bool fused = true;
+  std::vector<size_t> bytes((size_t)n_rep, 0);
   for (int32_t r = 0; r < n_rep && !e; ++r) {
     const pr_replica_desc& q = reps[r];
+    if (q.n < 1 || q.n > kMaxParticles || q.B < 1) e = fail(PR_EINVAL, "n=%d B=%d", q.n, q.B);
+    else if (q.brick < 0 || q.brick > kMaxBrick) e = fail(PR_EINVAL, "brick=%d", q.brick);
+    else e = validate_rule(&q.rule, q.L);
+    if (e) {
+      const std::string msg = g_err;
+      fail(e, "replica %d: %s", r, msg.c_str());
+    } else if (q.rule.policy == PR_POLICY_NEAREST) {
+      fused = false;
+    }
+  }
+  char* slab = nullptr;
+  for (int pass = fused ? 0 : 1; pass < 2 && !slab && !e; ++pass) {
+    fused = pass == 0;  // without room for the buckets the batch runs unfused
+    size_t all = 0;
+    for (int32_t r = 0; r < n_rep; ++r) {
+      const pr_replica_desc& q = reps[r];
+      Dev g{};
+      set_geometry(g, q.n, q.L, q.B, &q.rule, q.seed, q.brick > 0 ? q.brick : kDefaultBrick);
+      bytes[(size_t)r] = new_bytes(g, q.log_cap > 0 ? q.log_cap : q.n, fused);
+      all += bytes[(size_t)r];
+    }
+    const int ae = b->arena.alloc(&slab, all);
+    if (ae) {
+      slab = nullptr;
+      (void)hipGetLastError();
+      if (pass == 1) e = ae;
+    }
+  }
+  if (!e && hipHostMalloc((void**)&b->hctl, sizeof(Ctl) * (size_t)n_rep) != hipSuccess)
+    e = fail(PR_ENOMEM, "hipHostMalloc failed");
+  for (int32_t r = 0; r < n_rep && !e; ++r) {
+    const pr_replica_desc& q = reps[r];
+    SysLease lease;
+    lease.slab = slab;
+    lease.slab_bytes = bytes[(size_t)r];
+    lease.fused = fused;
+    lease.hctl = b->hctl + r;
+    slab += bytes[(size_t)r];
     pr_sys* s = nullptr;
-    e = pr_sys_create_ex(&s, q.n, q.L, q.B, &q.rule, q.seed, q.log_cap, stream, q.brick);
+    e = sys_create(&s, q.n, q.L, q.B, &q.rule, q.seed, q.log_cap, stream, q.brick, &lease);
     if (!e) {
       b->sys.push_back(s);
-      e = pr_sys_generate(s, q.gen_kind, q.gen_seed, q.gen_sigma0);
+      e = generate_begin(s, q.gen_kind, q.gen_seed, q.gen_sigma0);
     }
     if (e) {
       const std::string msg = g_err;
       fail(e, "replica %d: %s", r, msg.c_str());
     }
   }
-  if (!e) e = fill_maps(b->sys, b->arena, b->bl);
-  // fused binning when every replica can take it (one rule, the random
-  // selection): no binning kernel in the batch's steps
-  if (!e && !b->bl.any_nearest) {
-    bool all = true;
-    for (pr_sys* s : b->sys) {
-      if (alloc_fused(s) != PR_OK || !s->d.fcnt[0]) {
-        all = false;
-        break;
-      }
+  if (!e && hipStreamSynchronize(b->stream) != hipSuccess)
+    e = fail(PR_EHIP, "hipStreamSynchronize failed");
+  for (size_t r = 0; r < b->sys.size() && !e; ++r) {
+    if ((e = load_end(b->sys[r]))) {
+      const std::string msg = g_err;
+      fail(e, "replica %d: %s", (int)r, msg.c_str());
     }
-    b->bl.fuse = all ? 1 : 0;
   }
+  if (!e) e = fill_maps(b->sys, b->arena, b->bl);
+  b->bl.fuse = fused ? 1 : 0;
   if (!e) e = b->arena.alloc(&b->ds, (size_t)n_rep);
   if (e) {
     delete b;
@@ -2070,6 +2189,32 @@ namespace {
 
 using Clock = std::chrono::steady_clock;
 
+// A result array of a served request: not cleared, and large ones on huge
+// pages (a std::vector's zero fill and its 4 KiB page faults cost the finisher
+// more than the copy it then makes).
+template <typename T>
+struct HostBuf {
+  T* p = nullptr;
+  HostBuf() = default;
+  HostBuf(const HostBuf&) = delete;
+  HostBuf& operator=(const HostBuf&) = delete;
+  ~HostBuf() { std::free(p); }
+  bool resize(size_t count) {
+    constexpr size_t kHuge = (size_t)2 << 20;
+    const size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
+    std::free(p);
+    p = nullptr;
+    if (bytes < kHuge) {
+      p = (T*)std::malloc(bytes);
+    } else {
+      p = (T*)std::aligned_alloc(kHuge, (bytes + kHuge - 1) & ~(kHuge - 1));
+      if (p) (void)madvise((void*)p, bytes, MADV_HUGEPAGE);
+    }
+    return p != nullptr;
+  }
+  T* data() { return p; }
+};
+
 struct SrvReq {
   uint64_t ticket = 0;
   pr_replica_desc desc{};
@@ -2082,10 +2227,10 @@ struct SrvReq {
   std::atomic<bool> cancel{false};  // admitted and cancelled: retired at the round's end
   pr_sys* sys = nullptr;
   // results, host memory
-  std::vector<int32_t> bonds;
+  HostBuf<int32_t> bonds;
   int64_t n_bonds = 0;
-  std::vector<float> x, y, z;
-  std::vector<int32_t> state, adj;
+  HostBuf<float> x, y, z;
+  HostBuf<int32_t> state, adj;
   std::vector<pr_stats> stats;
 };
 
@@ -2183,17 +2328,17 @@ int srv_finish(pr_server* S, SrvReq* r) {
     else S->stage = nullptr;  // the copies then go to pageable memory
   }
   if (!e) {
-    r->bonds.resize((size_t)std::max<int64_t>(nb, 1) * 3);
-    e = sys_bonds(s, r->bonds.data(), nb, &nb, S->stage, S->stage_bytes);
+    if (!r->bonds.resize((size_t)std::max<int64_t>(nb, 1) * 3))
+      e = fail(PR_ENOMEM, "no host memory for the results");
+    else
+      e = sys_bonds(s, r->bonds.data(), nb, &nb, S->stage, S->stage_bytes);
     r->n_bonds = nb;
   }
   if (!e) {
-    r->x.resize(n);
-    r->y.resize(n);
-    r->z.resize(n);
-    r->state.resize(n);
-    r->adj.resize(n * B);
-    if (S->stage) {
+    if (!r->x.resize(n) || !r->y.resize(n) || !r->z.resize(n) || !r->state.resize(n) ||
+        !r->adj.resize(n * B)) {
+      e = fail(PR_ENOMEM, "no host memory for the results");
+    } else if (S->stage) {
       float* sx = (float*)S->stage;
       int32_t* ss = (int32_t*)(sx + 3 * n);
       int32_t* sa = ss + n;
