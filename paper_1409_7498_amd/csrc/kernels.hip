@@ -890,12 +890,16 @@ __device__ __forceinline__ void multi_candidates(const Dev& d, const Arr& a, uin
                                                  float r2, F f, const int4* arow = nullptr) {
   const uint32_t both = rt & ((uint32_t)a.role[sa] >> 4);
   if (!both) return;
-#pragma unroll
-  for (int r = 0; r < kMaxRules; ++r) {
-    if (r >= d.nrules || !((both >> r) & 1u) || !(r2 < d.mr[r].rc2)) continue;
-    const W4 w = philox(step, (uint32_t)ida, idj, d.mr[r].tag, d.seed);
-    const bool acc = w.w0 < d.mr[r].thresh;
-    f(r, w, acc && d.mr[r].r.exclude && pair_bonded(d, a, sa, idj, arow), acc);
+  // not unrolled: four copies of the generator took the sweep beyond the 72
+  // registers of seven waves per SIMD, and at six the 1728 bricks of 1,048,576
+  // particles need a second round of workgroups (40.5 us per step; 33.9 now)
+#pragma unroll 1
+  for (int r = 0; r < d.nrules; ++r) {
+    const RuleX& q = d.mr[r];
+    if (!((both >> r) & 1u) || !(r2 < q.rc2)) continue;
+    const W4 w = philox(step, (uint32_t)ida, idj, q.tag, d.seed);
+    const bool acc = w.w0 < q.thresh;
+    f(r, w, acc && q.r.exclude && pair_bonded(d, a, sa, idj, arow), acc);
   }
 }
 
@@ -3190,7 +3194,7 @@ __global__ void k_advance(Ctl* c, int K) {
 // lengthening the resolve.
 template <int kPol, bool kTwo, bool kF, bool kNt = false>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
-    kPol == kMulti || (kPol == kNearest && kTwo && !kF) ? 6 : 7))) void k_sweep(Dev d, int k) {
+    kPol == kNearest && kTwo && !kF ? 6 : 7))) void k_sweep(Dev d, int k) {
   if (kF && (int)blockIdx.x >= d.nwg_sweep) {
     __shared__ uint32_t s_wave[kThreads / 64 + 1];
     const StepInfo si = step_info(d.ctl, k);
