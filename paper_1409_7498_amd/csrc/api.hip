@@ -124,6 +124,29 @@ int prep_blocks(int32_t n) {
   return std::max(1, (int)(((int64_t)n + kThreads * kPrepRoles - 1) / (kThreads * kPrepRoles)));
 }
 
+// Sweep workgroups per brick, and the closing groups that cover the larger of
+// the two sweep grids (dense, bricks).
+void set_split(Dev& d, int32_t wshift) {
+  d.wshift = wshift;
+  d.ngroups = (std::max(d.nwg_sweep, d.nbricks << wshift) + kGroup - 1) / kGroup;
+}
+
+// The split of a single resident system (a batch fills the GPU with replicas),
+// as a shift: one, two or four workgroups per brick.  A small system's few
+// bricks leave most compute units idle and each workgroup's particles in
+// several passes of its threads; sharing a brick costs every workgroup the
+// staging of the region again, which is free only while they run beside each
+// other.  Us per step with 1 / 2 / 4 workgroups per brick (edge 4, step
+// growth): 8 bricks of 500 particles 17.9 / 15.8 / 13.6, 64 of 500 20.6 / 16.4
+// / 14.6, 125 20.0 / 17.9 / 16.3, 216 21.5 / 19.7 / 18.8, 512 22.2 / 21.4, 729
+// 23.4 / 24.0, 1728 30.5 / 41.1; 8 bricks of 250 15.8 / 13.9 / 13.5.  Bricks
+// below 224 particles stay whole: with few A's there is nothing to share but
+// the staging (8 bricks of 192, chain growth 11.3 whole and 11.6 shared).
+int32_t split_of(const Dev& d) {
+  if (d.n / d.nbricks < 224) return 0;
+  return d.nbricks <= 256 ? (d.n / d.nbricks < 384 ? 1 : 2) : d.nbricks <= 512 ? 1 : 0;
+}
+
 // Coarse A grid: nc cells per side of width L/nc >= 2 rc (1 + 2^-10); the
 // margin keeps the 2x2x2 block exact under FP32 rounding of the cell index.
 // Bricks of bs^3 cells; the staged region (bs + 2 cells per side) must not
@@ -170,8 +193,7 @@ void set_geometry(Dev& d, int32_t n, float L, int32_t B, const pr_rule* r, uint6
   d.nd = (d.bs + 1) * (d.bs + 1) * (d.bs + 1) + 1;  // the brick's A's, then its dual cells
   d.nb_m = (uint32_t)((1ull << 32) / (unsigned long long)d.nb);  // nb >= 1; nb = 1 gives 0
   d.sorted = 0;
-  // closing groups cover the larger of the two sweep grids (dense, bricks)
-  d.ngroups = (std::max(d.nwg_sweep, d.nbricks) + kGroup - 1) / kGroup;
+  set_split(d, 0);
 }
 
 // Validation of a set of concurrent rules (each as validate_rule; several
@@ -794,7 +816,7 @@ int sort_storage(pr_sys* s, hipStream_t st) {
   s->d.fuse = fuse_eligible(s) ? 1 : 0;
   HIP_TRY(launch_sort(s->d, !s->d.sorted, st));
   s->d.sorted = 1;
-  s->d.nwg_sweep = s->d.nbricks;
+  s->d.nwg_sweep = s->d.nbricks << s->d.wshift;
   s->steps_since_sort = 0;
   return PR_OK;
 }
@@ -842,7 +864,7 @@ void after_segment(pr_sys* s, int32_t K, bool with_sort) {
   if (with_sort) {
     s->d.fuse = fuse_eligible(s) ? 1 : 0;
     s->d.sorted = 1;
-    s->d.nwg_sweep = s->d.nbricks;
+    s->d.nwg_sweep = s->d.nbricks << s->d.wshift;
     s->steps_since_sort = K;
   } else {
     s->steps_since_sort += K;
@@ -906,7 +928,7 @@ namespace {
 // on demand) and the host-read staging buffers (on first read), added up (a
 // dry arena) or carved out of one allocation.
 int alloc_system(Arena& A, Dev& d, int32_t n, int32_t B, int64_t log_cap) {
-  int e = alloc_scratch(A, d, n, std::max(sweep_blocks(n), d.nbricks), nullptr);
+  int e = alloc_scratch(A, d, n, std::max(sweep_blocks(n), d.nbricks << d.wshift), nullptr);
   for (int q = 0; q < 2 && !e; ++q) {
     Arr& a = d.set[q];
     for (int p = 0; p < 2 && !e; ++p) {
@@ -1041,6 +1063,7 @@ int sys_create(pr_sys** out, int32_t n, float L, int32_t B, const pr_rule* rule,
   }
   Dev& d = s->d;
   set_geometry_rules(d, n, L, B, rule, nrules, seed, brick > 0 ? brick : kDefaultBrick);
+  if (!lease) set_split(d, split_of(d));
   s->log_cap = log_cap > 0 ? log_cap : n;
   // one device allocation for all arrays: creating a system of 45 allocations
   // and freeing them took 1.2 ms (every hipFree waits for the device)

@@ -161,6 +161,7 @@ struct Dev {
   int32_t ncell_clear;
   int32_t n, B, nc, ncell, nwg_sweep, nwg_prep, ngroups;
   int32_t bs, nb, nbricks, sorted;  // brick edge (cells), bricks per side, total, storage sorted
+  int32_t wshift;                    // 1 << wshift sweep workgroups per brick (see split_of)
   int32_t nd;                        // sort bins per brick, (bs + 1)^3 + 1
   uint32_t nb_m;                     // floor(2^32 / nb): brick coordinates by multiplication
   int32_t jitter;       // 1: resident system (positions ping-pong, re-jitter by jit_c)

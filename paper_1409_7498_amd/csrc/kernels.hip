@@ -743,12 +743,20 @@ __device__ __forceinline__ void fuse_drop(const Dev& d, uint32_t par, int slot) 
   fuse_drop_at(d, par, d.apos[slot]);
 }
 
+// The brick of sweep workgroup w (1 << wshift workgroups share one).
+__device__ __forceinline__ int brick_of(const Dev& d, int w) { return w >> d.wshift; }
+
 // Slot range of sweep/resolve workgroup w.
 template <bool kBrick>
 __device__ __forceinline__ void range_of(const Dev& d, int w, int& s0, int& s1) {
   if (kBrick) {
-    s0 = d.bstart[w];
-    s1 = d.bstart[w + 1];
+    const int b = brick_of(d, w);
+    s0 = d.bstart[b];
+    s1 = d.bstart[b + 1];
+    // its share of the brick's slots
+    const int per = (s1 - s0 + (1 << d.wshift) - 1) >> d.wshift;
+    s0 = min(s1, s0 + (w - (b << d.wshift)) * per);
+    s1 = min(s1, s0 + per);
   } else {
     s0 = w * kThreads;
     s1 = min(d.n, s0 + kThreads);
@@ -1062,7 +1070,7 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
     return (cz * nc + cy) * nc + cx;
   };
   int bxc, byc;
-  const int bzc = div_nb(d, div_nb(d, w, bxc), byc);
+  const int bzc = div_nb(d, div_nb(d, brick_of(d, w), bxc), byc);
   region_dim(d, bxc, bx, ex);
   region_dim(d, byc, by, ey);
   region_dim(d, bzc, bz, ez);
@@ -3717,9 +3725,10 @@ hipError_t launch_kinetics(const Dev& d, int nstate, int nbins, double rc, unsig
   Dev dn = d;
   dn.jit_c = 0.0f;
   dn.fuse = 0;  // binned into the plain buckets here, whatever the steps use
+  dn.wshift = 0;  // one workgroup per brick
   k_prep<<<d.nwg_prep, kThreads, 0, s>>>(dn, 0);
   if (d.sorted && d.bs <= kOneCellBrick)
-    k_kin_pairs_staged<<<d.nwg_sweep, kThreads, 0, s>>>(dn, nstate, nbins, rc, kin);
+    k_kin_pairs_staged<<<d.nbricks, kThreads, 0, s>>>(dn, nstate, nbins, rc, kin);
   else
     k_kin_pairs<<<std::min(blocks_for(d.n, kThreads), 2048), kThreads, 0, s>>>(dn, nstate, nbins,
                                                                                rc, kin);
