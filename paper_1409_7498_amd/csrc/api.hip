@@ -41,6 +41,8 @@ hipError_t launch_block_end(const Dev& d, int K, hipStream_t s);
 hipError_t launch_single(const Dev& d, uint32_t step, uint32_t par, SingleOut* out, hipStream_t s);
 hipError_t launch_sort(const Dev& d, bool fresh, hipStream_t s);
 hipError_t log_order(int32_t* log, int64_t n, hipStream_t s);
+hipError_t launch_log_segs(const Dev& d, int K, uint32_t* seg, hipStream_t s);
+hipError_t launch_log_steps(const Dev& d, int k0, int K, const uint32_t* seg, hipStream_t s);
 hipError_t launch_gather_out(const Dev& d, float* ox, float* oy, float* oz, int32_t* otyp,
                              int32_t* ost, int32_t* oadj, hipStream_t s);
 hipError_t launch_draws(const uint32_t* ctr, long long n, unsigned long long key, uint32_t* out,
@@ -625,6 +627,12 @@ struct pr_sys {
   int64_t part_cap = 0;
   int64_t steps_since_load = 0;
   int64_t steps_since_sort = 0;
+  // the bond log: whether every run since the load began after the steps of
+  // the one before it (log_next), and the rows and steps ordered by the last
+  // read
+  bool log_mono = true;
+  uint32_t log_next = 0;
+  int64_t log_done = 0, log_done_steps = 0;
   bool loaded = false;
   bool poisoned = false;
   int32_t sort_period = 0;
@@ -773,6 +781,16 @@ void fuse_after_run(pr_sys* s, uint32_t first_step, uint32_t n_steps) {
   s->rec_jit = s->d.jit_c;
 }
 
+// Books n_steps steps from first_step (launched or ended): counter-log records,
+// and whether the bond log still holds the steps in increasing order.
+void book_steps(pr_sys* s, uint32_t first_step, uint32_t n_steps) {
+  if (n_steps == 0) return;
+  if ((s->steps_since_load > 0 && first_step < s->log_next) || first_step + n_steps < first_step)
+    s->log_mono = false;
+  s->log_next = first_step + n_steps;
+  s->steps_since_load += n_steps;
+}
+
 // The device side of a load (the configuration is in storage set 0): the
 // launches, and the copy of the control block that load_end looks at.
 int load_begin(pr_sys* s) {
@@ -795,6 +813,9 @@ int load_begin(pr_sys* s) {
 int load_end(pr_sys* s) {
   if (s->d.md_theta > 0) s->d.md_all = s->hctl->md_lone ? 1 : 0;
   s->steps_since_load = 0;
+  s->log_mono = true;
+  s->log_next = 0;
+  s->log_done = s->log_done_steps = 0;
   if (s->hctl->err) {
     s->loaded = false;
     return fail(s->hctl->err, "invalid particle position (NaN or outside [0, L))");
@@ -1272,7 +1293,7 @@ static int run_impl(pr_sys* s, uint32_t first_step, uint32_t n_steps, double sig
       ms_sort[1] = (float)nsort;
     }
     for (auto& v : ev) (void)hipEventDestroy(v);
-    s->steps_since_load += n_steps;
+    book_steps(s, first_step, n_steps);
     fuse_after_run(s, first_step, n_steps);
     return PR_OK;
   }
@@ -1291,7 +1312,7 @@ static int run_impl(pr_sys* s, uint32_t first_step, uint32_t n_steps, double sig
     }
     left -= (uint32_t)K;
   }
-  s->steps_since_load += n_steps;
+  book_steps(s, first_step, n_steps);
   fuse_after_run(s, first_step, n_steps);
   return PR_OK;
 }
@@ -1562,36 +1583,43 @@ int pr_sys_read(pr_sys* s, float* x, float* y, float* z, int32_t* state, int32_t
 namespace {
 
 // The bond log in (step, id_A) order.  pin (may be NULL): pinned host memory
-// of pin_bytes for the device copy (the rows are ordered in place there).
+// of pin_bytes for the device copy (else it goes straight to out).
 int sys_bonds(pr_sys* s, int32_t* out, int64_t cap, int64_t* n, void* pin, size_t pin_bytes) {
   int e = check_sys(s, false);
   if (e) return e;
   if (!n || (cap > 0 && !out)) return fail(PR_EINVAL, "NULL output");
+  // the first row of every step, when the log can be ordered step by step (in
+  // the overflow array, idle between runs)
+  const int64_t steps = s->steps_since_load;
+  uint32_t* seg = (uint32_t*)s->d.ovf[0];
+  bool by_step = cap > 0 && s->log_mono && steps <= s->part_cap && steps < 4 * (int64_t)s->d.n;
+  if (by_step) HIP_TRY(launch_log_segs(s->d, (int)steps, seg, s->stream));
   if ((e = sync_ctl(s))) return e;
   const int64_t total = (int64_t)s->hctl->log_n;
   const int64_t have = std::min<int64_t>(total, s->log_cap);
   const int64_t m = std::min<int64_t>(have, cap);
+  by_step = by_step && total == have && s->hctl->log_rows == (uint64_t)total &&
+            (int64_t)s->hctl->stats_n0 == steps && s->hctl->log_most <= (uint32_t)kLogLds;
   if (m > 0) {
     // the rows of one step were appended in workgroup order: the device
-    // orders the log in place by (step, id_A) (log_order), then it is copied
+    // orders the log in place by (step, id_A), the steps not ordered yet one
+    // by one, else the whole log (log_order), then it is copied
     struct Row {
       int32_t step, a, t;
     };
-    HIP_TRY(log_order(s->d.log, have, s->stream));
-    std::vector<Row> vrows;
-    Row* rows = nullptr;
-    if (pin && pin_bytes >= (size_t)m * sizeof(Row)) {
-      rows = (Row*)pin;
-    } else {
-      vrows.resize((size_t)m);
-      rows = vrows.data();
-    }
+    if (by_step)
+      HIP_TRY(launch_log_steps(s->d, (int)s->log_done_steps, (int)steps, seg, s->stream));
+    else if (have != s->log_done)
+      HIP_TRY(log_order(s->d.log, have, s->stream));
+    s->log_done = have;
+    s->log_done_steps = by_step ? steps : 0;
+    Row* rows = pin && pin_bytes >= (size_t)m * sizeof(Row) ? (Row*)pin : (Row*)out;
     HIP_TRY(hipMemcpyAsync(rows, s->d.log, (size_t)m * sizeof(Row), hipMemcpyDeviceToHost,
                            s->stream));
     HIP_TRY(hipStreamSynchronize(s->stream));
     if (s->d.nrules > 1)  // the rule of each bond rides in bits 30-31 of id_T
       for (size_t i = 0; i < (size_t)m; ++i) rows[i].t &= 0x3FFFFFFF;
-    std::memcpy(out, rows, (size_t)m * sizeof(Row));
+    if (rows != (Row*)out) std::memcpy(out, rows, (size_t)m * sizeof(Row));
   }
   *n = total;
   if (total > s->log_cap)
@@ -1779,6 +1807,8 @@ int pr_sys_restore(pr_sys* s, const void* buf, int64_t bytes) {
   HIP_TRY(hipMemcpyAsync(&d.ctl->stats_n0, &n0, sizeof n0, hipMemcpyHostToDevice, s->stream));
   HIP_TRY(hipMemcpyAsync(&d.ctl->log_n, &ln, sizeof ln, hipMemcpyHostToDevice, s->stream));
   s->steps_since_load = h.steps;
+  // the restored rows are in order, of steps the counters do not name
+  s->log_mono = h.steps == 0 && h.rows == 0;
   return sync_ctl(s);
 }
 
@@ -2161,7 +2191,7 @@ int pr_batch_run(pr_batch* b, uint32_t first_step, uint32_t n_steps, double sigm
   for (pr_sys* s : b->sys) {
     drop_graph(s);
     s->steps_since_sort = n_steps % (uint32_t)K == 0 ? K : (int32_t)(n_steps % (uint32_t)K);
-    s->steps_since_load += n_steps;
+    book_steps(s, first_step, n_steps);
     s->d.kpar0 = (s->d.kpar0 + n_steps) & 1u;  // the batch advanced the parity origin
   }
   return PR_OK;
@@ -2467,10 +2497,10 @@ int srv_end_round(pr_server* S) {
   S->busy_s += ms * 1e-3;
   S->rounds++;
   for (SrvReq* r : S->active) {
+    book_steps(r->sys, 1u + r->done_steps, r->round_steps);
     r->done_steps += r->round_steps;
     drop_graph(r->sys);
     r->sys->steps_since_sort = (int64_t)r->round_steps;
-    r->sys->steps_since_load += r->round_steps;
     r->sys->d.kpar0 = (r->sys->d.kpar0 + r->round_steps) & 1u;
   }
   return PR_OK;

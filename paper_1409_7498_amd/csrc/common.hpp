@@ -17,6 +17,7 @@ constexpr int kThreads = 256;       // workgroup size of the per-particle kernel
 constexpr int kPrepRoles = 16;      // role bytes a prep thread scans for A's
 constexpr int kFinThreads = 1024;   // the single-workgroup finishing kernels
 constexpr int kSortLds = 4096;      // bonds of a stateless step sorted in LDS up to this
+constexpr int kLogLds = 4096;       // bond-log rows of one step ordered in LDS
 constexpr int kStatsPerStep = 9;    // pr_stats fields
 constexpr int kGroup = 256;         // sweep workgroups closed by one closing workgroup
 constexpr int kPart = 8;            // partial counters per closing workgroup and step
@@ -66,6 +67,7 @@ struct Ctl {
   uint32_t stats_n0;   // counter-log index of the block's first step
   uint64_t log_n;      // rows appended to the bond log (may exceed capacity)
   uint32_t fovf_n[3];  // fused binning: A records beyond their bucket, by step mod 3
+  uint32_t log_most, log_rows;  // k_log_segs: the most rows of a step, rows of all steps
   uint32_t md_lone;    // MD: some adjacency row names a particle whose own row is empty
 };
 

@@ -1,4 +1,6 @@
-// logsort.hip -- canonical order of a resident system's bond log, on the device.
+// logsort.hip -- canonical order of a resident system's bond log, on the device:
+// the general case (a log whose steps ran in increasing order is ordered step by
+// step, k_log_steps).
 //
 // The log holds rows (step, id_A, id_T) of int32.  The closing kernels append
 // the rows of one step together and the steps in order, but within a step in
