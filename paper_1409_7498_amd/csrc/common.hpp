@@ -174,6 +174,10 @@ struct Dev {
   int32_t k_limit;
   uint32_t first_step;
   float L, halfL, rc2, inv_w, jit_c;
+  // the sweep's scan: positions in units of L / 2^m, and the squared distance
+  // in those units below which a pair is a candidate
+  float qscale;
+  uint32_t qthr;
   unsigned long long thresh, seed;
   RuleD rule;
   // several concurrent rules (nrules > 1; then rc2 is the largest cutoff's)

@@ -44,6 +44,20 @@ struct W4 {
   uint32_t w0, w1, w2, w3;
 };
 
+// d behind a pointer that the compiler cannot see through, in read-only memory
+// (the kernel's arguments, or a batch's device array): what is read through it
+// comes in by scalar loads where it is used.  Read directly, the fields that a
+// long kernel uses anywhere are loaded ahead of it and kept, and what the
+// scalar registers do not hold is spilled into lanes of vector registers,
+// whose reads are vector instructions: in the sweep 88 spilled registers, 40
+// this way (1,048,576 particles, 256 steps with load and read-out: 7.80 -> 7.55 ms).
+__device__ __forceinline__ const Dev& fresh(const Dev& d) {
+  typedef const __attribute__((address_space(4))) Dev* cptr;
+  cptr p = (cptr)&d;
+  asm volatile("" : "+s"(p));
+  return *(const Dev*)p;
+}
+
 // a ^ b ^ c in one instruction (gfx950's three-input bitwise op; 0x96 is the
 // truth table of the three-way exclusive or)
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
@@ -602,18 +616,6 @@ __device__ __forceinline__ float dist2_plain(float xj, float yj, float zj, float
   return __fadd_rn(__fadd_rn(__fmul_rn(dx, dx), __fmul_rn(dy, dy)), __fmul_rn(dz, dz));
 }
 
-// dist2 of two positions whose differences lie within (-L/2, L/2) in every
-// component but axis kAxis (there the minimum image is taken as in dist2):
-// the same value as dist2.
-template <int kAxis>
-__device__ __forceinline__ float dist2_axis(const Dev& d, float xj, float yj, float zj, float4 a) {
-  float dx = __fsub_rn(xj, a.x), dy = __fsub_rn(yj, a.y), dz = __fsub_rn(zj, a.z);
-  if (kAxis == 0) dx = min_image(dx, d.L, d.halfL);
-  if (kAxis == 1) dy = min_image(dy, d.L, d.halfL);
-  if (kAxis == 2) dz = min_image(dz, d.L, d.halfL);
-  return __fadd_rn(__fadd_rn(__fmul_rn(dx, dx), __fmul_rn(dy, dy)), __fmul_rn(dz, dz));
-}
-
 __device__ __forceinline__ bool row_has(const int32_t* row, int B, int32_t v) {
   for (int b = 0; b < B; ++b)
     if (row[b] == v) return true;
@@ -763,14 +765,15 @@ __device__ __forceinline__ void range_of(const Dev& d, int w, int& s0, int& s1) 
   }
 }
 
-// Draw, exclusion and A-side choice of an in-range pair (steps 2-5).  A
-// retained pair lowers the A's key (w1, id_T) with a 64-bit atomicMin whose
+// Acceptance, exclusion and A-side choice of an in-range pair with draws r
+// (steps 2-5).  A retained pair lowers the A's key (w1, id_T) with a 64-bit atomicMin whose
 // result is not needed, flags its T and is handed to the resolve in the
 // workgroup's list.  arow: the A's adjacency row staged with its record
 // (nullptr: the row is read from the particle arrays).
-struct SweepAcc {
-  int t_elig, in_rc, drawn, excl, a_elig;
-};
+// The sweep counts in LDS (cnt: the workgroup's counters by WgOut), one atomic
+// per wavefront and event: per-lane counters would hold registers through the
+// scan and need a wavefront sum each at the end.
+__device__ __forceinline__ void count_one(int* c) { atomicAdd(c, 1); }
 
 struct RetList {
   int* n;
@@ -800,14 +803,13 @@ __device__ __forceinline__ bool pair_bonded(const Dev& d, const Arr& a, int sa, 
   return q.x == v || q.y == v || q.z == v || q.w == v;
 }
 
-__device__ __forceinline__ void retain(const Dev& d, const Arr& a, uint32_t step, int ida,
-                                       int sa, uint32_t idj, int sj, const int4* arow,
-                                       SweepAcc& n, const RetList& l) {
-  const W4 r = philox(step, (uint32_t)ida, idj, 0u, d.seed);
+__device__ __forceinline__ void retain(const Dev& d, const Arr& a, W4 r, int ida, int sa,
+                                       uint32_t idj, int sj, const int4* arow, int* cnt,
+                                       const RetList& l) {
   if (!((unsigned long long)r.w0 < d.thresh)) return;
-  n.drawn++;
+  count_one(&cnt[kOutDrawn]);
   if (d.rule.exclude && pair_bonded(d, a, sa, idj, arow)) {
-    n.excl++;
+    count_one(&cnt[kOutExcl]);
     return;
   }
   d.tflag[sj] = 1;
@@ -824,10 +826,10 @@ __device__ __forceinline__ void retain(const Dev& d, const Arr& a, uint32_t step
 // id_T) and its T's (r2 bits, id_A), the T's in LDS (r2 >= 0 orders like its
 // bits, equal distances go to the lower id).
 __device__ __forceinline__ void near_pair(const Dev& d, const Arr& a, int ida, int sa, uint32_t idj,
-                                          float r2, const int4* arow, SweepAcc& n,
+                                          float r2, const int4* arow, int* cnt,
                                           unsigned long long* best) {
   if (d.rule.exclude && pair_bonded(d, a, sa, idj, arow)) {
-    n.excl++;
+    count_one(&cnt[kOutExcl]);
     return;
   }
   const unsigned long long rb = (unsigned long long)__float_as_uint(r2) << 32;
@@ -916,14 +918,14 @@ __device__ __forceinline__ void multi_candidates(const Dev& d, const Arr& a, uin
 // into the list with their rule in bits 30-31 of id_T (ids are below 2^30).
 __device__ __forceinline__ void multi_pair(const Dev& d, const Arr& a, uint32_t step, uint32_t rt,
                                            int ida, int sa, uint32_t idj, int sj, float r2,
-                                           const int4* arow, SweepAcc& n, const RetList& l) {
+                                           const int4* arow, int* cnt, const RetList& l) {
   if ((uint32_t)ida == idj) return;  // a particle with both roles is no partner of itself
   multi_candidates(d, a, step, rt, sa, ida, idj, r2, [&](int r, W4 w, bool ex, bool acc) {
-    n.in_rc++;
+    count_one(&cnt[kOutInRc]);
     if (!acc) return;
-    n.drawn++;
+    count_one(&cnt[kOutDrawn]);
     if (ex) {
-      n.excl++;
+      count_one(&cnt[kOutExcl]);
       return;
     }
     d.tflag[sj] = 1;
@@ -935,6 +937,77 @@ __device__ __forceinline__ void multi_pair(const Dev& d, const Arr& a, uint32_t 
       l.w2[p] = w.w2;
     }
   }, arow);
+}
+
+// ---------------------------------------------------------------------------
+// The scan of a T's block in the staged records, the sweep's inner loop.  It
+// looks for candidates, not for in-range pairs: positions are taken as 16-bit
+// integers in units of L / 2^m (Dev::qscale, m >= 16, so that the integers wrap
+// around exactly where the box does and their differences need no minimum
+// image), two packed subtractions and two dot products give the squared
+// distance in those units, and every pair within the cutoff passes (Dev::qthr
+// allows for the rounding, set_quant).  The few others that pass (about 0.5%)
+// fall at the exact FP32 test, which every candidate takes on full wavefronts
+// from the queue.  The four runs of two x-adjacent cells are one sequence: a
+// word D counts down in each of its bytes to the ends of the runs, the sign
+// bits of the bytes say which runs are not yet done, and their dot product with
+// the (byte) steps between the runs moves the index.  Bound: VALU issue of the
+// trips of a wavefront's longest block, 16 instructions each instead of 24 (one
+// compare and select per run, FP32 distance), 30 in a region that wraps in one
+// axis and 42 beyond.  1,048,576 particles, 256 steps with load and read-out:
+// 7.90 -> 7.80 ms.
+// ---------------------------------------------------------------------------
+typedef short short2_t __attribute__((ext_vector_type(2)));
+
+// A position in the scan's units: (x | y << 16, z).
+__device__ __forceinline__ uint2 quant(const Dev& d, float x, float y, float z) {
+  const uint32_t qx = (uint32_t)(int)__fmul_rn(x, d.qscale), qy = (uint32_t)(int)__fmul_rn(y, d.qscale),
+                 qz = (uint32_t)(int)__fmul_rn(z, d.qscale);
+  return make_uint2(__builtin_amdgcn_perm(qy, qx, 0x05040100u), qz & 0xFFFFu);
+}
+
+// Squared distance in the scan's units (32-bit wrap; every component difference
+// is below 2^15 in magnitude).
+__device__ __forceinline__ uint32_t quant_d2(uint2 a, uint2 b) {
+  const short2_t dxy = __builtin_bit_cast(short2_t, a.x) - __builtin_bit_cast(short2_t, b.x);
+  const short2_t dz = __builtin_bit_cast(short2_t, a.y) - __builtin_bit_cast(short2_t, b.y);
+  return (uint32_t)__builtin_amdgcn_sdot2(dz, dz, __builtin_amdgcn_sdot2(dxy, dxy, 0, false), false);
+}
+
+// Candidates of the T at t among the staged records (s_qr) of its block, whose
+// first region cell is l0 (ex cells per row, exy per layer; s_off: first record
+// of each region cell): nh counts them, hits keeps the last four, one byte
+// each.
+__device__ __forceinline__ void scan_block(const uint2* s_qr, const uint16_t* s_off, int l0, int ex,
+                                           int exy, uint2 t, uint32_t thr, int& nh,
+                                           uint32_t& hits) {
+  // runs (dy, dz) = (0,0), (1,0), (0,1), (1,1): two cells each
+  const int l1 = l0 + ex, l2 = l0 + exy, l3 = l2 + ex;
+  const int b0 = (int)s_off[l0], b1 = (int)s_off[l1], b2 = (int)s_off[l2], b3 = (int)s_off[l3];
+  const int p1 = (int)s_off[l0 + 2] - b0;
+  const int p2 = p1 + (int)s_off[l1 + 2] - b1;
+  const int p3 = p2 + (int)s_off[l2 + 2] - b2;
+  const int tot = p3 + (int)s_off[l3 + 2] - b3;
+  static_assert(8 * kCellCap <= 127, "no borrow from byte to byte of D");
+  // record of place q: q + o3, plus (o2 - o3) while q < p3, (o1 - o2) while q
+  // < p2 and (o0 - o1) while q < p1 (o: the run's first record less its place)
+  const int o1 = b1 - p1, o2 = b2 - p2, o3 = b3 - p3;
+  uint32_t D = ((uint32_t)p1 | ((uint32_t)p2 << 8) | ((uint32_t)p3 << 16) | ((uint32_t)tot << 24)) +
+               0x7F7F7F7Fu;
+  // bytes -(step) mod 256: a set sign byte counts -128
+  const uint32_t step = ((uint32_t)(o1 - b0) & 0xFFu) | (((uint32_t)(o2 - o1) & 0xFFu) << 8) |
+                        (((uint32_t)(o3 - o2) & 0xFFu) << 16);
+  int acc = o3 << 7;  // 128 x the index, of which bits 7..14 count
+  while ((int32_t)D < 0) {  // the last byte: places left
+    const uint32_t v =
+        (uint32_t)__builtin_amdgcn_sdot4((int)(D & 0x80808080u), (int)step, acc, false);
+    const uint32_t r = (v >> 7) & 0xFFu;
+    const bool in = quant_d2(s_qr[r], t) < thr;
+    hits = in ? (hits << 8) | r : hits;
+    nh += in ? 1 : 0;
+    D -= 0x01010101u;
+    acc += 128;
+  }
 }
 
 // The selection a sweep is compiled for.
@@ -1008,12 +1081,14 @@ __device__ __forceinline__ void rejitter(const Dev& d, uint32_t step, uint32_t i
 // each pair where the scan met it, after a binning kernel: 1,048,576
 // particles, nearest 39.1 + 8.4 -> 31.3 us, two rules 28.8 + 5.4 -> 28.0.)
 template <int kPol, bool kTwo, bool kF = false, bool kNt = false>
-__device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) {
+__device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg) {
+  const Dev& d = d0;
   constexpr int kCells = kTwo ? kStageCells : kStageCells1;  // region cells at most
   constexpr int kPer = kTPass / kThreads;
   constexpr int kTP = kPer * kThreads;
   constexpr uint32_t kQEmpty = 0xFFFFFFFFu;
   __shared__ float4 s_rec[kStageRecs];
+  __shared__ uint2 s_qr[kStageRecs];      // the records' positions in the scan's units
   __shared__ int4 s_radj[kStageRecs];
   __shared__ int32_t s_rsa[kStageRecs];
   __shared__ uint16_t s_off[kCells + 1];  // first record of a region cell
@@ -1054,12 +1129,16 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
   int s0, s1;
   range_of<true>(d, w, s0, s1);
   int bx = 0, ex = 0, by = 0, ey = 0, bz = 0, ez = 0;
-  bool staged = false, nowrap = false, plain_x = false, plain_y = false, plain_z = false;
+  bool staged = false;
   const int nc = d.nc;
   int ncs = 0;
   uint32_t mine = 0, mine2 = 0, m_exy = 0, m_ex = 0;
   int gc = 0, gc2 = 0;  // global cells of this thread's region cells
   // global cell of region cell cl (region cells in z, y, x order)
+  auto put_rec = [&](uint32_t r, const float4& v) {
+    s_rec[r] = v;
+    s_qr[r] = quant(d, v.x, v.y, v.z);
+  };
   auto region_cell = [&](int cl) {
     const int lz = div_small(cl, m_exy), rem = cl - lz * ex * ey;
     const int ly = div_small(rem, m_ex), lx = rem - ly * ex;
@@ -1074,13 +1153,6 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
   region_dim(d, bxc, bx, ex);
   region_dim(d, byc, by, ey);
   region_dim(d, bzc, bz, ez);
-  // a region that does not wrap around the box and spans less than half of
-  // it: a difference of two positions in it is below L/2 in magnitude, and
-  // the minimum image leaves it unchanged
-  plain_x = d.nbricks > 1 && bx + ex <= nc && 2 * ex + 1 <= nc;
-  plain_y = d.nbricks > 1 && by + ey <= nc && 2 * ey + 1 <= nc;
-  plain_z = d.nbricks > 1 && bz + ez <= nc && 2 * ez + 1 <= nc;
-  nowrap = plain_x && plain_y && plain_z;
   ncs = ex * ey * ez;
   m_exy = recip16((uint32_t)(ex * ey));
   m_ex = recip16((uint32_t)ex);
@@ -1123,14 +1195,14 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
         if (m > 1u) { rv1 = bk.rec[r0 + nn]; sv1 = bk.sa[r0 + nn]; }
         if (kFirst > 2 && m > 2u) { rv2 = bk.rec[r0 + 2 * nn]; sv2 = bk.sa[r0 + 2 * nn]; }
         if (kFirst > 3 && m > 3u) { rv3 = bk.rec[r0 + 3 * nn]; sv3 = bk.sa[r0 + 3 * nn]; }
-        if (m > 0u) { s_rec[o] = rv0; s_rsa[o] = sv0; }
-        if (m > 1u) { s_rec[o + 1] = rv1; s_rsa[o + 1] = sv1; }
-        if (kFirst > 2 && m > 2u) { s_rec[o + 2] = rv2; s_rsa[o + 2] = sv2; }
-        if (kFirst > 3 && m > 3u) { s_rec[o + 3] = rv3; s_rsa[o + 3] = sv3; }
+        if (m > 0u) { put_rec(o, rv0); s_rsa[o] = sv0; }
+        if (m > 1u) { put_rec(o + 1, rv1); s_rsa[o + 1] = sv1; }
+        if (kFirst > 2 && m > 2u) { put_rec(o + 2, rv2); s_rsa[o + 2] = sv2; }
+        if (kFirst > 3 && m > 3u) { put_rec(o + 3, rv3); s_rsa[o + 3] = sv3; }
         if (!kF && d.adj_staged)
           for (uint32_t j = 0; j < m && j < (uint32_t)kFirst; ++j) s_radj[o + j] = d.radj[r0 + j * nn];
         for (uint32_t j = kFirst; j < m; ++j) {
-          s_rec[o + j] = bk.rec[r0 + j * nn];
+          put_rec(o + j, bk.rec[r0 + j * nn]);
           s_rsa[o + j] = bk.sa[r0 + j * nn];
           if (!kF && d.adj_staged) s_radj[o + j] = d.radj[r0 + j * nn];
         }
@@ -1143,19 +1215,15 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
   // the workgroup-uniform switches of the pass loop, one scalar register
   // whose bits are tested where they are used (kept as separate booleans
   // they would each occupy a 64-bit lane mask)
-  // kFWrapX/Y/Z: only that axis of the region needs the minimum image
-  constexpr uint32_t kFJit = 1u, kFMove = 2u, kFStaged = 4u, kFNowrap = 8u;
-  constexpr uint32_t kFWrapX = 16u, kFWrapY = 32u, kFWrapZ = 64u;
+  constexpr uint32_t kFJit = 1u, kFMove = 2u, kFStaged = 4u;
   const uint32_t flags0 = (uint32_t)__builtin_amdgcn_readfirstlane(
-      (jit ? kFJit : 0u) | (d.jitter ? kFMove : 0u) | (staged ? kFStaged : 0u) |
-      (nowrap ? kFNowrap : 0u) | (!plain_x && plain_y && plain_z ? kFWrapX : 0u) |
-      (plain_x && !plain_y && plain_z ? kFWrapY : 0u) |
-      (plain_x && plain_y && !plain_z ? kFWrapZ : 0u));
-  SweepAcc n = {0, 0, 0, 0, 0};
+      (jit ? kFJit : 0u) | (d.jitter ? kFMove : 0u) | (staged ? kFStaged : 0u));
+  int t_elig = 0, a_elig = 0;  // of the wavefront
   for (int base = s0; base < s1 && !dead; base += kTP) {
     if (base != s0) cur = load_part(a, X, Y, Z, base + tid, s1);
 #pragma unroll 1
     for (int u = 0; u < kPer; ++u) {
+      const Dev& d = fresh(d0);
       const int lt = u * kThreads + tid;
       const int slot = base + lt;
       uint32_t fl = flags0;
@@ -1166,6 +1234,9 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
       if (u == 0) __builtin_amdgcn_s_setprio(3);
       else if (u == 1) __builtin_amdgcn_s_setprio(2);
       else __builtin_amdgcn_s_setprio(1);
+      t_elig += (int)__popcll(__ballot(slot < s1 && pol_t<kPol>(cur.role)));
+      if (kF)
+        a_elig += (int)__popcll(__ballot(slot < s1 && role_is_a((uint32_t)cur.role, kPol == kMulti)));
       // the next particle's loads are in flight while this one is handled
       Part nxt = cur;
       if (u + 1 < kPer) nxt = load_part(a, X, Y, Z, slot + kThreads, s1);
@@ -1191,20 +1262,18 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
         // fused binning: the A's record of the next step, re-jittered once
         // more (its bucket's returning atomic completes behind the rest of
         // the pass)
-        n.a_elig++;
         float nx = cur.x, ny = cur.y, nz = cur.z;
         if (fl & kFJit) rejitter(d, step + 1u, idj, nx, ny, nz);
         fuse_bin(d, par ^ 1u, step + 1u, slot, idj, nx, ny, nz);
       }
       if (kPol == kNearest)
         near_list(slot < s1 && cur.role == kRoleA, cur.id, slot, (int2*)s_ent, &s_ne);
-      // in-range staged records of this T: nh counts them all, hits keeps the
+      // candidates among the staged records: nh counts them all, hits keeps the
       // first four, one byte each (a T with more is deferred)
       int nh = 0;
       uint32_t hits = 0;
       bool defer = false;
       if (slot < s1 && pol_t<kPol>(cur.role)) {
-        n.t_elig++;
         defer = true;
         if (kPol == kNearest) s_tid[lt] = (int)idj;
         if (fl & kFStaged) {
@@ -1216,37 +1285,8 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
                     lz0 = local_lo(pz, d.inv_w, bz, nc);
           if ((uint32_t)lx0 < (uint32_t)(ex - 1) && (uint32_t)ly0 < (uint32_t)(ey - 1) &&
               (uint32_t)lz0 < (uint32_t)(ez - 1)) {
-            // runs (dy, dz) = (0,0), (1,0), (0,1), (1,1): cells lx0 and lx0 + 1
             const int l0 = (int)__umul24(__umul24(lz0, ey) + ly0, ex) + lx0;  // small operands
-            const int l1 = l0 + ex, l2 = l0 + ex * ey, l3 = l2 + ex;
-            const int b0 = (int)s_off[l0], b1 = (int)s_off[l1], b2 = (int)s_off[l2],
-                      b3 = (int)s_off[l3];
-            const int p1 = (int)s_off[l0 + 2] - b0;
-            const int p2 = p1 + (int)s_off[l1 + 2] - b1;
-            const int p3 = p2 + (int)s_off[l2 + 2] - b2;
-            const int tot = p3 + (int)s_off[l3 + 2] - b3;
-            const int o1 = b1 - p1, o2 = b2 - p2, o3 = b3 - p3;
-            // the four runs, with the distance of the region's kind
-            auto scan = [&](auto dist) {
-              for (int q = 0; q < tot; ++q) {
-                const int r = q + (q < p1 ? b0 : (q < p2 ? o1 : (q < p3 ? o2 : o3)));
-                if (dist(s_rec[r]) < d.rc2) {
-                  hits |= (uint32_t)r << ((8 * nh) & 31);
-                  nh++;
-                }
-              }
-            };
-            if (fl & kFNowrap) {  // no difference can reach L/2 in this region
-              scan([&](float4 a) { return dist2_plain(px, py, pz, a); });
-            } else if (fl & kFWrapX) {  // the region wraps (or spans half the box) in x only
-              scan([&](float4 a) { return dist2_axis<0>(d, px, py, pz, a); });
-            } else if (fl & kFWrapY) {
-              scan([&](float4 a) { return dist2_axis<1>(d, px, py, pz, a); });
-            } else if (fl & kFWrapZ) {
-              scan([&](float4 a) { return dist2_axis<2>(d, px, py, pz, a); });
-            } else {
-              scan([&](float4 a) { return dist2(d, px, py, pz, a); });
-            }
+            scan_block(s_qr, s_off, l0, ex, ex * ey, quant(d, px, py, pz), d.qthr, nh, hits);
             defer = nh > 4;
           }
         }
@@ -1266,7 +1306,6 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
             qb + lanes_below(g1) + lanes_below(g2) + lanes_below(g3) + lanes_below(g4);
         if (nh > 0) {
           if (p + (uint32_t)nh <= (uint32_t)kQueue) {
-            if (kPol != kMulti) n.in_rc += nh;  // several rules: counted per rule
             for (int j = 0; j < nh; ++j)
               s_q[p + j] = (uint32_t)lt | (((hits >> (8 * j)) & 0xFFu) << 16);
           } else {
@@ -1282,6 +1321,7 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
       cur = nxt;
     }
     __syncthreads();
+    const Dev& d = fresh(d0);
     // the pass's queued pairs: draws (or keys) on full wavefronts
     const int qn = min(s_qn, kQueue);
     for (int e = tid; e < qn; e += kThreads) {
@@ -1291,18 +1331,23 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
       const uint32_t idj = (uint32_t)s_tid[lt];
       const int sj = base + (int)lt;
       const int4* arow = d.adj_staged && !kF ? &s_radj[r] : nullptr;
-      if (kPol == kRandom) {
-        retain(d, a, step, __float_as_int(s_rec[r].w), s_rsa[r], idj, sj, arow, n, rl);
-      } else {
-        const float4 A = s_rec[r];
-        const float r2 = d.jitter ? dist2(d, XW[sj], YW[sj], ZW[sj], A)
-                                  : dist2(d, X[sj], Y[sj], Z[sj], A);
-        if (kPol == kNearest)
-          near_pair(d, a, __float_as_int(A.w), s_rsa[r], idj, r2, arow, n, &s_best[lt]);
-        else
-          multi_pair(d, a, step, a.role[sj] & kMaskT, __float_as_int(A.w), s_rsa[r], idj, sj, r2,
-                     arow, n, rl);
-      }
+      // the exact test, on the T's position as this workgroup has just written
+      // it (the draws meanwhile: few candidates fail it)
+      const float4 A = s_rec[r];
+      const int ida = __float_as_int(A.w), sa = s_rsa[r];
+      const float tx = d.jitter ? XW[sj] : X[sj], ty = d.jitter ? YW[sj] : Y[sj],
+                  tz = d.jitter ? ZW[sj] : Z[sj];
+      W4 w4{0u, 0u, 0u, 0u};
+      if (kPol == kRandom) w4 = philox(step, (uint32_t)ida, idj, 0u, d.seed);
+      const float r2 = dist2(d, tx, ty, tz, A);
+      if (!(r2 < d.rc2)) continue;
+      if (kPol != kMulti) count_one(&s_cnt[kOutInRc]);  // several rules: counted per rule
+      if (kPol == kRandom)
+        retain(d, a, w4, ida, sa, idj, sj, arow, s_cnt, rl);
+      else if (kPol == kNearest)
+        near_pair(d, a, ida, sa, idj, r2, arow, s_cnt, &s_best[lt]);
+      else
+        multi_pair(d, a, step, a.role[sj] & kMaskT, ida, sa, idj, sj, r2, arow, s_cnt, rl);
     }
     // the deferred T's, re-jittered again from the previous positions: in the
     // staged records when the block lies in a staged region (T's with more
@@ -1318,13 +1363,14 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
       auto pair = [&](const float4& A, int sa, const int4* arow) __attribute__((always_inline)) {
         const float r2 = dist2(d, px, py, pz, A);
         if (!(r2 < d.rc2)) return;
-        if (kPol != kMulti) n.in_rc++;
+        if (kPol != kMulti) count_one(&s_cnt[kOutInRc]);
         if (kPol == kRandom)
-          retain(d, a, step, __float_as_int(A.w), sa, idj, slot, arow, n, rl);
+          retain(d, a, philox(step, (uint32_t)__float_as_int(A.w), idj, 0u, d.seed),
+                 __float_as_int(A.w), sa, idj, slot, arow, s_cnt, rl);
         else if (kPol == kNearest)
-          near_pair(d, a, __float_as_int(A.w), sa, idj, r2, arow, n, &s_best[lt]);
+          near_pair(d, a, __float_as_int(A.w), sa, idj, r2, arow, s_cnt, &s_best[lt]);
         else
-          multi_pair(d, a, step, rt, __float_as_int(A.w), sa, idj, slot, r2, arow, n, rl);
+          multi_pair(d, a, step, rt, __float_as_int(A.w), sa, idj, slot, r2, arow, s_cnt, rl);
       };
       if (staged) {
         const int lx0 = local_lo(px, d.inv_w, bx, nc), ly0 = local_lo(py, d.inv_w, by, nc),
@@ -1396,11 +1442,10 @@ __device__ __forceinline__ void sweep_body(const Dev& d, int k, int w, int nwg) 
   // a step with the binning kernel follows)
   for (int q = w * kThreads + tid; q < d.ncell; q += nwg * kThreads)
     pick(d.cnt, par ^ 1u)[q] = 0u;
-  wave_add(&s_cnt[kOutTElig], n.t_elig);
-  wave_add(&s_cnt[kOutInRc], n.in_rc);
-  wave_add(&s_cnt[kOutDrawn], n.drawn);
-  wave_add(&s_cnt[kOutExcl], n.excl);
-  if (kF) wave_add(&s_cnt[4], n.a_elig);
+  if (__lane_id() == 0) {
+    atomicAdd(&s_cnt[kOutTElig], t_elig);
+    if (kF) atomicAdd(&s_cnt[4], a_elig);
+  }
   __syncthreads();
   const int ne = s_ne;
   const int nk = kPol == kNearest ? ne : (ne < kRetCap ? ne : kRetCap);
@@ -1456,7 +1501,6 @@ __device__ __forceinline__ void dense_sweep_body(const Dev& d, int k, int w, int
   const bool dead = read_err(c) != 0;
   const Buckets bk = step_buckets<false>(d, par, step);
   const RetList rl{&s_ne, s_ent, s_ew1, s_ew2};
-  SweepAcc n = {0, 0, 0, 0, 0};
   const int slot = w * kThreads + tid;
   float x = 0.0f, y = 0.0f, z = 0.0f;
   uint32_t id = (uint32_t)slot;
@@ -1487,18 +1531,19 @@ __device__ __forceinline__ void dense_sweep_body(const Dev& d, int k, int w, int
   auto pair = [&](int lt, uint32_t idj, const float4& A, int sa) __attribute__((always_inline)) {
     const int sj = w * kThreads + lt;
     if (kPol == kRandom) {
-      retain(d, a, step, __float_as_int(A.w), sa, idj, sj, nullptr, n, rl);
+      retain(d, a, philox(step, (uint32_t)__float_as_int(A.w), idj, 0u, d.seed),
+             __float_as_int(A.w), sa, idj, sj, nullptr, s_cnt, rl);
       return;
     }
     const float r2 = dist2(d, s_pos[0][lt], s_pos[1][lt], s_pos[2][lt], A);
     if (kPol == kNearest)
-      near_pair(d, a, __float_as_int(A.w), sa, idj, r2, nullptr, n, &s_best[lt]);
+      near_pair(d, a, __float_as_int(A.w), sa, idj, r2, nullptr, s_cnt, &s_best[lt]);
     else
-      multi_pair(d, a, step, a.role[sj] & kMaskT, __float_as_int(A.w), sa, idj, sj, r2, nullptr, n,
+      multi_pair(d, a, step, a.role[sj] & kMaskT, __float_as_int(A.w), sa, idj, sj, r2, nullptr, s_cnt,
                  rl);
   };
   if (is_target) {
-    n.t_elig++;
+    count_one(&s_cnt[kOutTElig]);
     s_tid[tid] = (int32_t)id;
     if (kPol != kRandom) {
       s_pos[0][tid] = x;
@@ -1529,7 +1574,7 @@ __device__ __forceinline__ void dense_sweep_body(const Dev& d, int k, int w, int
     if (nc == 1) left &= 15u;
     auto hit = [&](const float4& A, uint32_t cell, uint32_t what) {
       if (!(dist2(d, x, y, z, A) < d.rc2)) return;
-      if (kPol != kMulti) n.in_rc++;
+      if (kPol != kMulti) count_one(&s_cnt[kOutInRc]);
       const int p = atomicAdd(&s_qn, 1);
       if (p < kDenseQ) {
         s_q[p] = make_uint2(cell, (uint32_t)tid | what);
@@ -1577,10 +1622,6 @@ __device__ __forceinline__ void dense_sweep_body(const Dev& d, int k, int w, int
   // clear the bucket counts of the next step's parity (as the other sweep)
   for (int q = w * kThreads + tid; q < d.ncell_clear; q += nwg * kThreads)
     pick(d.cnt, par ^ 1u)[q] = 0u;
-  wave_add(&s_cnt[kOutTElig], n.t_elig);
-  wave_add(&s_cnt[kOutInRc], n.in_rc);
-  wave_add(&s_cnt[kOutDrawn], n.drawn);
-  wave_add(&s_cnt[kOutExcl], n.excl);
   __syncthreads();
   const int ne = s_ne;
   const int nk = kPol == kNearest ? ne : (ne < kRetCap ? ne : kRetCap);
@@ -3250,6 +3291,11 @@ __global__ void k_advance(Ctl* c, int K) {
   if (threadIdx.x == 0 && blockIdx.x == 0) advance_ctl(c, K);
 }
 
+// The Dev argument (a kernel's first), see fresh.
+__device__ __forceinline__ const Dev& kernarg_dev() {
+  return fresh(*(const Dev*)__builtin_amdgcn_kernarg_segment_ptr());
+}
+
 // With fused binning there is no prep kernel: the closing groups of step
 // k - 1 trail the sweep of step k (workgroups nwg_sweep and up when k > 0).
 // Nothing the sweep reads or writes is theirs (the counters, staged bonds and
@@ -3259,7 +3305,7 @@ __global__ void k_advance(Ctl* c, int K) {
 // lengthening the resolve.
 template <int kPol, bool kTwo, bool kF, bool kNt = false>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
-    kPol == kNearest && kTwo && !kF ? 6 : 7))) void k_sweep(Dev d, int k) {
+    kPol == kNearest && !kF ? 6 : 7))) void k_sweep(Dev d, int k) {
   if (kF && (int)blockIdx.x >= d.nwg_sweep) {
     __shared__ uint32_t s_wave[kThreads / 64 + 1];
     const StepInfo si = step_info(d.ctl, k);
@@ -3267,7 +3313,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
                 (int)blockIdx.x - d.nwg_sweep, s_wave);
     return;
   }
-  sweep_body<kPol, kTwo, kF, kNt>(d, k, xcd_brick(blockIdx.x, d.nwg_sweep), d.nwg_sweep);
+  sweep_body<kPol, kTwo, kF, kNt>(kernarg_dev(), k, xcd_brick(blockIdx.x, d.nwg_sweep), d.nwg_sweep);
 }
 template <int kPol>
 __global__ __launch_bounds__(kThreads) void k_dense_sweep(Dev d, int k) {
@@ -3354,10 +3400,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
   const int4 m = uniform_map(map);
   const Dev& d = ds[m.x];
   if (k >= d.k_limit || d.rule.policy != PR_POLICY_RANDOM) return;
-  sweep_body<kRandom, kTwo, kF>(d, k, m.y, m.z);
+  sweep_body<kRandom, kTwo, kF>(fresh(d), k, m.y, m.z);
 }
 template <bool kTwo>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kTwo ? 6 : 7))) void k_near_sweep_b(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_near_sweep_b(
     const Dev* __restrict__ ds, const int4* __restrict__ map, int k) {
   const int4 m = uniform_map(map);
   const Dev& d = ds[m.x];
