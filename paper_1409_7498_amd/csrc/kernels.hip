@@ -286,20 +286,23 @@ __device__ __forceinline__ void wave_sync() {
 // Exclusive prefix sum over the workgroup (wavefront scans, then the
 // wavefront totals through LDS, read by every thread).  Every thread of the
 // block must call it, with every lane active.
+template <int kT = kThreads, bool kReuse = true>
 __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* s_wave,
                                                     uint32_t& total) {
-  const int lane = __lane_id(), w = threadIdx.x / 64, nw = blockDim.x / 64;
+  constexpr int nw = kT / 64;
+  const int lane = __lane_id(), w = threadIdx.x / 64;
   const uint32_t x = wave_scan_incl(v);
   if (lane == 63) s_wave[w] = x;
   __syncthreads();
   uint32_t below = 0, all = 0;
+#pragma unroll
   for (int i = 0; i < nw; ++i) {
     const uint32_t t = s_wave[i];
     below += i < w ? t : 0u;
     all += t;
   }
   total = all;
-  __syncthreads();  // s_wave is free for the next call
+  if (kReuse) __syncthreads();  // s_wave is free for the next call
   return below + x - v;
 }
 
@@ -951,11 +954,16 @@ __device__ __forceinline__ void multi_pair(const Dev& d, const Arr& a, uint32_t 
 // from the queue.  The four runs of two x-adjacent cells are one sequence: a
 // word D counts down in each of its bytes to the ends of the runs, the sign
 // bits of the bytes say which runs are not yet done, and their dot product with
-// the (byte) steps between the runs moves the index.  Bound: VALU issue of the
-// trips of a wavefront's longest block, 16 instructions each instead of 24 (one
-// compare and select per run, FP32 distance), 30 in a region that wraps in one
-// axis and 42 beyond.  1,048,576 particles, 256 steps with load and read-out:
-// 7.90 -> 7.80 ms.
+// the (byte) steps between the runs moves the index.  These words are the same
+// for every T of a block: the staging writes them once per block (s_blk, while
+// the records are on their way), instead of each T from eight cell offsets.
+// Bound: VALU issue, of the trips of a wavefront's longest block (14 instructions
+// each instead of 24 with one compare and select per run and FP32 distance, 30
+// in a region that wraps in one axis and 42 beyond) and of what comes before
+// them.  1,048,576 particles, 256 steps with load and read-out: 7.90 -> 7.80 ms
+// by the integer test, 7.54 -> 7.42 by the words of the block and a bit per
+// place for the hits; 4,194,304 (chain growth, blocks nearly empty), 128 steps:
+// 8.28 -> 8.09 by the latter.
 // ---------------------------------------------------------------------------
 typedef short short2_t __attribute__((ext_vector_type(2)));
 
@@ -974,40 +982,54 @@ __device__ __forceinline__ uint32_t quant_d2(uint2 a, uint2 b) {
   return (uint32_t)__builtin_amdgcn_sdot2(dz, dz, __builtin_amdgcn_sdot2(dxy, dxy, 0, false), false);
 }
 
-// Candidates of the T at t among the staged records (s_qr) of its block, whose
-// first region cell is l0 (ex cells per row, exy per layer; s_off: first record
-// of each region cell): nh counts them, hits keeps the last four, one byte
-// each.
-__device__ __forceinline__ void scan_block(const uint2* s_qr, const uint16_t* s_off, int l0, int ex,
-                                           int exy, uint2 t, uint32_t thr, int& nh,
-                                           uint32_t& hits) {
-  // runs (dy, dz) = (0,0), (1,0), (0,1), (1,1): two cells each
-  const int l1 = l0 + ex, l2 = l0 + exy, l3 = l2 + ex;
-  const int b0 = (int)s_off[l0], b1 = (int)s_off[l1], b2 = (int)s_off[l2], b3 = (int)s_off[l3];
-  const int p1 = (int)s_off[l0 + 2] - b0;
+// A block (first region cell l, ex cells per row, exy per layer; s_off: first
+// record of each region cell) as the scan takes it: x the word D, y the steps
+// between its runs (dy, dz) = (0,0), (1,0), (0,1), (1,1) of two cells each, and in
+// the last byte minus what the index starts from.
+__device__ __forceinline__ uint2 scan_entry(const uint16_t* s_off, int l, int ex, int exy) {
+  static_assert(8 * kCellCap <= 127, "no borrow from byte to byte of D");
+  const int l1 = l + ex, l2 = l + exy, l3 = l2 + ex;
+  const int b0 = (int)s_off[l], b1 = (int)s_off[l1], b2 = (int)s_off[l2], b3 = (int)s_off[l3];
+  const int p1 = (int)s_off[l + 2] - b0;
   const int p2 = p1 + (int)s_off[l1 + 2] - b1;
   const int p3 = p2 + (int)s_off[l2 + 2] - b2;
   const int tot = p3 + (int)s_off[l3 + 2] - b3;
-  static_assert(8 * kCellCap <= 127, "no borrow from byte to byte of D");
   // record of place q: q + o3, plus (o2 - o3) while q < p3, (o1 - o2) while q
   // < p2 and (o0 - o1) while q < p1 (o: the run's first record less its place)
   const int o1 = b1 - p1, o2 = b2 - p2, o3 = b3 - p3;
-  uint32_t D = ((uint32_t)p1 | ((uint32_t)p2 << 8) | ((uint32_t)p3 << 16) | ((uint32_t)tot << 24)) +
-               0x7F7F7F7Fu;
+  const uint32_t D =
+      ((uint32_t)p1 | ((uint32_t)p2 << 8) | ((uint32_t)p3 << 16) | ((uint32_t)tot << 24)) +
+      0x7F7F7F7Fu;
   // bytes -(step) mod 256: a set sign byte counts -128
   const uint32_t step = ((uint32_t)(o1 - b0) & 0xFFu) | (((uint32_t)(o2 - o1) & 0xFFu) << 8) |
-                        (((uint32_t)(o3 - o2) & 0xFFu) << 16);
-  int acc = o3 << 7;  // 128 x the index, of which bits 7..14 count
-  while ((int32_t)D < 0) {  // the last byte: places left
-    const uint32_t v =
-        (uint32_t)__builtin_amdgcn_sdot4((int)(D & 0x80808080u), (int)step, acc, false);
-    const uint32_t r = (v >> 7) & 0xFFu;
-    const bool in = quant_d2(s_qr[r], t) < thr;
-    hits = in ? (hits << 8) | r : hits;
-    nh += in ? 1 : 0;
-    D -= 0x01010101u;
-    acc += 128;
+                        (((uint32_t)(o3 - o2) & 0xFFu) << 16) | ((uint32_t)-o3 << 24);
+  return make_uint2(D, step);
+}
+constexpr uint32_t kScanMax = 32;  // records of a block the scan's mask holds
+
+// The staged record of place q (a block's word less q in every byte, q << 7).
+__device__ __forceinline__ uint32_t scan_index(uint32_t D, uint32_t step, uint32_t q7) {
+  return ((uint32_t)__builtin_amdgcn_sdot4((int)(D & 0x80808080u), (int)step, (int)q7, false) >>
+          7) & 0xFFu;
+}
+
+// Candidates of the T at t among the staged records (s_qr) of block e (at most
+// kScanMax records): a bit each, the last place's the lowest.
+__device__ __forceinline__ uint32_t scan_block(const uint2* s_qr, uint2 e, uint2 t, uint32_t thr) {
+  uint32_t m = 0, q7 = 0;
+  while ((int32_t)e.x < 0) {  // the last byte: places left
+    const uint32_t r = scan_index(e.x, e.y, q7);
+    m = m + m + (quant_d2(s_qr[r], t) < thr ? 1u : 0u);
+    e.x -= 0x01010101u;
+    q7 += 128u;
   }
+  return m;
+}
+
+// The staged record of a bit of scan_block's mask.
+__device__ __forceinline__ uint32_t scan_record(uint2 e, uint32_t bit) {
+  const uint32_t q = (e.x >> 24) - 0x80u - bit;
+  return scan_index(e.x - q * 0x01010101u, e.y, q << 7);
 }
 
 // The selection a sweep is compiled for.
@@ -1022,16 +1044,16 @@ __device__ __forceinline__ bool pol_t(int role) {
 // ---------------------------------------------------------------------------
 // k_sweep: every particle is re-jittered (resident systems) and written to
 // the other position buffer; T's test the step's A records at their new
-// positions.  Sorted storage: one workgroup per brick, the A records
-// of the brick and its halo (positions, ids, slots, adjacency rows) staged in
-// LDS, each region cell's by the thread that read its count, and the brick's
-// particles handled kTPass at a time.  A T whose 2x2x2 cell block lies in the staged region scans it as four
-// runs of two x-adjacent cells (contiguous in LDS) and keeps up to four
-// in-range pairs in registers (one byte each); the wavefront then reserves
-// queue slots for all of them at once (ballot and mbcnt over the per-lane
-// counts) and the queue is drawn on full wavefronts after the pass.  Every
-// other T is deferred to a list and scanned again after the queue: T's with
-// more in-range pairs than the registers hold, or whose pairs find the queue
+// positions.  Sorted storage: one workgroup per brick (or share of one), the A
+// records of the brick and its halo (positions, ids, slots, adjacency rows)
+// staged in LDS, each region cell's by the thread that read its count, and the
+// brick's particles handled kTPass at a time.  A T whose 2x2x2 cell block lies in
+// the staged region scans it for candidates (scan_block); the wavefront then
+// reserves queue slots for all of them at once (ballot and mbcnt over the
+// per-lane counts), and the queue takes the exact test and the draws on full
+// wavefronts after the pass.  Every other T is deferred to a list and scanned
+// again after the queue: T's with more than four candidates, of a block with
+// more records than the scan's mask holds, or whose pairs find the queue
 // full, in the staged records; in the global buckets particles that drifted
 // out of the staged region since the last sort, bricks whose region holds
 // more than kStageRecs records and steps with bucket overflow.  A deferred T
@@ -1092,7 +1114,12 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
   __shared__ int4 s_radj[kStageRecs];
   __shared__ int32_t s_rsa[kStageRecs];
   __shared__ uint16_t s_off[kCells + 1];  // first record of a region cell
-  __shared__ uint32_t s_q[kQueue];  // queued pair: local T | staged record << 16
+  // the 2x2x2 block from each region cell on that has one (scan_entry)
+  constexpr int kEdge = kTwo ? kMaxBrick + 2 : kOneCellBrick + 2;
+  __shared__ uint2 s_blk[(kEdge - 1) * kEdge * kEdge - kEdge - 1];
+  // queued candidate: local T | its block << 10 | bit of the scan's mask << 20
+  __shared__ uint32_t s_q[kQueue];
+  static_assert(kTP <= 1024 && kCells <= 1024 && kScanMax <= 32, "fields of a queued candidate");
   __shared__ int32_t s_tid[kTP];    // ids of the pass's T's
   __shared__ uint16_t s_def[kTP];            // deferred T's (local index in the pass)
   __shared__ int4 s_ent[kRetCap];  // retained pairs; nearest selection: the A's as (id, slot)
@@ -1173,43 +1200,52 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
   mine = mine < (uint32_t)kCellCap ? mine : (uint32_t)kCellCap;
   mine2 = mine2 < (uint32_t)kCellCap ? mine2 : (uint32_t)kCellCap;
   uint32_t total = 0;
-  const uint32_t off = block_scan_excl(mine + mine2, s_wave, total);
+  const uint32_t off = block_scan_excl<kThreads, false>(mine + mine2, s_wave, total);
   staged = total <= (uint32_t)kStageRecs && bk.novf == 0;
   // each thread stages the records of its own region cells: the first
   // kFirst of a cell loaded together, the rare rest one after another
   constexpr int kFirst = kTwo ? 2 : 4;
-#pragma unroll
-  for (int h = 0; h < (kTwo ? 2 : 1); ++h) {
-    const int cl = kTwo ? 2 * tid + h : tid;
-    const uint32_t o = h ? off + mine : off, m = h ? mine2 : mine;
-    if (cl < ncs) {
-      s_off[cl] = (uint16_t)o;
-      if (staged) {
-        // rank r of a cell lies r * ncell records further
-        const size_t r0 = (size_t)(h ? gc2 : gc), nn = (size_t)d.ncell;
-        // the first records in registers (named, so that none of them
-        // lives in scratch), loaded together, then written to LDS
-        float4 rv0 = make_float4(0.f, 0.f, 0.f, 0.f), rv1 = rv0, rv2 = rv0, rv3 = rv0;
-        int32_t sv0 = 0, sv1 = 0, sv2 = 0, sv3 = 0;
-        if (m > 0u) { rv0 = bk.rec[r0]; sv0 = bk.sa[r0]; }
-        if (m > 1u) { rv1 = bk.rec[r0 + nn]; sv1 = bk.sa[r0 + nn]; }
-        if (kFirst > 2 && m > 2u) { rv2 = bk.rec[r0 + 2 * nn]; sv2 = bk.sa[r0 + 2 * nn]; }
-        if (kFirst > 3 && m > 3u) { rv3 = bk.rec[r0 + 3 * nn]; sv3 = bk.sa[r0 + 3 * nn]; }
-        if (m > 0u) { put_rec(o, rv0); s_rsa[o] = sv0; }
-        if (m > 1u) { put_rec(o + 1, rv1); s_rsa[o + 1] = sv1; }
-        if (kFirst > 2 && m > 2u) { put_rec(o + 2, rv2); s_rsa[o + 2] = sv2; }
-        if (kFirst > 3 && m > 3u) { put_rec(o + 3, rv3); s_rsa[o + 3] = sv3; }
-        if (!kF && d.adj_staged)
-          for (uint32_t j = 0; j < m && j < (uint32_t)kFirst; ++j) s_radj[o + j] = d.radj[r0 + j * nn];
-        for (uint32_t j = kFirst; j < m; ++j) {
-          put_rec(o + j, bk.rec[r0 + j * nn]);
-          s_rsa[o + j] = bk.sa[r0 + j * nn];
-          if (!kF && d.adj_staged) s_radj[o + j] = d.radj[r0 + j * nn];
-        }
-      }
+  const int cl0 = kTwo ? 2 * tid : tid;
+  const size_t nn = (size_t)d.ncell;  // rank r of a cell lies r * ncell records further
+  // the first records in registers (named, so that none of them lives in
+  // scratch), loaded together, then written to LDS
+  float4 rv0 = make_float4(0.f, 0.f, 0.f, 0.f), rv1 = rv0, rv2 = rv0, rv3 = rv0;
+  int32_t sv0 = 0, sv1 = 0, sv2 = 0, sv3 = 0;
+  auto rec_load = [&](size_t r0, uint32_t m) {
+    if (m > 0u) { rv0 = bk.rec[r0]; sv0 = bk.sa[r0]; }
+    if (m > 1u) { rv1 = bk.rec[r0 + nn]; sv1 = bk.sa[r0 + nn]; }
+    if (kFirst > 2 && m > 2u) { rv2 = bk.rec[r0 + 2 * nn]; sv2 = bk.sa[r0 + 2 * nn]; }
+    if (kFirst > 3 && m > 3u) { rv3 = bk.rec[r0 + 3 * nn]; sv3 = bk.sa[r0 + 3 * nn]; }
+  };
+  auto rec_put = [&](size_t r0, uint32_t o, uint32_t m) {
+    if (m > 0u) { put_rec(o, rv0); s_rsa[o] = sv0; }
+    if (m > 1u) { put_rec(o + 1, rv1); s_rsa[o + 1] = sv1; }
+    if (kFirst > 2 && m > 2u) { put_rec(o + 2, rv2); s_rsa[o + 2] = sv2; }
+    if (kFirst > 3 && m > 3u) { put_rec(o + 3, rv3); s_rsa[o + 3] = sv3; }
+    if (!kF && d.adj_staged)
+      for (uint32_t j = 0; j < m && j < (uint32_t)kFirst; ++j) s_radj[o + j] = d.radj[r0 + j * nn];
+    for (uint32_t j = kFirst; j < m; ++j) {
+      put_rec(o + j, bk.rec[r0 + j * nn]);
+      s_rsa[o + j] = bk.sa[r0 + j * nn];
+      if (!kF && d.adj_staged) s_radj[o + j] = d.radj[r0 + j * nn];
     }
-  }
+  };
+  if (cl0 < ncs) s_off[cl0] = (uint16_t)off;
+  if (kTwo && cl0 + 1 < ncs) s_off[cl0 + 1] = (uint16_t)(off + mine);
   if (tid == 0) s_off[ncs] = (uint16_t)total;
+  if (!staged) mine = mine2 = 0;
+  rec_load((size_t)gc, mine);
+  if (kTwo) {
+    rec_put((size_t)gc, off, mine);
+    rec_load((size_t)gc2, mine2);
+  }
+  __syncthreads();
+  // the blocks (the last one's far corner is the region's last cell)
+#pragma unroll
+  for (int h = 0; h < (kTwo ? 2 : 1); ++h)
+    if (cl0 + h + ex * ey + ex + 2 <= ncs) s_blk[cl0 + h] = scan_entry(s_off, cl0 + h, ex, ex * ey);
+  if (kTwo) rec_put((size_t)gc2, off + mine, mine2);
+  else rec_put((size_t)gc, off, mine);
   __syncthreads();
   const bool dead = s_dead != 0;
   // the workgroup-uniform switches of the pass loop, one scalar register
@@ -1268,10 +1304,8 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
       }
       if (kPol == kNearest)
         near_list(slot < s1 && cur.role == kRoleA, cur.id, slot, (int2*)s_ent, &s_ne);
-      // candidates among the staged records: nh counts them all, hits keeps the
-      // first four, one byte each (a T with more is deferred)
-      int nh = 0;
-      uint32_t hits = 0;
+      // candidates among the staged records (a T with more than four is deferred)
+      uint32_t hits = 0, blk = 0;
       bool defer = false;
       if (slot < s1 && pol_t<kPol>(cur.role)) {
         defer = true;
@@ -1286,19 +1320,24 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
           if ((uint32_t)lx0 < (uint32_t)(ex - 1) && (uint32_t)ly0 < (uint32_t)(ey - 1) &&
               (uint32_t)lz0 < (uint32_t)(ez - 1)) {
             const int l0 = (int)__umul24(__umul24(lz0, ey) + ly0, ex) + lx0;  // small operands
-            scan_block(s_qr, s_off, l0, ex, ex * ey, quant(d, px, py, pz), d.qthr, nh, hits);
-            defer = nh > 4;
+            const uint2 e = s_blk[l0];
+            if (e.x < (0x80u + kScanMax) << 24) {
+              hits = scan_block(s_qr, e, quant(d, px, py, pz), d.qthr);
+              blk = (uint32_t)l0;
+              defer = __popc(hits) > 4;
+            }
           }
         }
       }
-      if (defer) nh = 0;
+      const int nh = defer ? 0 : __popc(hits);
       // queue slots for the wavefront's held pairs: lane j's pairs go after
       // those of the lower lanes (counts from four ballots)
-      const unsigned long long g1 = __ballot(nh >= 1), g2 = __ballot(nh >= 2),
-                               g3 = __ballot(nh >= 3), g4 = __ballot(nh >= 4);
-      const uint32_t wtot =
-          (uint32_t)(__popcll(g1) + __popcll(g2) + __popcll(g3) + __popcll(g4));
-      if (wtot) {
+      const unsigned long long g1 = __ballot(nh >= 1);
+      if (g1) {
+        const unsigned long long g2 = __ballot(nh >= 2), g3 = __ballot(nh >= 3),
+                                 g4 = __ballot(nh >= 4);
+        const uint32_t wtot =
+            (uint32_t)(__popcll(g1) + __popcll(g2) + __popcll(g3) + __popcll(g4));
         uint32_t qb = 0;
         if (__lane_id() == 0) qb = (uint32_t)atomicAdd(&s_qn, (int)wtot);
         qb = (uint32_t)__builtin_amdgcn_readlane((int)qb, 0);
@@ -1306,8 +1345,10 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
             qb + lanes_below(g1) + lanes_below(g2) + lanes_below(g3) + lanes_below(g4);
         if (nh > 0) {
           if (p + (uint32_t)nh <= (uint32_t)kQueue) {
-            for (int j = 0; j < nh; ++j)
-              s_q[p + j] = (uint32_t)lt | (((hits >> (8 * j)) & 0xFFu) << 16);
+            for (int j = 0; j < nh; ++j) {
+              s_q[p + j] = (uint32_t)lt | (blk << 10) | ((uint32_t)(__ffs((int)hits) - 1) << 20);
+              hits &= hits - 1u;
+            }
           } else {
             // the pairs do not all fit: the T is deferred and the slots it
             // reserved below kQueue are marked empty
@@ -1327,7 +1368,7 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
     for (int e = tid; e < qn; e += kThreads) {
       const uint32_t q = s_q[e];
       if (q == kQEmpty) continue;
-      const uint32_t lt = q & 0xFFFFu, r = q >> 16;
+      const uint32_t lt = q & 1023u, r = scan_record(s_blk[(q >> 10) & 1023u], q >> 20);
       const uint32_t idj = (uint32_t)s_tid[lt];
       const int sj = base + (int)lt;
       const int4* arow = d.adj_staged && !kF ? &s_radj[r] : nullptr;
@@ -3029,7 +3070,7 @@ __global__ __launch_bounds__(kFinThreads) void k_log_segs(Dev d, int K, uint32_t
       for (int g = 0; g < d.ngroups; ++g) v += (uint32_t)p[g * kPart];
     }
     uint32_t total = 0;
-    const uint32_t ex = block_scan_excl(v, s_wave, total);
+    const uint32_t ex = block_scan_excl<kFinThreads>(v, s_wave, total);
     if (k < K) seg[k] = carry + ex;
     carry += total;
     if (v) atomicMax(&s_most, v);
@@ -3166,7 +3207,7 @@ __device__ __forceinline__ void sort_scan_body(const Dev& d) {
     const int b = base + threadIdx.x;
     const uint32_t v = b < d.nbricks ? d.bcnt[b] : 0u;
     uint32_t total = 0;
-    const uint32_t ex = block_scan_excl(v, s_wave, total);
+    const uint32_t ex = block_scan_excl<kFinThreads>(v, s_wave, total);
     if (b < d.nbricks) {
       d.bstart[b] = (int32_t)(carry + ex);
       d.bcnt[b] = 0u;
@@ -3305,7 +3346,7 @@ __device__ __forceinline__ const Dev& kernarg_dev() {
 // lengthening the resolve.
 template <int kPol, bool kTwo, bool kF, bool kNt = false>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
-    kPol == kNearest && !kF ? 6 : 7))) void k_sweep(Dev d, int k) {
+    kPol == kNearest ? (kF ? (kTwo ? 6 : 7) : (kTwo ? 5 : 6)) : 7))) void k_sweep(Dev d, int k) {
   if (kF && (int)blockIdx.x >= d.nwg_sweep) {
     __shared__ uint32_t s_wave[kThreads / 64 + 1];
     const StepInfo si = step_info(d.ctl, k);
@@ -3403,12 +3444,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7))) v
   sweep_body<kRandom, kTwo, kF>(fresh(d), k, m.y, m.z);
 }
 template <bool kTwo>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_near_sweep_b(
-    const Dev* __restrict__ ds, const int4* __restrict__ map, int k) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
+    kTwo ? 5 : 6))) void k_near_sweep_b(const Dev* __restrict__ ds,
+                                                 const int4* __restrict__ map, int k) {
   const int4 m = uniform_map(map);
   const Dev& d = ds[m.x];
   if (k >= d.k_limit || d.rule.policy != PR_POLICY_NEAREST) return;
-  sweep_body<kNearest, kTwo>(d, k, m.y, m.z);
+  sweep_body<kNearest, kTwo>(fresh(d), k, m.y, m.z);
 }
 // four sweep workgroups' slots per workgroup (the resolve's map)
 __global__ __launch_bounds__(kThreads) void k_near_resolve_b(const Dev* __restrict__ ds,

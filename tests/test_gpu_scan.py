@@ -64,7 +64,7 @@ def test_pairs_at_the_cutoff(rel, scale, policy):
 
 
 @pytest.mark.parametrize("policy", ["random", "nearest"])
-@pytest.mark.parametrize("per_cell", [8, 7, 3])
+@pytest.mark.parametrize("per_cell", [8, 7, 5, 4, 3])
 def test_crowded_blocks(per_cell, policy):
     # 12^3 cells of width 2.5; A's in one 3x3x3 group of them only, per_cell in each
     L, w, rng = 30.0, 2.5, np.random.default_rng(per_cell)
