@@ -1390,71 +1390,78 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
       else
         multi_pair(d, a, step, a.role[sj] & kMaskT, ida, sa, idj, sj, r2, arow, s_cnt, rl);
     }
-    // the deferred T's, re-jittered again from the previous positions: in the
-    // staged records when the block lies in a staged region (T's with more
-    // pairs than the registers hold, or whose pairs found the queue full),
-    // else in the buckets (cells 0-7 of the block, then the overflow list)
+    // the deferred T's, eight lanes each, one cell of the block per lane: from
+    // the staged records when the block lies in a staged region, else from the
+    // buckets and the overflow list (a lane's count and its first two records
+    // in flight together).  They are few, and what bounds them is latency, at
+    // the end of the last workgroups with nothing left to hide it: one lane each
+    // walked the cells one after another, up to 5 us (1,048,576 particles, 256
+    // steps with load and read-out 7.45 ms, this 7.07; 262,144 with 60% A's, no
+    // brick staged, 1667 and 1399 us per step).  From the last thread down: the
+    // first wavefronts have the queue.
     const int ndef = s_ndef;
-    for (int e = tid; e < ndef; e += kThreads) {
-      const int lt = (int)s_def[e], slot = base + lt;
-      float px = X[slot], py = Y[slot], pz = Z[slot];
-      const uint32_t idj = a.id ? (uint32_t)a.id[slot] : (uint32_t)slot;
-      if (jit) rejitter(d, step, idj, px, py, pz);
+    for (int e = (kThreads - 1 - tid) >> 3; e < ndef; e += kThreads / 8) {
+      const int lt = (int)s_def[e], slot = base + lt, sub = tid & 7;
+      const float px = d.jitter ? XW[slot] : X[slot], py = d.jitter ? YW[slot] : Y[slot],
+                  pz = d.jitter ? ZW[slot] : Z[slot];
+      const uint32_t idj = (uint32_t)a.id[slot];
       const uint32_t rt = kPol == kMulti ? a.role[slot] & kMaskT : 0u;
-      auto pair = [&](const float4& A, int sa, const int4* arow) __attribute__((always_inline)) {
+      const int lx0 = local_lo(px, d.inv_w, bx, nc), ly0 = local_lo(py, d.inv_w, by, nc),
+                lz0 = local_lo(pz, d.inv_w, bz, nc);
+      const bool in = staged && (uint32_t)lx0 < (uint32_t)(ex - 1) &&
+                      (uint32_t)ly0 < (uint32_t)(ey - 1) && (uint32_t)lz0 < (uint32_t)(ez - 1);
+      int q = 0;  // the lane's cell: its first staged record, or the cell
+      uint32_t nr = 0, no = 0;
+      float4 A0 = make_float4(0.f, 0.f, 0.f, 0.f), A1 = A0;
+      int32_t sa0 = 0, sa1 = 0;
+      const size_t nn = (size_t)d.ncell;
+      if (in) {
+        const int lr = ((lz0 + (sub >> 2)) * ey + ly0 + ((sub >> 1) & 1)) * ex + lx0 + (sub & 1);
+        q = (int)s_off[lr];
+        nr = (uint32_t)s_off[lr + 1] - (uint32_t)q;
+      } else {
+        int cx0, cx1, cy0, cy1, cz0, cz1;
+        lo_hi(px, d.inv_w, nc, cx0, cx1);
+        lo_hi(py, d.inv_w, nc, cy0, cy1);
+        lo_hi(pz, d.inv_w, nc, cz0, cz1);
+        q = (((sub & 4) ? cz1 : cz0) * nc + ((sub & 2) ? cy1 : cy0)) * nc + ((sub & 1) ? cx1 : cx0);
+        nr = bk.cnt[q];
+        A0 = bk.rec[q];
+        A1 = bk.rec[q + nn];
+        sa0 = bk.sa[q];
+        sa1 = bk.sa[q + nn];
+        nr = nr < (uint32_t)kCellCap ? nr : (uint32_t)kCellCap;
+        if (nc == 1 && sub) nr = 0;  // one cell, not eight
+        no = (bk.novf + 7u - (uint32_t)sub) >> 3;
+      }
+      for (uint32_t r = 0; r < nr + no; ++r) {
+        float4 A = A0;
+        int32_t sa = sa0;
+        if (in) {
+          A = s_rec[q + r];
+          sa = s_rsa[q + r];
+        } else if (r >= nr) {
+          A = bk.ovf[(r - nr) * 8u + (uint32_t)sub];
+          sa = bk.osa[(r - nr) * 8u + (uint32_t)sub];
+        } else if (r == 1u) {
+          A = A1;
+          sa = sa1;
+        } else if (r > 1u) {
+          A = bk.rec[q + r * nn];
+          sa = bk.sa[q + r * nn];
+        }
         const float r2 = dist2(d, px, py, pz, A);
-        if (!(r2 < d.rc2)) return;
+        if (!(r2 < d.rc2)) continue;
+        const int4* arow = in && d.adj_staged && !kF ? &s_radj[q + r] : nullptr;
+        const int ida = __float_as_int(A.w);
         if (kPol != kMulti) count_one(&s_cnt[kOutInRc]);
         if (kPol == kRandom)
-          retain(d, a, philox(step, (uint32_t)__float_as_int(A.w), idj, 0u, d.seed),
-                 __float_as_int(A.w), sa, idj, slot, arow, s_cnt, rl);
+          retain(d, a, philox(step, (uint32_t)ida, idj, 0u, d.seed), ida, sa, idj, slot, arow,
+                 s_cnt, rl);
         else if (kPol == kNearest)
-          near_pair(d, a, __float_as_int(A.w), sa, idj, r2, arow, s_cnt, &s_best[lt]);
+          near_pair(d, a, ida, sa, idj, r2, arow, s_cnt, &s_best[lt]);
         else
-          multi_pair(d, a, step, rt, __float_as_int(A.w), sa, idj, slot, r2, arow, s_cnt, rl);
-      };
-      if (staged) {
-        const int lx0 = local_lo(px, d.inv_w, bx, nc), ly0 = local_lo(py, d.inv_w, by, nc),
-                  lz0 = local_lo(pz, d.inv_w, bz, nc);
-        if ((uint32_t)lx0 < (uint32_t)(ex - 1) && (uint32_t)ly0 < (uint32_t)(ey - 1) &&
-            (uint32_t)lz0 < (uint32_t)(ez - 1)) {
-          const int l0 = (lz0 * ey + ly0) * ex + lx0;
-#pragma unroll 1
-          for (int run = 0; run < 4; ++run) {
-            const int lr = l0 + ((run & 1) ? ex : 0) + ((run & 2) ? ex * ey : 0);
-            const int r1 = (int)s_off[lr + 2];
-            for (int r = (int)s_off[lr]; r < r1; ++r)
-              pair(s_rec[r], s_rsa[r], d.adj_staged && !kF ? &s_radj[r] : nullptr);
-          }
-          continue;
-        }
-      }
-      int cx0, cx1, cy0, cy1, cz0, cz1;
-      lo_hi(px, d.inv_w, nc, cx0, cx1);
-      lo_hi(py, d.inv_w, nc, cy0, cy1);
-      lo_hi(pz, d.inv_w, nc, cz0, cz1);
-      const int m = nc > 1 ? 2 : 1;
-      for (int q = 0; q < 9; ++q) {
-        const float4* rp;
-        const int32_t* sp;
-        size_t rstep;
-        uint32_t nr;
-        if (q < 8) {
-          const int ia = q >> 2, ib = (q >> 1) & 1, ie = q & 1;
-          if (ia >= m || ib >= m || ie >= m) continue;
-          const int cc = ((ia ? cz1 : cz0) * nc + (ib ? cy1 : cy0)) * nc + (ie ? cx1 : cx0);
-          nr = bk.cnt[cc];
-          nr = nr < (uint32_t)kCellCap ? nr : (uint32_t)kCellCap;
-          rp = bk.rec + cc;
-          sp = bk.sa + cc;
-          rstep = (size_t)d.ncell;
-        } else {
-          nr = bk.novf;
-          rp = bk.ovf;
-          sp = bk.osa;
-          rstep = 1;
-        }
-        for (uint32_t r = 0; r < nr; ++r) pair(rp[r * rstep], sp[r * rstep], nullptr);
+          multi_pair(d, a, step, rt, ida, sa, idj, slot, r2, arow, s_cnt, rl);
       }
     }
     __syncthreads();
