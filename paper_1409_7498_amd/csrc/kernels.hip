@@ -784,15 +784,20 @@ struct RetList {
   uint32_t *w1, *w2;  // w1: several rules only
 };
 
-// Whether v is in the adjacency row of width B at `row` (rows of width <=
-// kAdjStage: every entry loaded at once).
-__device__ __forceinline__ bool row_has_wide(const int32_t* row, int B, int32_t v) {
-  if (B > kAdjStage) return row_has(row, B, v);
+// The adjacency row of width B <= kAdjStage at `row`, every entry loaded at once.
+__device__ __forceinline__ int4 row_load(const int32_t* row, int B) {
   int4 r = make_int4(-1, -1, -1, -1);
   r.x = row[0];
   if (B > 1) r.y = row[1];
   if (B > 2) r.z = row[2];
   if (B > 3) r.w = row[3];
+  return r;
+}
+
+// Whether v is in the adjacency row of width B at `row`.
+__device__ __forceinline__ bool row_has_wide(const int32_t* row, int B, int32_t v) {
+  if (B > kAdjStage) return row_has(row, B, v);
+  const int4 r = row_load(row, B);
   return r.x == v || r.y == v || r.z == v || r.w == v;
 }
 
@@ -828,16 +833,16 @@ __device__ __forceinline__ void retain(const Dev& d, const Arr& a, W4 r, int ida
 // in-range pair that is not excluded as bonded lowers the A's key (r2 bits,
 // id_T) and its T's (r2 bits, id_A), the T's in LDS (r2 >= 0 orders like its
 // bits, equal distances go to the lower id).
-__device__ __forceinline__ void near_pair(const Dev& d, const Arr& a, int ida, int sa, uint32_t idj,
-                                          float r2, const int4* arow, int* cnt,
-                                          unsigned long long* best) {
-  if (d.rule.exclude && pair_bonded(d, a, sa, idj, arow)) {
+__device__ __forceinline__ void near_pair(int ida, uint32_t idj, float r2, bool excluded, int* cnt,
+                                          unsigned long long* best_a,
+                                          unsigned long long* best_t) {
+  if (excluded) {
     count_one(&cnt[kOutExcl]);
     return;
   }
   const unsigned long long rb = (unsigned long long)__float_as_uint(r2) << 32;
-  atomicMin(&d.slotA[ida], rb | idj);
-  atomicMin(best, rb | (uint32_t)ida);
+  atomicMin(best_a, rb | idj);
+  atomicMin(best_t, rb | (uint32_t)ida);
 }
 
 // The A's of a nearest sweep's workgroup, (id, slot) of the first kNearList of
@@ -1120,18 +1125,23 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
   // queued candidate: local T | its block << 10 | bit of the scan's mask << 20
   __shared__ uint32_t s_q[kQueue];
   static_assert(kTP <= 1024 && kCells <= 1024 && kScanMax <= 32, "fields of a queued candidate");
-  __shared__ int32_t s_tid[kTP];    // ids of the pass's T's
+  // ids of the pass's T's (nearest selection: read again with the position)
+  __shared__ int32_t s_tid[kPol == kNearest ? 1 : kTP];
   __shared__ uint16_t s_def[kTP];            // deferred T's (local index in the pass)
   __shared__ int4 s_ent[kRetCap];  // retained pairs; nearest selection: the A's as (id, slot)
   __shared__ uint32_t s_ew1[kPol == kMulti ? kRetCap : 1], s_ew2[kPol == kNearest ? 1 : kRetCap];
-  __shared__ unsigned long long s_best[kPol == kNearest ? kTP : 1];  // per T of the pass
+  // nearest selection: the best key of each T of the pass, of each staged A
+  __shared__ unsigned long long s_best[kPol == kNearest ? kTP : 1];
+  __shared__ unsigned long long s_best_a[kPol == kNearest ? kStageRecs : 1];
   __shared__ uint32_t s_wave[kThreads / 64 + 1];
   __shared__ int s_cnt[5];
   __shared__ int s_qn, s_ndef, s_ne, s_dead;
   const int tid = threadIdx.x;
   if (tid < 5) s_cnt[tid] = 0;
-  if (kPol == kNearest)
+  if (kPol == kNearest) {
     for (int q = tid; q < kTP; q += kThreads) s_best[q] = kEmpty;
+    for (int q = tid; q < kStageRecs; q += kThreads) s_best_a[q] = kEmpty;
+  }
   if (tid == 0) {
     s_qn = 0;
     s_ndef = 0;
@@ -1257,6 +1267,8 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
   int t_elig = 0, a_elig = 0;  // of the wavefront
   for (int base = s0; base < s1 && !dead; base += kTP) {
     if (base != s0) cur = load_part(a, X, Y, Z, base + tid, s1);
+    int id_0 = 0, id_1 = 0, id_2 = 0;  // nearest selection: ids of the thread's particles
+    static_assert(kPer == 3, "id_0, id_1, id_2");
 #pragma unroll 1
     for (int u = 0; u < kPer; ++u) {
       const Dev& d = fresh(d0);
@@ -1277,6 +1289,11 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
       Part nxt = cur;
       if (u + 1 < kPer) nxt = load_part(a, X, Y, Z, slot + kThreads, s1);
       const uint32_t idj = (uint32_t)cur.id;
+      if (kPol == kNearest) {
+        id_0 = id_1;
+        id_1 = id_2;
+        id_2 = cur.id;
+      }
       if (slot < s1 && (fl & kFMove)) {  // the re-jitter (stand-in for the MD between steps)
         if (fl & kFJit) rejitter(d, step, idj, cur.x, cur.y, cur.z);
         const uint32_t bo = (uint32_t)slot * 4u;  // 32-bit byte offsets: scalar-base stores
@@ -1309,7 +1326,6 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
       bool defer = false;
       if (slot < s1 && pol_t<kPol>(cur.role)) {
         defer = true;
-        if (kPol == kNearest) s_tid[lt] = (int)idj;
         if (fl & kFStaged) {
           if (kPol != kNearest) s_tid[lt] = (int)idj;
           const float px = cur.x, py = cur.y, pz = cur.z;
@@ -1363,14 +1379,21 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
     }
     __syncthreads();
     const Dev& d = fresh(d0);
+    // nearest selection, whole bricks: the pairs of a staged A (about five) are
+    // merged in LDS before the device-wide minimum, which is served beyond the
+    // chiplet's cache and bounds the queue of a full chip (64 steps at
+    // 1,048,576 particles with load and read-out 2.57 -> 2.48 ms).  Where bricks
+    // are shared among workgroups the chip is not full, and the minimum comes
+    // sooner without (137,899 particles, 218 steps: 4.27 ms, merged 4.31).
+    const bool merge_a = kPol == kNearest && d.wshift == 0;
     // the pass's queued pairs: draws (or keys) on full wavefronts
     const int qn = min(s_qn, kQueue);
     for (int e = tid; e < qn; e += kThreads) {
       const uint32_t q = s_q[e];
       if (q == kQEmpty) continue;
       const uint32_t lt = q & 1023u, r = scan_record(s_blk[(q >> 10) & 1023u], q >> 20);
-      const uint32_t idj = (uint32_t)s_tid[lt];
       const int sj = base + (int)lt;
+      const uint32_t idj = (uint32_t)(kPol == kNearest ? a.id[sj] : s_tid[lt]);
       const int4* arow = d.adj_staged && !kF ? &s_radj[r] : nullptr;
       // the exact test, on the T's position as this workgroup has just written
       // it (the draws meanwhile: few candidates fail it)
@@ -1378,6 +1401,12 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
       const int ida = __float_as_int(A.w), sa = s_rsa[r];
       const float tx = d.jitter ? XW[sj] : X[sj], ty = d.jitter ? YW[sj] : Y[sj],
                   tz = d.jitter ? ZW[sj] : Z[sj];
+      // the nearest selection tests every pair's exclusion, several rules its T's
+      // role: what they read is under way with the position
+      const bool row_ahead = kPol == kNearest && d.rule.exclude && !arow && d.B <= kAdjStage;
+      int4 row = make_int4(-1, -1, -1, -1);
+      if (row_ahead) row = row_load(a.adj + (size_t)sa * d.B, d.B);
+      const uint32_t rt = kPol == kMulti ? a.role[sj] & kMaskT : 0u;
       W4 w4{0u, 0u, 0u, 0u};
       if (kPol == kRandom) w4 = philox(step, (uint32_t)ida, idj, 0u, d.seed);
       const float r2 = dist2(d, tx, ty, tz, A);
@@ -1385,10 +1414,14 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
       if (kPol != kMulti) count_one(&s_cnt[kOutInRc]);  // several rules: counted per rule
       if (kPol == kRandom)
         retain(d, a, w4, ida, sa, idj, sj, arow, s_cnt, rl);
-      else if (kPol == kNearest)
-        near_pair(d, a, ida, sa, idj, r2, arow, s_cnt, &s_best[lt]);
-      else
-        multi_pair(d, a, step, a.role[sj] & kMaskT, ida, sa, idj, sj, r2, arow, s_cnt, rl);
+      else if (kPol == kNearest) {
+        const bool excl = row_ahead ? row.x == (int)idj || row.y == (int)idj ||
+                                          row.z == (int)idj || row.w == (int)idj
+                                    : d.rule.exclude && pair_bonded(d, a, sa, idj, arow);
+        if (merge_a) near_pair(ida, idj, r2, excl, s_cnt, &s_best_a[r], &s_best[lt]);
+        else near_pair(ida, idj, r2, excl, s_cnt, &d.slotA[ida], &s_best[lt]);
+      } else
+        multi_pair(d, a, step, rt, ida, sa, idj, sj, r2, arow, s_cnt, rl);
     }
     // the deferred T's, eight lanes each, one cell of the block per lane: from
     // the staged records when the block lies in a staged region, else from the
@@ -1459,18 +1492,31 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
           retain(d, a, philox(step, (uint32_t)ida, idj, 0u, d.seed), ida, sa, idj, slot, arow,
                  s_cnt, rl);
         else if (kPol == kNearest)
-          near_pair(d, a, ida, sa, idj, r2, arow, s_cnt, &s_best[lt]);
+          near_pair(ida, idj, r2, d.rule.exclude && pair_bonded(d, a, sa, idj, arow), s_cnt,
+                    &d.slotA[ida], &s_best[lt]);
         else
           multi_pair(d, a, step, rt, ida, sa, idj, slot, r2, arow, s_cnt, rl);
       }
     }
     __syncthreads();
-    if (kPol == kNearest) {  // every T of the pass with a candidate: its closest A, its slot
-      for (int q = tid; q < kTP; q += kThreads) {
-        const unsigned long long b = s_best[q];
+    if (kPol == kNearest) {
+      // the staged A's with a candidate: one global minimum each
+      for (int q = tid; merge_a && q < kStageRecs; q += kThreads) {
+        const unsigned long long b = s_best_a[q];
         if (b == kEmpty) continue;
-        d.tnear[s_tid[q]] = make_int2((int)(uint32_t)b, base + q);
-        s_best[q] = kEmpty;
+        atomicMin(&d.slotA[__float_as_int(s_rec[q].w)], b);
+        s_best_a[q] = kEmpty;
+      }
+      // every T of the pass with a candidate: its closest A, its slot
+      unsigned long long b[kPer];
+      const int t[kPer] = {id_0, id_1, id_2};
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) b[u] = s_best[u * kThreads + tid];
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        if (b[u] == kEmpty) continue;
+        d.tnear[t[u]] = make_int2((int)(uint32_t)b[u], base + u * kThreads + tid);
+        s_best[u * kThreads + tid] = kEmpty;
       }
     }
     if (tid == 0) {
@@ -1585,7 +1631,9 @@ __device__ __forceinline__ void dense_sweep_body(const Dev& d, int k, int w, int
     }
     const float r2 = dist2(d, s_pos[0][lt], s_pos[1][lt], s_pos[2][lt], A);
     if (kPol == kNearest)
-      near_pair(d, a, __float_as_int(A.w), sa, idj, r2, nullptr, s_cnt, &s_best[lt]);
+      near_pair(__float_as_int(A.w), idj, r2,
+                d.rule.exclude && pair_bonded(d, a, sa, idj, nullptr), s_cnt,
+                &d.slotA[__float_as_int(A.w)], &s_best[lt]);
     else
       multi_pair(d, a, step, a.role[sj] & kMaskT, __float_as_int(A.w), sa, idj, sj, r2, nullptr, s_cnt,
                  rl);
