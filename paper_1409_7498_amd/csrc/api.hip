@@ -117,9 +117,14 @@ unsigned long long threshold(double p) {
 // particles 30.9 -> 30.45 us per step, the gap between the sweep and the next
 // kernel 2.8 -> 2.0 us; 4M particles, and the 4.5M of a 256-replica batch,
 // 2-3% slower (their positions leave the L2s during the kernel anyway).
-// Batches keep plain stores.
+// The random selection only: the queues of the others and their resolves read
+// the positions of many more pairs again (1M particles, 64 steps with load and
+// read-out, non-temporal and plain stores: nearest 2.46 and 2.33 ms, two rules
+// 2.34 and 2.33, random, 256 steps, 7.03 and 7.10).  Batches keep plain stores.
 constexpr int64_t kNtPosBytes = 16ll << 20;
-int32_t nt_positions(int64_t n) { return 12 * n <= kNtPosBytes ? 1 : 0; }
+int32_t nt_positions(int64_t n, int32_t policy) {
+  return policy == PR_POLICY_RANDOM && 12 * n <= kNtPosBytes ? 1 : 0;
+}
 
 int sweep_blocks(int32_t n) { return std::max(1, (n + kThreads - 1) / kThreads); }
 int prep_blocks(int32_t n) {
@@ -197,7 +202,7 @@ void set_geometry(Dev& d, int32_t n, float L, int32_t B, const pr_rule* r, uint6
   d.nwg_sweep = sweep_blocks(n);
   d.nwg_prep = prep_blocks(n);
   d.adj_staged = B <= kAdjStage ? 1 : 0;
-  d.nt_pos = nt_positions(n);
+  d.nt_pos = nt_positions(n, r->policy);
   d.k_limit = INT32_MAX;
   d.first_step = 0;
   d.jit_c = 0.0f;
@@ -246,6 +251,7 @@ void set_geometry_rules(Dev& d, int32_t n, float L, int32_t B, const pr_rule* ru
     return;
   }
   d.nrules = nrules;
+  d.nt_pos = 0;
   for (int32_t r = 0; r < nrules; ++r) {
     const pr_rule& q = rules[r];
     d.mr[r] = RuleX{RuleD{q.type_a, q.a_min, q.a_max, q.d_a, q.type_t, q.t_min, q.t_max, q.d_t,

@@ -1,6 +1,7 @@
 // kernels.hip -- HIP kernels of the reaction step for gfx950 (CDNA4, wave64).
 //
-// One reaction step is up to three kernels (Table I of the paper, steps 1-9, on
+// One reaction step is two kernels (sweep and resolve) where the sweep bins the
+// next step's A's, up to four elsewhere (Table I of the paper, steps 1-9, on
 // one GPU; the communication steps 4, 6 and 8 have nothing to exchange):
 //   k_prep     closes the previous step (counters, bond rows), bins the
 //              A-role particles into coarse cells of width >= 2 rc (record:
@@ -9,9 +10,9 @@
 //              between two buffers)
 //   k_sweep    every particle streams once with coalesced SoA loads (in brick
 //              order once the storage is sorted, the A records of the brick and
-//              its halo staged in LDS); in-range pairs (step 1) go to an LDS
-//              queue so that the keyed Philox draws (step 2) run on full
-//              wavefronts; each retained pair lowers its A's key (w1, id_T) by
+//              its halo staged in LDS); candidates go to an LDS queue so that
+//              the exact distance test (step 1) and the keyed Philox draws
+//              (step 2) run on full wavefronts; each retained pair lowers its A's key (w1, id_T) by
 //              a 64-bit atomicMin (steps 3-5) and joins the workgroup's list
 //   k_resolve  per sweep workgroup (one wavefront each), the listed pairs
 //              whose A chose their T; of those the smallest (w2, id_A) per T
@@ -1100,7 +1101,8 @@ __device__ __forceinline__ void rejitter(const Dev& d, uint32_t step, uint32_t i
 // kTwo: two region cells per thread while staging (brick edges above
 // kOneCellBrick); else one, with the smaller tables.
 // kF: fused binning (the sweep bins the next step's A records; sorted storage).
-// kNt: the re-jittered positions stored non-temporally (Dev::nt_pos).
+// kNt: the re-jittered positions stored non-temporally (Dev::nt_pos; random
+// selection only).
 // kPol: the selection (Policy).  The nearest selection and several rules need
 // a queued pair's distance: it is computed again from the T's position, just
 // written by this workgroup.  (Their pairs on full wavefronts from the queue
@@ -3739,8 +3741,7 @@ static hipError_t launch_selection(const Dev& d, int k, hipStream_t s, hipEvent_
   else if (pol == kMulti && !d.fuse)
     kern = two ? k_sweep<kMulti, true, false> : k_sweep<kMulti, false, false>;
   else if (pol == kMulti)
-    kern = two ? (d.nt_pos ? k_sweep<kMulti, true, true, true> : k_sweep<kMulti, true, true>)
-               : (d.nt_pos ? k_sweep<kMulti, false, true, true> : k_sweep<kMulti, false, true>);
+    kern = two ? k_sweep<kMulti, true, true> : k_sweep<kMulti, false, true>;
   else if (!d.fuse)
     kern = pol == kRandom ? (two ? k_sweep<kRandom, true, false> : k_sweep<kRandom, false, false>)
                           : (two ? k_sweep<kNearest, true, false> : k_sweep<kNearest, false, false>);
@@ -3748,8 +3749,7 @@ static hipError_t launch_selection(const Dev& d, int k, hipStream_t s, hipEvent_
     kern = two ? (d.nt_pos ? k_sweep<kRandom, true, true, true> : k_sweep<kRandom, true, true>)
                : (d.nt_pos ? k_sweep<kRandom, false, true, true> : k_sweep<kRandom, false, true>);
   else
-    kern = two ? (d.nt_pos ? k_sweep<kNearest, true, true, true> : k_sweep<kNearest, true, true>)
-               : (d.nt_pos ? k_sweep<kNearest, false, true, true> : k_sweep<kNearest, false, true>);
+    kern = two ? k_sweep<kNearest, true, true> : k_sweep<kNearest, false, true>;
   if (ev_sweep0) hipExtLaunchKernelGGL(kern, g, b, 0, s, ev_sweep0, ev_sweep1, 0, d, k);
   else kern<<<g, b, 0, s>>>(d, k);
   if (pol == kMulti) {
