@@ -376,8 +376,8 @@ def bench_row(args):
                                            "p=0.02 each; a step = re-jitter (sigma=%g) + "
                                            "reaction step over both rules" % (N, L, workload.RC,
                                                                                cfg.sigma),
-                               "row": "f2", "path": "graph replay (binning kernel, sweep, "
-                                                    "resolve, final kernels per step)"}})
+                               "row": "f2", "path": "graph replay (sweep, resolve, final "
+                                                    "kernels per step)"}})
     elif args.row == "f3":
         s = binding.System(cfg.N, cfg.L, cfg.B, cfg.rule(), cfg.seed, log_cap=2 * cfg.N,
                            stream=stream)
@@ -405,8 +405,8 @@ def bench_row(args):
                                  "bytes_per_launch": KIN_B_PER_PARTICLE * cfg.N},
                     "config": {"workload": "step growth N=%d after %d steps; 8 states, 16 "
                                            "distance bins" % (cfg.N, W), "row": "f3",
-                               "path": "median wall time of one call (binning, two kernels, "
-                                       "copy to host)"}})
+                               "path": "median wall time of one call (three kernels, the last "
+                                       "writes to host memory)"}})
     elif args.row == "f4":
         theta = args.md_theta
         s = binding.System(cfg.N, cfg.L, cfg.B, cfg.rule(), cfg.seed, log_cap=2 * cfg.N,
@@ -616,7 +616,7 @@ def main():
         "t_elig_per_step": n_t,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "k_sweep" if args.policy == "random" else "k_near_sweep",
+                     "kernel": "k_sweep",
                      "bytes_per_launch": sweep_bytes},
         "cpu_baseline": None,
     }

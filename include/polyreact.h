@@ -207,7 +207,8 @@ int pr_sys_create_multi(pr_sys** out, int32_t n, float L, int32_t B, const pr_ru
                         int32_t brick);
 
 /* The handle's geometry: coarse cells per side, effective brick edge and
- * number of bricks (= sweep workgroups once sorted).  Any output may be NULL. */
+ * number of bricks (once sorted, one sweep workgroup each, or two or four
+ * sharing a brick where there are few).  Any output may be NULL. */
 int pr_sys_geometry(pr_sys* s, int32_t* nc, int32_t* brick, int32_t* nbricks);
 void pr_sys_destroy(pr_sys* s);
 
@@ -321,9 +322,10 @@ int pr_sys_read(pr_sys* s, float* x, float* y, float* z, int32_t* state, int32_t
  * host memory, ordered by step and, within a step, by id_A (Table I, step 9);
  * *n receives the total logged (PR_ECAP if it exceeded the log capacity; rows
  * beyond it were dropped).  The order is made on the device, in place: the
- * log in HBM stays in that order and later steps append after it.  Takes
- * temporary device memory (about 24 bytes per logged row) from the stream's
- * memory pool.  Synchronises. */
+ * log in HBM stays in that order and later steps append after it.  A log whose
+ * steps were run in increasing order is ordered step by step without further
+ * memory; any other takes temporary device memory (about 24 bytes per logged
+ * row) from the stream's memory pool.  Synchronises. */
 int pr_sys_bonds(pr_sys* s, int32_t* out, int64_t cap, int64_t* n);
 
 /* Copies the per-step counters of the steps run since the last load (at most
