@@ -1431,9 +1431,8 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
     // in flight together).  They are few, and what bounds them is latency, at
     // the end of the last workgroups with nothing left to hide it: one lane each
     // walked the cells one after another, up to 5 us (1,048,576 particles, 256
-    // steps with load and read-out 7.45 ms, this 7.07; 262,144 with 60% A's, no
-    // brick staged, 1667 and 1399 us per step).  From the last thread down: the
-    // first wavefronts have the queue.
+    // steps with load and read-out 7.45 ms, this 7.07).  From the last thread
+    // down: the first wavefronts have the queue.
     const int ndef = s_ndef;
     for (int e = (kThreads - 1 - tid) >> 3; e < ndef; e += kThreads / 8) {
       const int lt = (int)s_def[e], slot = base + lt, sub = tid & 7;
@@ -1441,12 +1440,31 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
                   pz = d.jitter ? ZW[slot] : Z[slot];
       const uint32_t idj = (uint32_t)a.id[slot];
       const uint32_t rt = kPol == kMulti ? a.role[slot] & kMaskT : 0u;
-      const int lx0 = local_lo(px, d.inv_w, bx, nc), ly0 = local_lo(py, d.inv_w, by, nc),
-                lz0 = local_lo(pz, d.inv_w, bz, nc);
-      const bool in = staged && (uint32_t)lx0 < (uint32_t)(ex - 1) &&
-                      (uint32_t)ly0 < (uint32_t)(ey - 1) && (uint32_t)lz0 < (uint32_t)(ez - 1);
+      int lx0 = 0, ly0 = 0, lz0 = 0;
+      bool in = staged;
+      if (staged) {
+        lx0 = local_lo(px, d.inv_w, bx, nc);
+        ly0 = local_lo(py, d.inv_w, by, nc);
+        lz0 = local_lo(pz, d.inv_w, bz, nc);
+        in = (uint32_t)lx0 < (uint32_t)(ex - 1) && (uint32_t)ly0 < (uint32_t)(ey - 1) &&
+             (uint32_t)lz0 < (uint32_t)(ez - 1);
+      }
+      // a pair within the cutoff
+      auto take = [&](const float4& A, int sa, float r2, const int4* arow)
+                      __attribute__((always_inline)) {
+        const int ida = __float_as_int(A.w);
+        if (kPol != kMulti) count_one(&s_cnt[kOutInRc]);
+        if (kPol == kRandom)
+          retain(d, a, philox(step, (uint32_t)ida, idj, 0u, d.seed), ida, sa, idj, slot, arow,
+                 s_cnt, rl);
+        else if (kPol == kNearest)
+          near_pair(ida, idj, r2, d.rule.exclude && pair_bonded(d, a, sa, idj, arow), s_cnt,
+                    &d.slotA[ida], &s_best[lt]);
+        else
+          multi_pair(d, a, step, rt, ida, sa, idj, slot, r2, arow, s_cnt, rl);
+      };
       int q = 0;  // the lane's cell: its first staged record, or the cell
-      uint32_t nr = 0, no = 0;
+      uint32_t nr = 0;
       float4 A0 = make_float4(0.f, 0.f, 0.f, 0.f), A1 = A0;
       int32_t sa0 = 0, sa1 = 0;
       const size_t nn = (size_t)d.ncell;
@@ -1467,17 +1485,13 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
         sa1 = bk.sa[q + nn];
         nr = nr < (uint32_t)kCellCap ? nr : (uint32_t)kCellCap;
         if (nc == 1 && sub) nr = 0;  // one cell, not eight
-        no = (bk.novf + 7u - (uint32_t)sub) >> 3;
       }
-      for (uint32_t r = 0; r < nr + no; ++r) {
+      for (uint32_t r = 0; r < nr; ++r) {
         float4 A = A0;
         int32_t sa = sa0;
         if (in) {
           A = s_rec[q + r];
           sa = s_rsa[q + r];
-        } else if (r >= nr) {
-          A = bk.ovf[(r - nr) * 8u + (uint32_t)sub];
-          sa = bk.osa[(r - nr) * 8u + (uint32_t)sub];
         } else if (r == 1u) {
           A = A1;
           sa = sa1;
@@ -1486,18 +1500,28 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
           sa = bk.sa[q + r * nn];
         }
         const float r2 = dist2(d, px, py, pz, A);
-        if (!(r2 < d.rc2)) continue;
-        const int4* arow = in && d.adj_staged && !kF ? &s_radj[q + r] : nullptr;
-        const int ida = __float_as_int(A.w);
-        if (kPol != kMulti) count_one(&s_cnt[kOutInRc]);
-        if (kPol == kRandom)
-          retain(d, a, philox(step, (uint32_t)ida, idj, 0u, d.seed), ida, sa, idj, slot, arow,
-                 s_cnt, rl);
-        else if (kPol == kNearest)
-          near_pair(ida, idj, r2, d.rule.exclude && pair_bonded(d, a, sa, idj, arow), s_cnt,
-                    &d.slotA[ida], &s_best[lt]);
-        else
-          multi_pair(d, a, step, rt, ida, sa, idj, slot, r2, arow, s_cnt, rl);
+        if (r2 < d.rc2) take(A, sa, r2, in && d.adj_staged && !kF ? &s_radj[q + r] : nullptr);
+      }
+      // the overflow list (no brick is staged then), kOvfAhead records of the
+      // lane's eighth in flight: the long lists of crowded steps are walked at
+      // the latency of their reads (262,144 particles, half of them A's: 410 us
+      // per step, with one record and its slot at a time 560; one million, 15-20%
+      // A's, no list and no brick staged: within 4% of one lane per T)
+      constexpr uint32_t kOvfAhead = 4;
+      for (uint32_t r0 = (uint32_t)sub; r0 < bk.novf; r0 += 8u * kOvfAhead) {
+        float4 V[kOvfAhead];
+#pragma unroll
+        for (uint32_t u = 0; u < kOvfAhead; ++u) V[u] = bk.ovf[min(r0 + 8u * u, bk.novf - 1u)];
+        uint32_t hit = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < kOvfAhead; ++u)
+          hit |= r0 + 8u * u < bk.novf && dist2(d, px, py, pz, V[u]) < d.rc2 ? 1u << u : 0u;
+        while (hit) {
+          const uint32_t r = r0 + 8u * (uint32_t)(__ffs((int)hit) - 1);
+          hit &= hit - 1u;
+          const float4 A = bk.ovf[r];
+          take(A, bk.osa[r], dist2(d, px, py, pz, A), nullptr);
+        }
       }
     }
     __syncthreads();
