@@ -3067,7 +3067,8 @@ __global__ __launch_bounds__(kFinThreads) void k_single_finish(Dev d, uint32_t p
     if (p < kSortLds) s_b[p] = key;
     d.sortbuf[p] = key;
   };
-  int v[kPart] = {0, 0, 0, 0, 0, 0, 0, 0};
+  // in 64 bits: a wavefront adds up a sixteenth of all workgroups' counters
+  long long v[kPart] = {0, 0, 0, 0, 0, 0, 0, 0};
   constexpr int kAt = 4;  // sweep workgroups per thread and round, loaded together
   for (int w0 = tid; w0 < d.nwg_sweep; w0 += kAt * kFinThreads) {
     int nb[kAt];
@@ -3095,8 +3096,11 @@ __global__ __launch_bounds__(kFinThreads) void k_single_finish(Dev d, uint32_t p
   }
 #pragma unroll
   for (int q = 0; q < kPart; ++q) {
-    const uint32_t t = wave_scan_incl((uint32_t)v[q]);
-    if (__lane_id() == 63 && t) atomicAdd(&s_sum[q], (unsigned long long)t);
+    // 24 bits and (if any) the rest, so that neither sum of 64 lanes wraps
+    const uint32_t high = (uint32_t)(v[q] >> 24);
+    unsigned long long t = wave_scan_incl((uint32_t)v[q] & 0xFFFFFFu);
+    if (__ballot(high != 0u)) t += (unsigned long long)wave_scan_incl(high) << 24;
+    if (__lane_id() == 63 && t) atomicAdd(&s_sum[q], t);
   }
   for (int e = tid; e < nwov; e += kFinThreads) keep(pick(d.wov, par)[e]);
   __syncthreads();
