@@ -322,10 +322,11 @@ int pr_sys_read(pr_sys* s, float* x, float* y, float* z, int32_t* state, int32_t
  * host memory, ordered by step and, within a step, by id_A (Table I, step 9);
  * *n receives the total logged (PR_ECAP if it exceeded the log capacity; rows
  * beyond it were dropped).  The order is made on the device, in place: the
- * log in HBM stays in that order and later steps append after it.  A log whose
- * steps were run in increasing order is ordered step by step without further
- * memory; any other takes temporary device memory (about 24 bytes per logged
- * row) from the stream's memory pool.  Synchronises. */
+ * log in HBM stays in that order and later steps append after it.  Where steps
+ * were run in increasing order, the new ones since the last read (up to 4,096)
+ * are ordered one by one without further memory; else the log is sorted whole,
+ * in temporary device memory (about 24 bytes per logged row) from the stream's
+ * memory pool.  Synchronises. */
 int pr_sys_bonds(pr_sys* s, int32_t* out, int64_t cap, int64_t* n);
 
 /* Copies the per-step counters of the steps run since the last load (at most

@@ -41,8 +41,9 @@ hipError_t launch_block_end(const Dev& d, int K, hipStream_t s);
 hipError_t launch_single(const Dev& d, uint32_t step, uint32_t par, SingleOut* out, hipStream_t s);
 hipError_t launch_sort(const Dev& d, bool fresh, hipStream_t s);
 hipError_t log_order(int32_t* log, int64_t n, hipStream_t s);
-hipError_t launch_log_segs(const Dev& d, int K, uint32_t* seg, hipStream_t s);
-hipError_t launch_log_steps(const Dev& d, int k0, int K, const uint32_t* seg, hipStream_t s);
+hipError_t launch_log_segs(const Dev& d, int k0, int K, uint32_t row0, uint32_t* seg,
+                           hipStream_t s);
+hipError_t launch_log_steps(const Dev& d, int K, const uint32_t* seg, hipStream_t s);
 hipError_t launch_gather_out(const Dev& d, float* ox, float* oy, float* oz, int32_t* otyp,
                              int32_t* ost, int32_t* oadj, hipStream_t s);
 hipError_t launch_draws(const uint32_t* ctr, long long n, unsigned long long key, uint32_t* out,
@@ -664,11 +665,11 @@ struct pr_sys {
   int64_t steps_since_load = 0;
   int64_t steps_since_sort = 0;
   // the bond log: whether every run since the load began after the steps of
-  // the one before it (log_next), and the rows and steps ordered by the last
-  // read
+  // the one before it (log_next), the rows ordered by the last read, and the
+  // last read whose rows were all those of the steps so far: their numbers
   bool log_mono = true;
   uint32_t log_next = 0;
-  int64_t log_done = 0, log_done_steps = 0;
+  int64_t log_done = 0, log_base = 0, log_base_steps = 0;
   bool loaded = false;
   bool poisoned = false;
   int32_t sort_period = 0;
@@ -853,7 +854,7 @@ int load_end(pr_sys* s) {
   s->steps_since_load = 0;
   s->log_mono = true;
   s->log_next = 0;
-  s->log_done = s->log_done_steps = 0;
+  s->log_done = s->log_base = s->log_base_steps = 0;
   if (s->hctl->err) {
     s->loaded = false;
     return fail(s->hctl->err, "invalid particle position (NaN or outside [0, L))");
@@ -1623,24 +1624,39 @@ int pr_sys_read(pr_sys* s, float* x, float* y, float* z, int32_t* state, int32_t
 
 namespace {
 
+// The most new steps that a read of the bond log orders one by one: more of them
+// take longer than sorting the whole log, unless they hold many rows.  First
+// read after K steps, step by step and sorted whole, us: 60,000 particles (12,000
+// rows) K = 2,000 213-278 and 174-290, 8,000 505-657 and 145-560, 131,072
+// 1,080-1,260 and 212-422; 1,048,576 (160,000-209,000 rows) 4,000 654-695 and
+// 861-875, 8,000 797-856 and 753-841; 4,194,304 2,000 1,284-1,290 and
+// 1,358-1,413.
+constexpr int64_t kLogSteps = 4096;
+
 // The bond log in (step, id_A) order.  pin (may be NULL): pinned host memory
 // of pin_bytes for the device copy (else it goes straight to out).
 int sys_bonds(pr_sys* s, int32_t* out, int64_t cap, int64_t* n, void* pin, size_t pin_bytes) {
   int e = check_sys(s, false);
   if (e) return e;
   if (!n || (cap > 0 && !out)) return fail(PR_EINVAL, "NULL output");
-  // the first row of every step, when the log can be ordered step by step (in
-  // the overflow array, idle between runs)
-  const int64_t steps = s->steps_since_load;
+  // the first row of every step since the last read that had all rows, when
+  // these can be ordered step by step (in the overflow array, idle between runs)
+  const int64_t steps = s->steps_since_load, fresh = steps - s->log_base_steps;
   uint32_t* seg = (uint32_t*)s->d.ovf[0];
-  bool by_step = cap > 0 && s->log_mono && steps <= s->part_cap && steps < 4 * (int64_t)s->d.n;
-  if (by_step) HIP_TRY(launch_log_segs(s->d, (int)steps, seg, s->stream));
+  bool by_step = cap > 0 && s->log_mono && steps <= s->part_cap && steps <= INT32_MAX &&
+                 fresh < 4 * (int64_t)s->d.n && fresh <= kLogSteps;
+  if (by_step && fresh > 0)
+    HIP_TRY(launch_log_segs(s->d, (int)s->log_base_steps, (int)fresh, (uint32_t)s->log_base, seg,
+                            s->stream));
   if ((e = sync_ctl(s))) return e;
   const int64_t total = (int64_t)s->hctl->log_n;
   const int64_t have = std::min<int64_t>(total, s->log_cap);
   const int64_t m = std::min<int64_t>(have, cap);
-  by_step = by_step && total == have && s->hctl->log_rows == (uint64_t)total &&
-            (int64_t)s->hctl->stats_n0 == steps && s->hctl->log_most <= (uint32_t)kLogLds;
+  const bool whole = s->log_mono && total == have && (int64_t)s->hctl->stats_n0 == steps;
+  by_step = by_step && whole && total <= (int64_t)UINT32_MAX &&
+            (fresh > 0 ? s->log_base + (int64_t)s->hctl->log_rows == total &&
+                             s->hctl->log_most <= (uint32_t)kLogLds
+                       : s->log_base == total);
   if (m > 0) {
     // the rows of one step were appended in workgroup order: the device
     // orders the log in place by (step, id_A), the steps not ordered yet one
@@ -1649,11 +1665,10 @@ int sys_bonds(pr_sys* s, int32_t* out, int64_t cap, int64_t* n, void* pin, size_
       int32_t step, a, t;
     };
     if (by_step)
-      HIP_TRY(launch_log_steps(s->d, (int)s->log_done_steps, (int)steps, seg, s->stream));
+      HIP_TRY(launch_log_steps(s->d, (int)fresh, seg, s->stream));
     else if (have != s->log_done)
       HIP_TRY(log_order(s->d.log, have, s->stream));
     s->log_done = have;
-    s->log_done_steps = by_step ? steps : 0;
     Row* rows = pin && pin_bytes >= (size_t)m * sizeof(Row) ? (Row*)pin : (Row*)out;
     HIP_TRY(hipMemcpyAsync(rows, s->d.log, (size_t)m * sizeof(Row), hipMemcpyDeviceToHost,
                            s->stream));
@@ -1661,6 +1676,10 @@ int sys_bonds(pr_sys* s, int32_t* out, int64_t cap, int64_t* n, void* pin, size_
     if (s->d.nrules > 1)  // the rule of each bond rides in bits 30-31 of id_T
       for (size_t i = 0; i < (size_t)m; ++i) rows[i].t &= 0x3FFFFFFF;
     if (rows != (Row*)out) std::memcpy(out, rows, (size_t)m * sizeof(Row));
+  }
+  if (cap > 0 && whole) {
+    s->log_base = have;
+    s->log_base_steps = steps;
   }
   *n = total;
   if (total > s->log_cap)

@@ -67,7 +67,7 @@ struct Ctl {
   uint32_t stats_n0;   // counter-log index of the block's first step
   uint64_t log_n;      // rows appended to the bond log (may exceed capacity)
   uint32_t fovf_n[3];  // fused binning: A records beyond their bucket, by step mod 3
-  uint32_t log_most, log_rows;  // k_log_segs: the most rows of a step, rows of all steps
+  uint32_t log_most, log_rows;  // k_log_segs: the most rows of a step, rows of its steps
   uint32_t md_lone;    // MD: some adjacency row names a particle whose own row is empty
 };
 

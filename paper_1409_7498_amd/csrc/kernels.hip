@@ -3134,15 +3134,17 @@ __global__ __launch_bounds__(kFinThreads) void k_single_finish(Dev d, uint32_t p
 // Order of a resident system's bond log by (step, id_A) when the steps were
 // run in increasing order and no row was dropped: the rows of each step then lie
 // together, as many as its counters say, and only need their order by id_A.
-// k_log_segs finds the first row of every step (seg[0 .. K]) from the counter
-// log and leaves the most rows of a step in ctl->log_most; k_log_steps sorts
-// the rows of step k0 + blockIdx.x in LDS, in place.  Bound by latency (two
+// k_log_segs finds the first row of each of the K steps from k0 on (seg[0 .. K],
+// step k0's is row0) from the counter log and leaves the most rows of a step
+// and the rows of all in ctl->log_most and log_rows; k_log_steps sorts the rows
+// of step blockIdx.x of these in LDS, in place.  Bound by latency (two
 // launches; the steps are sorted beside each other).  It replaces a radix sort
 // of the whole log (eight passes over 64-bit keys) for logs of up to kLogLds
 // rows per step: 13 launches; a system of 4,000 particles after 200 steps read
 // its bonds in 80 us, now 54.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kFinThreads) void k_log_segs(Dev d, int K, uint32_t* seg) {
+__global__ __launch_bounds__(kFinThreads) void k_log_segs(Dev d, int k0, int K, uint32_t row0,
+                                                           uint32_t* seg) {
   __shared__ uint32_t s_wave[kFinThreads / 64 + 1];
   __shared__ uint32_t s_most;
   if (threadIdx.x == 0) s_most = 0;
@@ -3151,26 +3153,27 @@ __global__ __launch_bounds__(kFinThreads) void k_log_segs(Dev d, int K, uint32_t
     const int k = base + (int)threadIdx.x;
     uint32_t v = 0;
     if (k < K) {
-      const int32_t* p = d.part + (size_t)k * d.ngroups * kPart + 6;  // the bonds of each group
+      // the bonds of each group
+      const int32_t* p = d.part + (size_t)(k0 + k) * d.ngroups * kPart + 6;
       for (int g = 0; g < d.ngroups; ++g) v += (uint32_t)p[g * kPart];
     }
     uint32_t total = 0;
     const uint32_t ex = block_scan_excl<kFinThreads>(v, s_wave, total);
-    if (k < K) seg[k] = carry + ex;
+    if (k < K) seg[k] = row0 + carry + ex;
     carry += total;
     if (v) atomicMax(&s_most, v);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    seg[K] = carry;
+    seg[K] = row0 + carry;
     d.ctl->log_most = s_most;
     d.ctl->log_rows = carry;
   }
 }
 
-__global__ __launch_bounds__(kThreads) void k_log_steps(Dev d, int k0, const uint32_t* seg) {
+__global__ __launch_bounds__(kThreads) void k_log_steps(Dev d, const uint32_t* seg) {
   __shared__ unsigned long long s_b[kLogLds];
-  const uint32_t r0 = seg[k0 + blockIdx.x], r1 = seg[k0 + blockIdx.x + 1];
+  const uint32_t r0 = seg[blockIdx.x], r1 = seg[blockIdx.x + 1];
   const int m = (int)(r1 - r0);
   if (m < 2 || m > kLogLds) return;
   int32_t* row = d.log + 3 * (size_t)r0;
@@ -3915,13 +3918,14 @@ hipError_t launch_gather_out(const Dev& d, float* ox, float* oy, float* oz, int3
   return hipGetLastError();
 }
 
-hipError_t launch_log_segs(const Dev& d, int K, uint32_t* seg, hipStream_t s) {
-  k_log_segs<<<1, kFinThreads, 0, s>>>(d, K, seg);
+hipError_t launch_log_segs(const Dev& d, int k0, int K, uint32_t row0, uint32_t* seg,
+                           hipStream_t s) {
+  k_log_segs<<<1, kFinThreads, 0, s>>>(d, k0, K, row0, seg);
   return hipGetLastError();
 }
 
-hipError_t launch_log_steps(const Dev& d, int k0, int K, const uint32_t* seg, hipStream_t s) {
-  if (K > k0) k_log_steps<<<K - k0, kThreads, 0, s>>>(d, k0, seg);
+hipError_t launch_log_steps(const Dev& d, int K, const uint32_t* seg, hipStream_t s) {
+  if (K > 0) k_log_steps<<<K, kThreads, 0, s>>>(d, seg);
   return hipGetLastError();
 }
 
