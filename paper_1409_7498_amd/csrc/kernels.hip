@@ -2558,9 +2558,10 @@ __device__ __forceinline__ bool md_bond(const Dev& d, float4 p, float4 o, float&
   return true;
 }
 
-// The compact index of partner id j (-1: none).
+// The compact index of partner id j (-1: none; an entry that names no particle,
+// which a loaded row may hold, is no bond).
 __device__ __forceinline__ int32_t md_index(const Dev& d, int32_t j) {
-  return j >= 0 ? d.rank[d.slot_of[j]] : -1;
+  return (uint32_t)j < (uint32_t)d.n ? d.rank[d.slot_of[j]] : -1;
 }
 
 __global__ __launch_bounds__(kThreads) void k_md_sub(Dev d, int k, int m) {
@@ -2644,7 +2645,7 @@ __global__ __launch_bounds__(kThreads) void k_md_check(Dev d) {
   const int32_t* adj = pick_set(d, d.ctl->set & 1u).adj;
   for (int b = 0; b < d.B; ++b) {
     const int32_t j = adj[(size_t)i * d.B + b];
-    if (j < 0) continue;
+    if ((uint32_t)j >= (uint32_t)d.n) continue;  // names no particle
     const int32_t* row = adj + (size_t)d.slot_of[j] * d.B;
     bool empty = true;
     for (int e = 0; e < d.B; ++e) empty &= row[e] < 0;
