@@ -267,7 +267,8 @@ int pr_sys_prepare(pr_sys* s, uint32_t n_steps, double sigma);
  * Irwin-Hall(4) offset of the bytes of word d of the Philox block (0, id,
  * 0, 6) under vseed, times fl32(sqrt(temp / 21845)).  pr_sys_run then needs
  * sigma = 0.  theta = 0 switches back to the re-jitter.  A bond stretched to
- * 2 sc or beyond is reported as PR_EINVAL by the next synchronising call.
+ * 2 sc or beyond, and a particle that a drift of L or more leaves outside the
+ * box, is reported as PR_EINVAL by the next synchronising call.
  * Call after pr_sys_load / pr_sys_generate.  Synchronises. */
 int pr_sys_set_md(pr_sys* s, int32_t theta, double dt, double sig, double eps, double temp,
                   uint64_t vseed);

@@ -2456,6 +2456,12 @@ __device__ __forceinline__ void multi_final_body(const Dev& d, int k, int wg, in
 // kernel over all particles per MD step took 11 x 15.5 us; k_md_free 18 us
 // and 11 x 4.6 us.
 // ---------------------------------------------------------------------------
+// Whether the MD left a particle in the box: a drift of a box length or more is
+// not undone by the single wrap, and a position outside has no cell.
+__device__ __forceinline__ bool in_box(const Dev& d, float x, float y, float z) {
+  return x >= 0.0f && x < d.L && y >= 0.0f && y < d.L && z >= 0.0f && z < d.L;
+}
+
 __global__ __launch_bounds__(kThreads) void k_md_free(Dev d, int k) {
   __shared__ int32_t s_slot[kThreads * kMdPer];  // the workgroup's bonded slots
   __shared__ int s_n;
@@ -2501,6 +2507,7 @@ __global__ __launch_bounds__(kThreads) void k_md_free(Dev d, int k) {
       if (bonded[u]) s_slot[at + (int)lanes_below(m)] = i0 + u * kThreads;
     }
   }
+  bool inside = true;
 #pragma unroll
   for (int u = 0; u < kMdPer; ++u) {
     const int i = i0 + u * kThreads;
@@ -2516,6 +2523,7 @@ __global__ __launch_bounds__(kThreads) void k_md_free(Dev d, int k) {
       py = wrap_box(__fadd_rn(py, sy), d.L);
       pz = wrap_box(__fadd_rn(pz, sz), d.L);
     }
+    inside &= in_box(d, px, py, pz);
     X[i] = px;
     Y[i] = py;
     Z[i] = pz;
@@ -2523,6 +2531,7 @@ __global__ __launch_bounds__(kThreads) void k_md_free(Dev d, int k) {
     a.vy[i] = wy;
     a.vz[i] = wz;
   }
+  if (!inside) set_err(d.ctl, PR_EINVAL);
   __syncthreads();
   const int nb = s_n, q0 = blockIdx.x * (kThreads * kMdPer);
   if (threadIdx.x == 0) d.md_n[blockIdx.x] = nb;
@@ -2626,6 +2635,7 @@ __global__ __launch_bounds__(kThreads) void k_md_sub(Dev d, int k, int m) {
                           wrap_box(__fadd_rn(p.z, __fmul_rn(d.md_dt, vz)), d.L), 0.0f);
       d.md_vel[q] = make_float4(vx, vy, vz, v4.w);
     } else {
+      if (!in_box(d, p.x, p.y, p.z)) set_err(d.ctl, PR_EINVAL);
       pick(a.x, par)[slot] = p.x;
       pick(a.y, par)[slot] = p.y;
       pick(a.z, par)[slot] = p.z;
