@@ -2769,15 +2769,18 @@ __device__ __forceinline__ Buckets kin_buckets(const Dev& d, const Ctl* c, uint3
 __global__ __launch_bounds__(kThreads) void k_kin_pairs(Dev d, int nstate, int nbins, double rc,
                                                         unsigned long long* __restrict__ kin) {
   __shared__ KinLds s_kin;
+  const Ctl* c = d.ctl;
+  // after an error positions may be outside the box: nothing is counted, and the
+  // end reports it
+  const bool dead = read_err(c) != 0;
   kin_init(s_kin, nstate, nbins, rc);
   __syncthreads();
   const float scale = nbins > 0 ? (float)nbins / __fsqrt_rn(d.rc2) : 0.0f;
-  const Ctl* c = d.ctl;
   const uint32_t par = c->par0;
   const Arr a = pick_set(d, c->set & 1u);
   const float *X = pick(a.x, par), *Y = pick(a.y, par), *Z = pick(a.z, par);
   const Buckets bk = kin_buckets(d, c, par);
-  for (int slot = blockIdx.x * blockDim.x + threadIdx.x; slot < d.n;
+  for (int slot = blockIdx.x * blockDim.x + threadIdx.x; slot < d.n && !dead;
        slot += gridDim.x * blockDim.x) {
     kin_count_pop(d, s_kin, nstate, a.typ[slot], a.st[slot]);
     if (a.role[slot] != kRoleT) continue;
@@ -2812,10 +2815,11 @@ __global__ __launch_bounds__(kThreads) void k_kin_pairs_staged(
   __shared__ uint16_t s_def[kTPass];  // T's handled one by one
   __shared__ int s_qn, s_ndef;
   const int tid = threadIdx.x;
+  const Ctl* c = d.ctl;
+  const bool dead = read_err(c) != 0;  // as above
   kin_init(s_kin, nstate, nbins, rc);
   if (tid == 0) s_qn = s_ndef = 0;
   const float scale = nbins > 0 ? (float)nbins / __fsqrt_rn(d.rc2) : 0.0f;
-  const Ctl* c = d.ctl;
   const uint32_t par = c->par0;
   const Arr a = pick_set(d, c->set & 1u);
   const float *X = pick(a.x, par), *Y = pick(a.y, par), *Z = pick(a.z, par);
@@ -2830,7 +2834,7 @@ __global__ __launch_bounds__(kThreads) void k_kin_pairs_staged(
   g.off = s_off;
   stage_region(d, bk, w, g, s_wave);  // ends with a barrier (the tables above too)
   const bool rows = d.adj_staged != 0;
-  for (int base = s0; base < s1; base += kTPass) {
+  for (int base = s0; base < s1 && !dead; base += kTPass) {
     Part cur = load_part(a, X, Y, Z, base + tid, s1);
     int32_t typ = base + tid < s1 ? a.typ[base + tid] : 0, st = base + tid < s1 ? a.st[base + tid] : -1;
 #pragma unroll 1
