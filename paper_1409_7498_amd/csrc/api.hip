@@ -2114,6 +2114,20 @@ int pr_batch_create(pr_batch** out, const pr_replica_desc* reps, int32_t n_rep, 
   if (!out) return fail(PR_EINVAL, "out is NULL");
   *out = nullptr;
   if (n_rep < 1 || !reps) return fail(PR_EINVAL, "n_rep=%d", n_rep);
+  // every description is looked at before anything is sized by their number
+  int e = PR_OK;
+  bool fused = true;  // all of them can fuse: one rule, the random selection
+  for (int32_t r = 0; r < n_rep; ++r) {
+    const pr_replica_desc& q = reps[r];
+    if (q.n < 1 || q.n > kMaxParticles || q.B < 1) e = fail(PR_EINVAL, "n=%d B=%d", q.n, q.B);
+    else if (q.brick < 0 || q.brick > kMaxBrick) e = fail(PR_EINVAL, "brick=%d", q.brick);
+    else e = validate_rule(&q.rule, q.L);
+    if (e) {
+      const std::string msg = g_err;
+      return fail(e, "replica %d: %s", r, msg.c_str());
+    }
+    if (q.rule.policy == PR_POLICY_NEAREST) fused = false;
+  }
   pr_batch* b = new pr_batch();
   b->stream = (hipStream_t)stream;
   if (hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking) != hipSuccess ||
@@ -2122,22 +2136,8 @@ int pr_batch_create(pr_batch** out, const pr_replica_desc* reps, int32_t n_rep, 
     return fail(PR_EHIP, "hipStreamCreate/hipEventCreate failed");
   }
   // one device allocation for the arrays of all replicas (with their fused
-  // buckets when all of them can fuse: one rule, the random selection)
-  int e = PR_OK;
-  bool fused = true;
+  // buckets when all of them can fuse)
   std::vector<size_t> bytes((size_t)n_rep, 0);
-  for (int32_t r = 0; r < n_rep && !e; ++r) {
-    const pr_replica_desc& q = reps[r];
-    if (q.n < 1 || q.n > kMaxParticles || q.B < 1) e = fail(PR_EINVAL, "n=%d B=%d", q.n, q.B);
-    else if (q.brick < 0 || q.brick > kMaxBrick) e = fail(PR_EINVAL, "brick=%d", q.brick);
-    else e = validate_rule(&q.rule, q.L);
-    if (e) {
-      const std::string msg = g_err;
-      fail(e, "replica %d: %s", r, msg.c_str());
-    } else if (q.rule.policy == PR_POLICY_NEAREST) {
-      fused = false;
-    }
-  }
   char* slab = nullptr;
   for (int pass = fused ? 0 : 1; pass < 2 && !slab && !e; ++pass) {
     fused = pass == 0;  // without room for the buckets the batch runs unfused
