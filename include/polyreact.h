@@ -444,8 +444,10 @@ int pr_batch_kinetics(pr_batch* b, int32_t rep, int32_t nstate, int64_t* pop, in
                       int32_t nbins, int64_t* hist);
 
 
-/* Device bytes a resident system of this description allocates for a run of
- * n_steps steps (the admission measure of the server).  PR_EINVAL as
+/* Device bytes a served replica of this description takes for n_steps steps (the
+ * admission measure of the server).  A stand-alone handle (pr_sys_create) takes
+ * more: some 70 KB between each two of its large arrays, its fused-binning
+ * buckets and, where bricks are shared, their lists.  PR_EINVAL as
  * pr_sys_create. */
 int pr_footprint(const pr_replica_desc* r, uint32_t n_steps, int64_t* bytes);
 

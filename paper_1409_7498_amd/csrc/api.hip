@@ -1021,13 +1021,14 @@ int clear_system(const Dev& d, hipStream_t st) {
   return PR_OK;
 }
 
-// Steps the counter log of a new system holds.
+// Steps the counter log of a new system holds at least.
 constexpr int64_t kPartSteps = 1024;
 
-// The arrays of a new system (d: its geometry) and its first counter log.
+// The arrays of a new system (d: its geometry, part_cap: the steps its counter
+// log is to hold).
 int alloc_new(Arena& A, Dev& d, int64_t log_cap) {
   int e = alloc_system(A, d, d.n, d.B, log_cap);
-  if (!e) e = A.alloc(&d.part, (size_t)kPartSteps * d.ngroups * kPart);
+  if (!e) e = A.alloc(&d.part, (size_t)d.part_cap * d.ngroups * kPart);
   return e;
 }
 
@@ -1079,12 +1080,14 @@ namespace {
 // retired while other work runs, and a plain hipFree would wait for that
 // work).  A batch: a piece of its own allocation (slab), with room for the
 // fused buckets when fused is set.  Both: a pinned control word (allocating one
-// per system, and hipHostFree, wait for the device).
+// per system, and hipHostFree, wait for the device).  steps: what the system is
+// to run, so that its counter log need not grow.
 struct SysLease {
   hipMemPool_t pool = nullptr;
   char* slab = nullptr;
   size_t slab_bytes = 0;
   bool fused = false;
+  int64_t steps = 0;
   Ctl* hctl = nullptr;
 };
 
@@ -1126,6 +1129,7 @@ int sys_create(pr_sys** out, int32_t n, float L, int32_t B, const pr_rule* rule,
   set_geometry_rules(d, n, L, B, rule, nrules, seed, brick > 0 ? brick : kDefaultBrick);
   if (!lease) set_split(d, split_of(d));
   s->log_cap = log_cap > 0 ? log_cap : n;
+  d.part_cap = std::max(kPartSteps, lease ? lease->steps : 0);
   // one device allocation for all arrays: creating a system of 45 allocations
   // and freeing them took 1.2 ms (every hipFree waits for the device)
   Arena carve;
@@ -1147,8 +1151,7 @@ int sys_create(pr_sys** out, int32_t n, float L, int32_t B, const pr_rule* rule,
     delete s;
     return e;
   }
-  s->part_cap = kPartSteps;
-  d.part_cap = kPartSteps;
+  s->part_cap = d.part_cap;
   d.bonds = nullptr;
   d.bonds_cap = 0;
   d.log_cap = s->log_cap;
@@ -2146,6 +2149,7 @@ int pr_batch_create(pr_batch** out, const pr_replica_desc* reps, int32_t n_rep, 
       const pr_replica_desc& q = reps[r];
       Dev g{};
       set_geometry(g, q.n, q.L, q.B, &q.rule, q.seed, q.brick > 0 ? q.brick : kDefaultBrick);
+      g.part_cap = kPartSteps;
       bytes[(size_t)r] = new_bytes(g, q.log_cap > 0 ? q.log_cap : q.n, fused);
       all += bytes[(size_t)r];
     }
@@ -2489,10 +2493,10 @@ int srv_admit(pr_server* S, SrvReq* r) {
   pr_sys* s = nullptr;
   SysLease lease;
   lease.pool = S->pool;
+  lease.steps = r->n_steps;
   if (!(lease.hctl = srv_ctl(S))) return fail(PR_ENOMEM, "hipHostMalloc failed");
   int e = sys_create(&s, q.n, q.L, q.B, &q.rule, q.seed, q.log_cap, S->iostream, q.brick, &lease);
   if (!e) e = pr_sys_generate(s, q.gen_kind, q.gen_seed, q.gen_sigma0);
-  if (!e) e = grow_part(s, std::max<int64_t>(1024, r->n_steps));
   if (e) {
     if (s) pr_sys_destroy(s);  // a leased word is not the system's to free
     srv_put_ctl(S, lease.hctl);
