@@ -773,10 +773,10 @@ bool fuse_eligible(const pr_sys* s) {
 int alloc_buckets(Arena& A, Dev& d);
 
 // The fused-binning buckets, allocated (as one piece) on the first run that can
-// use them.
+// use them (one that sorts, without MD).
 int alloc_fused(pr_sys* s) {
   Dev& d = s->d;
-  if (d.fcnt[0] || !s->allow_fuse) return PR_OK;
+  if (d.fcnt[0] || !s->allow_fuse || d.md_theta > 0 || s->sort_period == 0) return PR_OK;
   Dev t = d;
   Arena dry;
   dry.dry = true;
