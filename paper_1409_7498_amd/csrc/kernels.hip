@@ -1173,11 +1173,13 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
   int ncs = 0;
   uint32_t mine = 0, mine2 = 0, m_exy = 0, m_ex = 0;
   int gc = 0, gc2 = 0;  // global cells of this thread's region cells
-  // global cell of region cell cl (region cells in z, y, x order)
   auto put_rec = [&](uint32_t r, const float4& v) {
     s_rec[r] = v;
-    s_qr[r] = quant(d, v.x, v.y, v.z);
+    // a dropped record's x is NaN, which has no integer: any position will do,
+    // the exact test lets no pair with it pass
+    s_qr[r] = quant(d, v.x == v.x ? v.x : 0.0f, v.y, v.z);
   };
+  // global cell of region cell cl (region cells in z, y, x order)
   auto region_cell = [&](int cl) {
     const int lz = div_small(cl, m_exy), rem = cl - lz * ex * ey;
     const int ly = div_small(rem, m_ex), lx = rem - ly * ex;
