@@ -27,6 +27,7 @@
 #include <sys/mman.h>
 
 #include "common.hpp"
+#include "scan_units.hpp"
 #include "../../include/polyreact.h"
 
 namespace pr {
@@ -155,25 +156,6 @@ int32_t split_of(const Dev& d) {
   return d.nbricks <= 256 ? (d.n / d.nbricks < 384 ? 1 : 2) : d.nbricks <= 512 ? 1 : 0;
 }
 
-// The scan's units (see scan_block): L / 2^m with m from 16 (the integers wrap at
-// 2^16 and the box at a multiple of it) to 22 (positions times 2^m / L keep
-// their FP32 rounding below two units), the cutoff 4096 to 8191 units where that
-// allows.  The threshold lets every pair through that the FP32 test can accept:
-// the truncations move a component difference by less than one unit, the
-// rounding of the two products by less than 2^(m - 22), that of the FP32
-// distance itself by less than 2^-20 of the cutoff and 2^(m - 23) units.
-void set_quant(Dev& d, float L, float rc) {
-  int m = 16;
-  while (m < 22 && (double)rc / (double)L * (double)(1u << m) < 4096.0) ++m;
-  d.qscale = (float)((double)(1u << m) / (double)L);
-  const double e = 1.0 + std::ldexp(1.0, m - 21);
-  const double r = (double)rc / (double)L * (double)(1u << m) * (1.0 + 1.0 / (1 << 16)) + 2.0 * e;
-  d.qthr = (uint32_t)std::min(std::ceil(r * r), 4294967295.0);
-  // near the smallest FP32 numbers the FP32 test itself is that coarse: every
-  // pair of a block is a candidate
-  if (rc * rc < 1e-30f) d.qthr = 4294967295u;
-}
-
 // Coarse A grid: nc cells per side of width L/nc >= 2 rc (1 + 2^-10); the
 // margin keeps the 2x2x2 block exact under FP32 rounding of the cell index.
 // Bricks of bs^3 cells; the staged region (bs + 2 cells per side) must not
@@ -185,7 +167,9 @@ void set_geometry(Dev& d, int32_t n, float L, int32_t B, const pr_rule* r, uint6
   d.L = L;
   d.halfL = 0.5f * L;
   d.rc2 = r->rc * r->rc;
-  set_quant(d, L, r->rc);
+  const ScanUnits u = scan_units(L, r->rc);
+  d.qscale = u.scale;
+  d.qthr = u.thr;
   long long nc = (long long)std::floor((double)L / (2.0 * (double)r->rc * (1.0 + 1.0 / 1024.0)));
   if (nc < 1) nc = 1;
   const long long cell_cap = std::max<long long>(2LL * n, 4096LL);

@@ -13,7 +13,7 @@ PKG = os.path.dirname(HERE)
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libpolyreact.so")
 SOURCES = ["kernels.hip", "api.hip", "logsort.hip"]
-HEADERS = ["common.hpp", os.path.join("..", "..", "include", "polyreact.h")]
+HEADERS = ["common.hpp", "scan_units.hpp", os.path.join("..", "..", "include", "polyreact.h")]
 
 HIPFLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-ffp-contract=off",
             "-fno-fast-math", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

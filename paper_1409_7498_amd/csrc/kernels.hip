@@ -955,7 +955,7 @@ __device__ __forceinline__ void multi_pair(const Dev& d, const Arr& a, uint32_t 
 // around exactly where the box does and their differences need no minimum
 // image), two packed subtractions and two dot products give the squared
 // distance in those units, and every pair within the cutoff passes (Dev::qthr
-// allows for the rounding, set_quant).  The few others that pass (about 0.5%)
+// allows for the rounding, scan_units).  The few others that pass (about 0.5%)
 // fall at the exact FP32 test, which every candidate takes on full wavefronts
 // from the queue.  The four runs of two x-adjacent cells are one sequence: a
 // word D counts down in each of its bytes to the ends of the runs, the sign
