@@ -364,16 +364,16 @@ int pr_sys_set_sort_period(pr_sys* s, int32_t sort_period);
 int pr_sys_set_graphs(pr_sys* s, int32_t on);
 
 /* Fused binning (Table I step 1, the candidate search): enable = 1 (default)
- * lets a handle on sorted storage without MD skip the binning kernel: each step's sweep bins the A's of the next step
- * (at their positions re-jittered once more) into cell buckets of its own,
- * and the resolve drops or adds the A's whose roles its bonds change, so a
- * step is two kernels (three with several rules).  The buckets are allocated on the first run that can
- * use them (about 2 x 160 bytes per cell and 40 per particle) and filled by
- * the spatial sort; they hold the A's of one reaction step, so a run that
- * does not continue the previous one (another first_step or sigma, after
- * pr_sys_jitter or pr_sys_set_md) sorts first.  enable = 0: the binning
- * kernel runs before every sweep.  Results are identical.  PR_EINVAL for
- * enable outside {0, 1}. */
+ * lets a handle on sorted storage without MD skip the binning kernel: each
+ * step's sweep bins the A's of the next step (at their positions re-jittered
+ * once more) into cell buckets of its own, and the resolve drops or adds the
+ * A's whose roles its bonds change, so a step is two kernels (three with
+ * several rules).  The buckets are allocated on the first run that can use them
+ * (about 2 x 160 bytes per cell and 40 per particle) and filled by the spatial
+ * sort; they hold the A's of one reaction step, so a run that does not continue
+ * the previous one (another first_step or sigma, after pr_sys_jitter or
+ * pr_sys_set_md) sorts first.  enable = 0: the binning kernel runs before every
+ * sweep.  Results are identical.  PR_EINVAL for enable outside {0, 1}. */
 int pr_sys_set_fused_binning(pr_sys* s, int32_t enable);
 
 /* *active = 1 when the handle's next step uses fused binning (as the last run

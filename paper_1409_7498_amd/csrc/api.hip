@@ -2387,8 +2387,6 @@ struct pr_server {
 
 namespace {
 
-// The worker's results copy of a finished replica, then its device memory
-// freed.  Returns the error code (0 = done).
 // A pinned control word from the server's pool (worker thread; the
 // finisher returns words concurrently, so both hold ctl_mu).
 Ctl* srv_ctl(pr_server* S) {
@@ -2412,6 +2410,8 @@ void srv_put_ctl(pr_server* S, Ctl* c) {
   S->ctl_free.push_back(c);
 }
 
+// The finisher's results copy of a finished replica, then its device memory
+// freed.  Returns the error code (0 = done).
 int srv_finish(pr_server* S, SrvReq* r) {
   pr_sys* s = r->sys;
   const size_t n = (size_t)r->desc.n, B = (size_t)r->desc.B;
@@ -2584,10 +2584,6 @@ void srv_fail(pr_server* S, SrvReq* r, int e) {
   S->n_failed++;
 }
 
-// The worker: round r + 1 is launched as soon as round r has ended; while it
-// runs, the requests that finished in round r are copied out and freed and
-// new requests are admitted (their generation runs on the I/O stream), to
-// join round r + 2.
 // The finisher: retires finished replicas in arrival order of completion.
 void fin_loop(pr_server* S) {
   (void)hipSetDevice(S->dev);
@@ -2620,6 +2616,10 @@ void fin_loop(pr_server* S) {
   }
 }
 
+// The worker: round r + 1 is launched as soon as round r has ended; while it
+// runs, the requests that finished in round r are copied out and freed (by the
+// finisher) and new requests are admitted (their generation runs on the I/O
+// stream), to join round r + 2.
 void srv_loop(pr_server* S) {
   (void)hipSetDevice(S->dev);
   std::vector<SrvReq*> incoming, finished;

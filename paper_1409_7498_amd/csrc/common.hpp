@@ -184,10 +184,10 @@ struct Dev {
   int32_t nrules;
   RuleX mr[kMaxRules];
   uint8_t *wfa, *wft;   // per slot: won as an A / as a T in this step (one writer each)
-  // fused binning (fuse = 1: sorted storage, no MD): the sweep of step k bins the A records of step k + 1 itself, so no
-  // binning kernel runs.  Counts by step mod 3 (read in step k, filled for
-  // k + 1, cleared for k + 2), bucket records and overflow by step parity;
-  // apos[slot]: where the A's record of the next step went (bucket index, or
+  // fused binning (fuse = 1: sorted storage, no MD): the sweep of step k bins
+  // the A records of step k + 1 itself, so no binning kernel runs.  Counts by
+  // step mod 3 (read in step k, filled for k + 1, cleared for k + 2), bucket
+  // records and overflow by step parity; apos[slot]: where the A's record of the next step went (bucket index, or
   // -1 - overflow index), for the resolve to drop it if the A's role ends
   int32_t fuse;
   // resident systems: the control block's parity origin (par0) as the host

@@ -337,8 +337,7 @@ __global__ void k_ctl_reset(Ctl* c, uint32_t step, int full) {
   }
 }
 
-// Position validation and the roles (after a load, and for the stateless
-// single step).
+// Position validation and the roles after a load.
 __global__ __launch_bounds__(kThreads) void k_classify(Dev d) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= d.n) return;
@@ -705,11 +704,6 @@ __device__ __forceinline__ int div_nb(const Dev& d, int w, int& r) {
 // instead of an integer division.
 __device__ __forceinline__ uint32_t recip16(uint32_t d) { return (65536u + d - 1u) / d; }
 __device__ __forceinline__ int div_small(int x, uint32_t m) { return (int)(((uint32_t)x * m) >> 16); }
-
-__device__ __forceinline__ int local_of(int c, int base, int nc) {
-  const int l = c - base;
-  return l < 0 ? l + nc : l;
-}
 
 // ---------------------------------------------------------------------------
 // Fused binning.  The sweep of step k writes the A records of step k + 1 into
@@ -1850,15 +1844,6 @@ struct BondOps {
   float tx, ty, tz;
 };
 
-__device__ __forceinline__ int4 load_row4(const int32_t* row, int B) {
-  int4 r = make_int4(0, 0, 0, 0);  // entries beyond B are not used
-  r.x = row[0];
-  if (B > 1) r.y = row[1];
-  if (B > 2) r.z = row[2];
-  if (B > 3) r.w = row[3];
-  return r;
-}
-
 // The slot adj_append would fill in a row read ahead (B when it is full).
 __device__ __forceinline__ int first_empty(int4 r, int B) {
   if (r.x < 0) return 0;
@@ -1902,23 +1887,20 @@ __device__ __forceinline__ void make_bond_ahead(const Dev& d, const Arr& a, uint
   }
 }
 
-// kWave: one wavefront per unit (four units per workgroup, unit = blockIdx.x
-// * 4 + wavefront); else the whole workgroup handles unit w.  Every barrier
-// is taken by the whole workgroup (mode is the same for all its units).
+// One wavefront per unit (four units per workgroup).  Every barrier is taken by
+// the whole workgroup (mode is the same for all its units).
 // kHostPar: the step's parity from Dev::kpar0 (resident systems), else from
 // the control block.
-template <bool kBrick, bool kWave, bool kHostPar = false>
-__device__ __forceinline__ void resolve_body(const Dev& d, int k, int w, int nunits) {
-  constexpr int kG = kWave ? kThreads / 64 : 1;  // units per workgroup
-  constexpr int kL = kWave ? 64 : kThreads;      // lanes per unit
+template <bool kBrick, bool kHostPar = false>
+__device__ __forceinline__ void resolve_body(const Dev& d, int k, int wg, int nunits) {
+  constexpr int kG = kThreads / 64;  // units per workgroup
   __shared__ int s_nw[kG], s_lost[kG], s_prop[kG];
   __shared__ int s_mode;
   __shared__ unsigned long long s_key[kG][kRetCap];
   __shared__ int32_t s_sj[kG][kRetCap];
-  const int g = kWave ? (int)(threadIdx.x >> 6) : 0;
-  const int tid = kWave ? (int)__lane_id() : (int)threadIdx.x;
-  if (kWave) w = w * kG + g;
-  const bool live = !kWave || w < nunits;  // the last workgroup's spare wavefronts
+  const int g = (int)(threadIdx.x >> 6), tid = (int)__lane_id();
+  const int w = wg * kG + g;
+  const bool live = w < nunits;  // the last workgroup's spare wavefronts
   const Ctl* c = d.ctl;
   const StepInfo si = step_info(c, k);
   const uint32_t par = kHostPar ? (d.kpar0 + (uint32_t)k) & 1u : si.par, step = si.step;
@@ -1957,8 +1939,8 @@ __device__ __forceinline__ void resolve_body(const Dev& d, int k, int w, int nun
         ops.stt = a.st[e.z];
         ops.tya = a.typ[e.y];
         ops.tyt = a.typ[e.z];
-        ops.rowa = load_row4(a.adj + (size_t)e.y * d.B, d.B);
-        ops.rowt = load_row4(a.adj + (size_t)e.z * d.B, d.B);
+        ops.rowa = row_load(a.adj + (size_t)e.y * d.B, d.B);
+        ops.rowt = row_load(a.adj + (size_t)e.z * d.B, d.B);
         if (d.fuse) {
           ops.apa = d.apos[e.y];
           ops.tx = pick(a.x, par ^ 1u)[e.z];
@@ -1991,7 +1973,7 @@ __device__ __forceinline__ void resolve_body(const Dev& d, int k, int w, int nun
     const Buckets bk = d.fuse ? step_buckets<true>(d, par, step) : step_buckets<false>(d, par, step);
     int s0, s1;
     range_of<kBrick>(d, w, s0, s1);
-    for (int base = s0; base < s1; base += kL) {
+    for (int base = s0; base < s1; base += 64) {
       const int slot = base + tid;
       if (slot < s1 && d.tflag[slot]) {
         d.tflag[slot] = 0;
@@ -2384,8 +2366,8 @@ __device__ __forceinline__ void multi_final_body(const Dev& d, int k, int wg, in
     BondOps o{a.st[sa], a.st[slot], a.typ[sa], a.typ[slot], make_int4(0, 0, 0, 0),
               make_int4(0, 0, 0, 0), 0, 0.0f, 0.0f, 0.0f};
     if (d.adj_staged) {
-      o.rowa = load_row4(a.adj + (size_t)sa * d.B, d.B);
-      o.rowt = load_row4(a.adj + (size_t)slot * d.B, d.B);
+      o.rowa = row_load(a.adj + (size_t)sa * d.B, d.B);
+      o.rowt = row_load(a.adj + (size_t)slot * d.B, d.B);
     }
     const W4 wd = philox(step, (uint32_t)ida, id, rule_tag(d, r), d.seed);
     bool keep = true;
@@ -3467,7 +3449,7 @@ __global__ __launch_bounds__(kThreads) void k_dense_sweep(Dev d, int k) {
 }
 template <bool kBrick>
 __global__ __launch_bounds__(kThreads) void k_resolve(Dev d, int k) {
-  resolve_body<kBrick, true, true>(d, k, blockIdx.x, d.nwg_sweep);
+  resolve_body<kBrick, true>(d, k, blockIdx.x, d.nwg_sweep);
 }
 template <bool kBrick>
 __global__ __launch_bounds__(kThreads) void k_near_resolve(Dev d, int k) {
@@ -3570,7 +3552,7 @@ __global__ __launch_bounds__(kThreads) void k_resolve_b(const Dev* __restrict__ 
   const int4 m = uniform_map(map);
   const Dev& d = ds[m.x];
   if (k >= d.k_limit || d.rule.policy != PR_POLICY_RANDOM) return;
-  resolve_body<true, true>(d, k, m.y, m.z);
+  resolve_body<true>(d, k, m.y, m.z);
 }
 __global__ __launch_bounds__(kThreads) void k_close_b(const Dev* __restrict__ ds,
                                                       const int4* __restrict__ map, int k) {
