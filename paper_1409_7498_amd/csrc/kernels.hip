@@ -1423,12 +1423,17 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
     }
     // the deferred T's, eight lanes each, one cell of the block per lane: from
     // the staged records when the block lies in a staged region, else from the
-    // buckets and the overflow list (a lane's count and its first two records
-    // in flight together).  They are few, and what bounds them is latency, at
-    // the end of the last workgroups with nothing left to hide it: one lane each
-    // walked the cells one after another, up to 5 us (1,048,576 particles, 256
-    // steps with load and read-out 7.45 ms, this 7.07).  From the last thread
-    // down: the first wavefronts have the queue.
+    // buckets and the overflow list.  They are few, and what bounds them is
+    // latency, at the end of the last workgroups with nothing left to hide it:
+    // one lane each walked the cells one after another, up to 5 us (1,048,576
+    // particles, 256 steps with load and read-out 7.45 ms, this 7.07).  A lane
+    // reads its count and first record together; what not every lane needs (a
+    // second record, the slots of pairs in range) is read when it does, as each
+    // is a request of its own: where nearly every T is deferred (particles that
+    // move a cutoff per step, 1,048,576 of them) these requests bound the sweep,
+    // 70 us per step, with two records and slots ahead 91, with one lane each
+    // and a cell's records in one line 75.  From the last thread down: the first
+    // wavefronts have the queue.
     const int ndef = s_ndef;
     for (int e = (kThreads - 1 - tid) >> 3; e < ndef; e += kThreads / 8) {
       const int lt = (int)s_def[e], slot = base + lt, sub = tid & 7;
@@ -1461,8 +1466,7 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
       };
       int q = 0;  // the lane's cell: its first staged record, or the cell
       uint32_t nr = 0;
-      float4 A0 = make_float4(0.f, 0.f, 0.f, 0.f), A1 = A0;
-      int32_t sa0 = 0, sa1 = 0;
+      float4 A0 = make_float4(0.f, 0.f, 0.f, 0.f);
       const size_t nn = (size_t)d.ncell;
       if (in) {
         const int lr = ((lz0 + (sub >> 2)) * ey + ly0 + ((sub >> 1) & 1)) * ex + lx0 + (sub & 1);
@@ -1476,27 +1480,19 @@ __device__ __forceinline__ void sweep_body(const Dev& d0, int k, int w, int nwg)
         q = (((sub & 4) ? cz1 : cz0) * nc + ((sub & 2) ? cy1 : cy0)) * nc + ((sub & 1) ? cx1 : cx0);
         nr = bk.cnt[q];
         A0 = bk.rec[q];
-        A1 = bk.rec[q + nn];
-        sa0 = bk.sa[q];
-        sa1 = bk.sa[q + nn];
         nr = nr < (uint32_t)kCellCap ? nr : (uint32_t)kCellCap;
         if (nc == 1 && sub) nr = 0;  // one cell, not eight
       }
       for (uint32_t r = 0; r < nr; ++r) {
         float4 A = A0;
-        int32_t sa = sa0;
-        if (in) {
-          A = s_rec[q + r];
-          sa = s_rsa[q + r];
-        } else if (r == 1u) {
-          A = A1;
-          sa = sa1;
-        } else if (r > 1u) {
-          A = bk.rec[q + r * nn];
-          sa = bk.sa[q + r * nn];
-        }
+        if (in) A = s_rec[q + r];
+        else if (r > 0u) A = bk.rec[q + r * nn];
         const float r2 = dist2(d, px, py, pz, A);
-        if (r2 < d.rc2) take(A, sa, r2, in && d.adj_staged && !kF ? &s_radj[q + r] : nullptr);
+        if (!(r2 < d.rc2)) continue;
+        int32_t sa;
+        if (in) sa = s_rsa[q + r];
+        else sa = bk.sa[q + r * nn];
+        take(A, sa, r2, in && d.adj_staged && !kF ? &s_radj[q + r] : nullptr);
       }
       // the overflow list (no brick is staged then), kOvfAhead records of the
       // lane's eighth in flight: the long lists of crowded steps are walked at
