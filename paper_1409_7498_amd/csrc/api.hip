@@ -799,6 +799,7 @@ void fuse_check_run(pr_sys* s, uint32_t first_step) {
 }
 
 void fuse_after_run(pr_sys* s, uint32_t first_step, uint32_t n_steps) {
+  if (n_steps == 0) return;  // nothing was binned
   s->rec_ok = s->d.sorted && s->d.fuse;
   s->rec_step = first_step + n_steps;
   s->rec_jit = s->d.jit_c;
