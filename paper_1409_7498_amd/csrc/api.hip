@@ -660,8 +660,9 @@ struct pr_sys {
   int32_t use_graphs = 1;
   // fused binning: allowed (pr_sys_set_fused_binning), and the step and
   // jitter scale the device's next-step A records were written for (rec_ok:
-  // they exist)
+  // they exist); wraps: the current run's step numbers pass 2^32 (see wraps_steps)
   int32_t allow_fuse = 1;
+  bool wraps = false;
   bool rec_ok = false;
   uint32_t rec_step = 0;
   float rec_jit = 0.0f;
@@ -674,6 +675,7 @@ struct pr_sys {
     hipGraphExec_t gexec = nullptr;
     int32_t steps = 0;
     bool sort = false;
+    bool fuse = false;  // a sort takes up fused binning
     Dev d{};
     uint64_t used = 0;
   };
@@ -748,10 +750,17 @@ void set_dense(pr_sys* s) {
 
 // Whether the sweeps of a sorted system can bin the next step's A's
 // themselves: no MD (the MD moves the particles between steps), the buckets
-// allocated.
+// allocated, step numbers that go on to 2^32.
 bool fuse_eligible(const pr_sys* s) {
   const Dev& d = s->d;
-  return s->allow_fuse && d.md_theta == 0 && d.fcnt[0] != nullptr;
+  return s->allow_fuse && d.md_theta == 0 && d.fcnt[0] != nullptr && !s->wraps;
+}
+
+// Whether steps first .. first + n - 1 and the two that their sweeps provide for
+// pass 2^32.  The fused counts rotate by the step number mod 3, and 2^32 is no
+// multiple of three: such a run bins every step's A's with the binning kernel.
+bool wraps_steps(uint32_t first, uint32_t n) {
+  return (uint64_t)first + n + 1 >= (1ull << 32);
 }
 
 int alloc_buckets(Arena& A, Dev& d);
@@ -788,7 +797,12 @@ int alloc_fused(pr_sys* s) {
 // device holds the A records of one step only (binned at their re-jittered
 // positions), so a run that does not continue the last one sorts (and bins
 // them again) first.
-void fuse_check_run(pr_sys* s, uint32_t first_step) {
+void fuse_check_run(pr_sys* s, uint32_t first_step, uint32_t n_steps) {
+  s->wraps = wraps_steps(first_step, n_steps);
+  if (s->wraps) {
+    s->d.fuse = 0;
+    s->rec_ok = false;
+  }
   if (!s->d.sorted || !s->d.fuse) return;
   if (s->rec_ok && s->rec_step == first_step && s->rec_jit == s->d.jit_c) return;
   if (s->sort_period > 0)
@@ -921,7 +935,8 @@ void after_segment(pr_sys* s, int32_t K, bool with_sort) {
 // with_sort), capturing it on the private stream if it is not cached.
 int segment_graph(pr_sys* s, int32_t K, bool with_sort, hipGraphExec_t* out) {
   for (pr_sys::Seg& g : s->segs)
-    if (g.steps == K && g.sort == with_sort && std::memcmp(&g.d, &s->d, sizeof(Dev)) == 0) {
+    if (g.steps == K && g.sort == with_sort && g.fuse == fuse_eligible(s) &&
+        std::memcmp(&g.d, &s->d, sizeof(Dev)) == 0) {
       g.used = ++s->seg_clock;
       *out = g.gexec;
       return PR_OK;
@@ -958,6 +973,7 @@ int segment_graph(pr_sys* s, int32_t K, bool with_sort, hipGraphExec_t* out) {
   seg.gexec = ge;
   seg.steps = K;
   seg.sort = with_sort;
+  seg.fuse = fuse_eligible(s);
   seg.used = ++s->seg_clock;
   s->segs.push_back(seg);
   std::memcpy((void*)&s->segs.back().d, (const void*)&s->d, sizeof(Dev));
@@ -1275,7 +1291,7 @@ static int run_impl(pr_sys* s, uint32_t first_step, uint32_t n_steps, double sig
   if ((e = grow_part(s, s->steps_since_load + n_steps))) return e;
   if ((e = alloc_fused(s))) return e;
   s->d.jit_c = (float)(sigma / std::sqrt(21845.0));  // unit-variance offsets
-  fuse_check_run(s, first_step);
+  fuse_check_run(s, first_step, n_steps);
   hipStream_t st = s->stream;
   HIP_TRY(launch_ctl_reset(s->d.ctl, first_step, 0, st));
   if (ms) {
@@ -1365,6 +1381,7 @@ int pr_sys_prepare(pr_sys* s, uint32_t n_steps, double sigma) {
   if ((e = grow_part(s, s->steps_since_load + n_steps))) return e;
   if ((e = alloc_fused(s))) return e;
   s->d.jit_c = (float)(sigma / std::sqrt(21845.0));
+  s->wraps = false;
   // walk the segments the run would take, capturing each, then restore the
   // host-side state (nothing ran)
   const Dev saved_d = s->d;
@@ -1995,6 +2012,7 @@ struct pr_batch {
   hipGraphExec_t gexec = nullptr;
   int32_t g_steps = 0;
   Ctl* hctl = nullptr;            // the replicas' pinned control words
+  bool fused = false;             // every replica has its fused buckets
   ~pr_batch() {
     if (gexec) (void)hipGraphExecDestroy(gexec);
     if (copied) (void)hipEventDestroy(copied);
@@ -2057,7 +2075,7 @@ int fill_maps(const std::vector<pr_sys*>& sys, Arena& arena, BatchLaunch& bl) {
   bl.two = two;
   bl.any_random = any_random;
   bl.any_nearest = any_nearest;
-  bl.fuse = 0;  // set by the batch when every replica has its fused buckets
+  bl.fuse = 0;  // set by the batch's runs when every replica has its fused buckets
   bl.res = mr;
   bl.n_res = (int)res.size();
   bl.nrep = (int)sys.size();
@@ -2175,7 +2193,7 @@ int pr_batch_create(pr_batch** out, const pr_replica_desc* reps, int32_t n_rep, 
     }
   }
   if (!e) e = fill_maps(b->sys, b->arena, b->bl);
-  b->bl.fuse = fused ? 1 : 0;
+  b->fused = fused;
   if (!e) e = b->arena.alloc(&b->ds, (size_t)n_rep);
   if (e) {
     delete b;
@@ -2203,6 +2221,13 @@ int pr_batch_run(pr_batch* b, uint32_t first_step, uint32_t n_steps, double sigm
       return fail(PR_EINVAL, "sigma=%g", sigma);
   }
   if (n_steps == 0) return PR_OK;
+  const int fuse = b->fused && !wraps_steps(first_step, n_steps) ? 1 : 0;
+  if (b->bl.fuse != fuse) {
+    HIP_TRY(hipStreamSynchronize(b->stream));  // the graph may still run
+    if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
+    b->gexec = nullptr;
+    b->bl.fuse = fuse;
+  }
   hipStream_t st = b->stream;
   HIP_TRY(hipEventSynchronize(b->copied));  // the staging copy of a previous run is done
   // the replicas' Devs as the batch's blocks leave them: storage sorted at
