@@ -297,9 +297,11 @@ struct Arena {
 // The stagger of a system's slab: where n is a power of two, arrays laid end to
 // end start a multiple of megabytes apart, and equal elements of all of them are
 // served by the same memory channels (the re-jitter alone, three arrays read and
-// three written at 1,048,576 particles: 7.4 us; 5.6 with this stagger, 5.8 with
-// 17 channel lines of 256 bytes, 5.7 in allocations of their own; 1,000,003
-// particles 5.5 to 5.7 in every layout).
+// three written at 1,048,576 particles, per step of pr_sys_jitter over 64 steps
+// launched behind each other: 7.4 us; 5.6-5.8 with this stagger, 5.8 with 17
+// channel lines of 256 bytes, 5.7 in allocations of their own; 1,000,003
+// particles 5.5 to 5.8 in every layout.  A single launch, stamped at its own
+// start and end, takes 7.7-8.2).
 constexpr size_t kStagger = 273 * 256;
 
 // Scratch of one step (everything but the particle arrays and the logs).

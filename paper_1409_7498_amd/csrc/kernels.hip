@@ -2434,7 +2434,9 @@ __device__ __forceinline__ void multi_final_body(const Dev& d, int k, int wg, in
 // its launch while few particles are bonded.  1,048,576 particles, ten MD
 // steps per reaction step, the first 32 reaction steps (up to 6% bonded): one
 // kernel over all particles per MD step took 11 x 15.5 us; k_md_free 18 us
-// and 11 x 4.6 us.
+// and 11 x 4.5-4.8 us.  Over 320 reaction steps k_md_sub takes 7.4 us on
+// average, 17 at most; with every particle bonded (1,030,301 in chains) a run of
+// 8 reaction steps takes 2.4 ms, 4.4 by the one kernel.
 // ---------------------------------------------------------------------------
 // Whether the MD left a particle in the box: a drift of a box length or more is
 // not undone by the single wrap, and a position outside has no cell.
@@ -3044,7 +3046,7 @@ __device__ __forceinline__ void put_bond(const Dev& d, int64_t t, unsigned long 
 // its round trips: the counters of 4 sweep workgroups per thread at 1M
 // particles are loaded together.  It replaces the closing, block-end and sort
 // kernels and two copies: 36 us of kernels at 1,000,003 particles (950 bonds),
-// now 17.5 us; 9 us at 4,000, now 5.
+// now 17.4-19.9 us; 9 us at 4,000, now 5.
 __global__ __launch_bounds__(kFinThreads) void k_single_finish(Dev d, uint32_t par, SingleOut* out) {
   __shared__ unsigned long long s_b[kSortLds];
   __shared__ unsigned long long s_sum[kPart];
@@ -3362,8 +3364,9 @@ __device__ __forceinline__ void sort_scatter_body(const Dev& d, int k) {
 // and one 8-byte one (type, state) per particle instead of seven 4- and 1-byte
 // stores, into the overflow arrays (idle at a sort), and the rows in place;
 // sort_unpack then writes the arrays in slot order.  Bound by the number of
-// scattered stores: 1,048,576 particles 113 us, now 59 us with the
-// unpacking; 4,194,304: 750 and 375.
+// scattered stores: 1,048,576 particles, rows of four, 113 us, now 51 and 12 us
+// for the unpacking (rows of two, two rules: 70 and 13); 4,194,304: 750 us, now
+// 348 and 35.
 __device__ __forceinline__ void sort_scatter_fresh_body(const Dev& d, int k) {
   if (k >= d.n) return;
   const uint32_t s = d.ctl->set & 1u, par = d.ctl->par0;
