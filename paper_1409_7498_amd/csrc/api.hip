@@ -2077,7 +2077,7 @@ int fill_maps(const std::vector<pr_sys*>& sys, Arena& arena, BatchLaunch& bl) {
   bl.two = two;
   bl.any_random = any_random;
   bl.any_nearest = any_nearest;
-  bl.fuse = 0;  // set by the batch's runs when every replica has its fused buckets
+  bl.fuse = 0;  // set by a batch whose replicas all have their fused buckets
   bl.res = mr;
   bl.n_res = (int)res.size();
   bl.nrep = (int)sys.size();
@@ -2196,6 +2196,7 @@ int pr_batch_create(pr_batch** out, const pr_replica_desc* reps, int32_t n_rep, 
   }
   if (!e) e = fill_maps(b->sys, b->arena, b->bl);
   b->fused = fused;
+  b->bl.fuse = fused ? 1 : 0;
   if (!e) e = b->arena.alloc(&b->ds, (size_t)n_rep);
   if (e) {
     delete b;
