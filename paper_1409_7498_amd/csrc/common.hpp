@@ -62,7 +62,7 @@ struct Ctl {
   int32_t err;         // first device-detected error (0 = none)
   uint32_t set;        // which of the two storage sets holds the particles
   uint32_t ovf_n[2];   // A records beyond their cell bucket, by parity
-  uint32_t ret_ovf[2];    // retained pairs beyond kRetCap (the resolve then re-enumerates)
+  uint32_t ret_ovf[2];    // some list overflowed kRetCap (the resolve then re-enumerates)
   uint32_t nwin_ovf[2];   // bonds beyond kWinCap, by parity
   uint32_t stats_n0;   // counter-log index of the block's first step
   uint64_t log_n;      // rows appended to the bond log (may exceed capacity)
