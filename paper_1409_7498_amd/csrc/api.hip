@@ -301,7 +301,7 @@ struct Arena {
 // launched behind each other: 7.4 us; 5.6-5.8 with this stagger, 5.8 with 17
 // channel lines of 256 bytes, 5.7 in allocations of their own; 1,000,003
 // particles 5.5 to 5.8 in every layout.  A single launch, stamped at its own
-// start and end, takes 7.7-8.2).
+// start and end, takes 7.3-8.2).
 constexpr size_t kStagger = 273 * 256;
 
 // Scratch of one step (everything but the particle arrays and the logs).
